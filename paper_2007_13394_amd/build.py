@@ -27,6 +27,7 @@ SOURCES = {
     "sort.hip": [],
     "adjoint.hip": [],
     "net.hip": [],
+    "net_bwd.hip": [],
     "host_cosmo.cpp": ["-ffp-contract=off", "-x", "hip"],
     "host.cpp": ["-x", "hip"],
 }

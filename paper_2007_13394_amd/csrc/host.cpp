@@ -104,7 +104,7 @@ int ilog2i(int v)
 
 struct Layout {
     size_t q, f, tw, flag, partial, tables, segtab, xs, ps, tags, ids, koff, cnt, bsum, cnt_next, total;
-    size_t net_phif, net_z1, net_a1, net_z2, net_a2, net_g1, net_g2, net_dpsi, net_dk, net_acc, net_table, net_tbar,
+    size_t net_phif, net_z1, net_a1, net_z2, net_a2, net_g1, net_g2, net_dk, net_acc, net_table, net_tbar,
         net_red, net_wpk;
     int64_t nkeys;
 };
@@ -167,7 +167,7 @@ Layout layout(const pm_config &c)
         L.cnt = s0;
         L.bsum = L.cnt + align256(4 * (size_t)(L.nkeys + 1));
     }
-    L.net_phif = L.net_z1 = L.net_a1 = L.net_z2 = L.net_a2 = L.net_g1 = L.net_g2 = L.net_dpsi = L.net_dk = 0;
+    L.net_phif = L.net_z1 = L.net_a1 = L.net_z2 = L.net_a2 = L.net_g1 = L.net_g2 = L.net_dk = 0;
     L.net_acc = L.net_table = L.net_tbar = L.net_red = L.net_wpk = 0;
     if (c.flags & PM_FLAG_LEARNED) {
         const size_t M = (size_t)(n * n * n);
@@ -179,7 +179,6 @@ Layout layout(const pm_config &c)
         L.net_a2 = take(M * pm::NET_C * 2);
         L.net_g1 = take(M * pm::NET_C * 4);
         L.net_g2 = take(M * pm::NET_C * 4);
-        L.net_dpsi = take(M * 4);
         L.net_dk = take((size_t)(n * n * nhp) * 8);
         L.net_acc = take((size_t)(3 * P) * 4);
         L.net_table = take(pm::NET_NB * 4);
@@ -562,9 +561,8 @@ pm_status learned_solve(pm_ctx *c, const float *th, double a, bool keep, hipStre
         LAUNCH(pm::K_COLS_INV, pm::launch_cols(lg, true, F + cs, n * nhp, nhp, n, ncb, c->ws.tw, s));
         LAUNCH(pm::K_COLS_INV, pm::launch_cols(lg, true, F + cs, nhp, n * nhp, n, ncb, c->ws.tw, s));
         LAUNCH(pm::K_C2R, pm::launch_c2r_rows(lg, F + cs, nhp, c->ws.net_phif, rs, n2, c->ws.tw, s));
-        LAUNCH(pm::K_NET, pm::launch_cnn_fwd(c->ws.q, qs, n, th, c->ws.net_z1, c->ws.net_a1, c->ws.net_z2,
-                                             c->ws.net_a2, c->ws.net_dpsi, s));
-        LAUNCH(pm::K_NET, pm::launch_combine(c->ws.net_phif, c->ws.net_dpsi, rs, n, Fr, s));
+        LAUNCH(pm::K_NET, pm::launch_cnn_fwd(c->ws.q, qs, c->ws.net_phif, rs, n, th, c->ws.net_wpk, c->ws.net_z1,
+                                             c->ws.net_a1, c->ws.net_z2, c->ws.net_a2, Fr, s));
         LAUNCH(pm::K_R2C, pm::launch_r2c_rows_f32(lg, Fr, rs, F, nhp, n2, c->ws.tw, s));
         LAUNCH(pm::K_COLS_FWD, pm::launch_cols(lg, false, F, nhp, n * nhp, n, ncb, c->ws.tw, s));
         LAUNCH(pm::K_COLS_FWD, pm::launch_cols(lg, false, F, n * nhp, nhp, n, ncb, c->ws.tw, s));
@@ -693,7 +691,6 @@ pm_status pm_init(const pm_config *cfg, void *workspace, size_t workspace_bytes,
         c->ws.net_a2 = reinterpret_cast<uint16_t *>(b + L.net_a2);
         c->ws.net_g1 = reinterpret_cast<float *>(b + L.net_g1);
         c->ws.net_g2 = reinterpret_cast<float *>(b + L.net_g2);
-        c->ws.net_dpsi = reinterpret_cast<float *>(b + L.net_dpsi);
         c->ws.net_dk = reinterpret_cast<float2 *>(b + L.net_dk);
         c->ws.net_acc = reinterpret_cast<float *>(b + L.net_acc);
         c->ws.net_table = reinterpret_cast<float *>(b + L.net_table);
@@ -1405,7 +1402,8 @@ pm_status pm_learned_loss(pm_ctx *c, const float *th, double a, const float *x, 
     LAUNCH(pm::K_COLS_INV, pm::launch_cols(lg, true, F, nhp, n * nhp, n, ncb, c->ws.tw, s));
     LAUNCH(pm::K_C2R, pm::launch_c2r_rows(lg, F, nhp, Fr, rs, n2, c->ws.tw, s));
     LAUNCH(pm::K_NET, pm::launch_cnn_bwd(c->ws.q, ldexp(1.0, -c->cfg.shift), Fr, rs, n, th, c->ws.net_z1,
-                                         c->ws.net_a1, c->ws.net_z2, c->ws.net_a2, c->ws.net_g1, c->ws.net_g2, dth, s));
+                                         c->ws.net_a1, c->ws.net_z2, c->ws.net_a2, c->ws.net_g1, c->ws.net_g2,
+                                         c->ws.net_wpk, dth, s));
     LAUNCH(pm::K_R2C, pm::launch_r2c_rows_f32(lg, Fr, rs, F, nhp, n2, c->ws.tw, s));
     LAUNCH(pm::K_COLS_FWD, pm::launch_cols(lg, false, F, nhp, n * nhp, n, ncb, c->ws.tw, s));
     LAUNCH(pm::K_COLS_FWD, pm::launch_cols(lg, false, F, n * nhp, nhp, n, ncb, c->ws.tw, s));

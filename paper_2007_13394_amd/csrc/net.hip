@@ -8,18 +8,12 @@
 // the int64 mesh); the force is minus the spectral gradient of phi_f + cnn.
 // Parameters: one flat FP32 array (offsets in pm_internal.h).  The CNN takes
 // BF16 activations and weights and accumulates in FP32; the 16 -> 16 layer,
-// 89 % of the network's arithmetic, runs on MFMA (16x16x16 BF16 tiles).
-#include <type_traits>
-
-#include "pm_internal.h"
+// 89 % of the network's arithmetic, runs on MFMA.  The CNN's reverse mode is in
+// net_bwd.hip.
+#include "net_common.h"
 
 namespace pm {
 namespace {
-
-typedef short v4s __attribute__((ext_vector_type(4)));
-typedef float v4f __attribute__((ext_vector_type(4)));
-typedef __bf16 v2bf __attribute__((ext_vector_type(2)));
-typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 
 // sum + a.lo b.lo + a.hi b.hi for BF16 pairs, FP32 accumulation
 __device__ __forceinline__ float dot2_bf16(uint32_t a, uint32_t b, float sum)
@@ -34,17 +28,6 @@ inline unsigned grid_for(int64_t n, int block, int64_t cap = 65536LL * 16)
     if (b < 1) b = 1;
     return (unsigned)b;
 }
-
-__device__ __forceinline__ float silu(float z) { return z * __builtin_amdgcn_rcpf(1.f + __expf(-z)); }
-__device__ __forceinline__ float dsilu(float z)
-{
-    const float s = 1.f / (1.f + __expf(-z));
-    return s + z * s * (1.f - s);
-}
-// round to the nearest BF16 (ties to even; the hardware conversion) and back
-__device__ __forceinline__ uint16_t to_bf16(float f) { return __builtin_bit_cast(uint16_t, (__bf16)f); }
-__device__ __forceinline__ float from_bf16(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
-__device__ __forceinline__ float bf16r(float f) { return from_bf16(to_bf16(f)); }
 
 __device__ __forceinline__ float bin_kt(int b) { return (float)b * 1.7320508075688772f / (float)(NET_NB - 1); }
 
@@ -261,147 +244,11 @@ __global__ void k_grad3_t(float2 *F, int64_t nhp, int64_t fs, int n, float scale
 
 // ---------------------------------------------------------------- convolutions
 // Voxel v = (i0 n + i1) n + i2; tap t = (t0 3 + t1) 3 + t2, offset t_e - 1.
-__device__ __forceinline__ int64_t nb_voxel(int i0, int i1, int i2, int t, int n)
-{
-    const int m = n - 1;
-    return ((int64_t)((i0 + t / 9 - 1) & m) * n + ((i1 + (t / 3) % 3 - 1) & m)) * n + ((i2 + t % 3 - 1) & m);
-}
+constexpr int C2X = 16, C2Y = 8, C2HX = C2X + 2, C2HY = C2Y + 2;
 
-// The CNN input: density contrast q 2^-S - 1 of the int64 mesh, rounded to BF16.
-__device__ __forceinline__ uint16_t delta_bf16(int64_t q, double qs) { return to_bf16((float)((double)q * qs - 1.0)); }
-
-// conv1: delta (int64 mesh q, quantum qs) rounded to BF16 -> z1 (FP32),
-// a1 = SiLU(z1) (BF16), 16 channels per voxel.
-__global__ __launch_bounds__(256) void k_conv1_fwd(const int64_t *__restrict__ q, double qs, int n,
-                                                   const float *__restrict__ th, float *z1, uint16_t *a1)
-{
-    __shared__ float W[NET_C * 27], B[NET_C];
-    for (int i = threadIdx.x; i < NET_C * 27; i += blockDim.x) W[i] = bf16r(th[NC1W + i]);
-    if (threadIdx.x < NET_C) B[threadIdx.x] = th[NC1B + threadIdx.x];
-    __syncthreads();
-    const int64_t M = (int64_t)n * n * n;
-    for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < M; v += (int64_t)gridDim.x * blockDim.x) {
-        const int i2 = (int)(v % n), i1 = (int)((v / n) % n), i0 = (int)(v / ((int64_t)n * n));
-        float x[27];
-#pragma unroll
-        for (int t = 0; t < 27; t++) {
-            x[t] = from_bf16(delta_bf16(q[nb_voxel(i0, i1, i2, t, n)], qs));
-        }
-        float z[NET_C];
-#pragma unroll
-        for (int co = 0; co < NET_C; co++) {
-            float acc = B[co];
-#pragma unroll
-            for (int t = 0; t < 27; t++) acc += W[co * 27 + t] * x[t];
-            z[co] = acc;
-        }
-#pragma unroll
-        for (int co = 0; co < NET_C; co += 4) {
-            *reinterpret_cast<float4 *>(z1 + v * NET_C + co) = make_float4(z[co], z[co + 1], z[co + 2], z[co + 3]);
-            const uint32_t lo = (uint32_t)to_bf16(silu(z[co])) | ((uint32_t)to_bf16(silu(z[co + 1])) << 16);
-            const uint32_t hi = (uint32_t)to_bf16(silu(z[co + 2])) | ((uint32_t)to_bf16(silu(z[co + 3])) << 16);
-            *reinterpret_cast<uint2 *>(a1 + v * NET_C + co) = make_uint2(lo, hi);
-        }
-    }
-}
-
-// conv2 (16 -> 16) on MFMA.  Workgroup tile: 16 (axis 2) x 8 (axis 1) x 4
-// (axis 0) voxels with its one-voxel halo in LDS as BF16 [z][y][x][16]; the
-// weights as BF16 [tap][co][ci].  Per 16-voxel row and tap one
-// v_mfma_f32_16x16x16_bf16: D[co][vox] += W_t[co][ci] X_t[ci][vox] (lane l
-// holds A[co = l % 16][ci = 4 (l / 16) + r], B[ci = 4 (l / 16) + r][vox = l % 16]
-// and D[co = 4 (l / 16) + r][vox = l % 16]).
-constexpr int C2X = 16, C2Y = 8, C2Z = 4, C2HX = C2X + 2, C2HY = C2Y + 2, C2HZ = C2Z + 2;
-constexpr int C2HALO = C2HX * C2HY * C2HZ;
-
-__global__ __launch_bounds__(256) void k_conv2_fwd(const uint16_t *__restrict__ a1, int n,
-                                                   const float *__restrict__ th, float *z2, uint16_t *a2)
-{
-    __shared__ __align__(16) uint16_t X[C2HALO * NET_C];
-    __shared__ __align__(16) uint16_t W[27 * NET_C * NET_C];
-    __shared__ float B[NET_C];
-    const int tid = threadIdx.x;
-    const int ntx = n / C2X, nty = n / C2Y;
-    const int tile = blockIdx.x;
-    const int tx = tile % ntx, ty = (tile / ntx) % nty, tz = tile / (ntx * nty);
-    const int x0 = tx * C2X, y0 = ty * C2Y, z0 = tz * C2Z, m = n - 1;
-    // weights [co][ci][t] (FP32) -> LDS [t][co][ci] (BF16)
-    for (int e = tid; e < 27 * NET_C * NET_C; e += 256) {
-        const int t = e / (NET_C * NET_C), co = (e / NET_C) % NET_C, ci = e % NET_C;
-        W[e] = to_bf16(th[NC2W + (co * NET_C + ci) * 27 + t]);
-    }
-    if (tid < NET_C) B[tid] = th[NC2B + tid];
-    // halo tile: two 16-byte chunks per voxel
-    for (int e = tid; e < C2HALO * 2; e += 256) {
-        const int hv = e >> 1, half = e & 1;
-        const int hx = hv % C2HX, hy = (hv / C2HX) % C2HY, hz = hv / (C2HX * C2HY);
-        const int64_t g = ((int64_t)((z0 + hz - 1) & m) * n + ((y0 + hy - 1) & m)) * n + ((x0 + hx - 1) & m);
-        reinterpret_cast<uint4 *>(X)[hv * 2 + half] = reinterpret_cast<const uint4 *>(a1 + g * NET_C)[half];
-    }
-    __syncthreads();
-    const int lane = tid & 63, wave = tid >> 6;
-    const int col = lane & 15, kg = lane >> 4;   // voxel within the row / co and ci group
-    for (int row = wave; row < C2Y * C2Z; row += 4) {
-        const int ry = row % C2Y, rz = row / C2Y;
-        v4f acc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll 3
-        for (int t = 0; t < 27; t++) {
-            const int dz = t / 9, dy = (t / 3) % 3, dx = t % 3;
-            const v4s wa = *reinterpret_cast<const v4s *>(W + (t * NET_C + col) * NET_C + 4 * kg);
-            const int hv = ((rz + dz) * C2HY + (ry + dy)) * C2HX + (col + dx);
-            const v4s xb = *reinterpret_cast<const v4s *>(X + hv * NET_C + 4 * kg);
-            acc = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(wa, xb, acc, 0, 0, 0);
-        }
-        // lane holds D[co = 4 kg + r][vox = col]
-        const int64_t v = ((int64_t)(z0 + rz) * n + (y0 + ry)) * n + (x0 + col);
-        float zz[4];
-        uint16_t aa[4];
-#pragma unroll
-        for (int r = 0; r < 4; r++) {
-            zz[r] = acc[r] + B[4 * kg + r];
-            aa[r] = to_bf16(silu(zz[r]));
-        }
-        *reinterpret_cast<float4 *>(z2 + v * NET_C + 4 * kg) = make_float4(zz[0], zz[1], zz[2], zz[3]);
-        *reinterpret_cast<uint2 *>(a2 + v * NET_C + 4 * kg) =
-            make_uint2((uint32_t)aa[0] | ((uint32_t)aa[1] << 16), (uint32_t)aa[2] | ((uint32_t)aa[3] << 16));
-    }
-}
-
-// conv3 (16 -> 1): out(v) = b + sum_{ci,t} W[ci][t] a2[v + o(t)][ci].
-__global__ __launch_bounds__(256) void k_conv3_fwd(const uint16_t *__restrict__ a2, int n,
-                                                   const float *__restrict__ th, float *out)
-{
-    __shared__ float W[27 * NET_C];   // [t][ci]
-    for (int e = threadIdx.x; e < 27 * NET_C; e += blockDim.x) {
-        const int t = e / NET_C, ci = e % NET_C;
-        W[e] = bf16r(th[NC3W + ci * 27 + t]);
-    }
-    __syncthreads();
-    const float b = th[NC3B];
-    const int64_t M = (int64_t)n * n * n;
-    for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < M; v += (int64_t)gridDim.x * blockDim.x) {
-        const int i2 = (int)(v % n), i1 = (int)((v / n) % n), i0 = (int)(v / ((int64_t)n * n));
-        float acc = b;
-        for (int t = 0; t < 27; t++) {
-            const int64_t u = nb_voxel(i0, i1, i2, t, n);
-            const uint4 *p = reinterpret_cast<const uint4 *>(a2 + u * NET_C);
-#pragma unroll
-            for (int h = 0; h < 2; h++) {
-                const uint4 q = p[h];
-                const uint32_t w4[4] = {q.x, q.y, q.z, q.w};
-#pragma unroll
-                for (int k = 0; k < 4; k++) {
-                    const int ci = h * 8 + 2 * k;
-                    acc += W[t * NET_C + ci] * from_bf16((uint16_t)(w4[k] & 0xffff)) +
-                           W[t * NET_C + ci + 1] * from_bf16((uint16_t)(w4[k] >> 16));
-                }
-            }
-        }
-        out[v] = acc;
-    }
-}
-
-// ---- inference path: no pre-activations kept, a1 never leaves LDS
+// ---- forward passes: in inference (KEEP false) no pre-activations are kept and
+// a1 never leaves LDS; training (KEEP true) also stores z1, a1 and z2, each
+// voxel's by the workgroup that owns it
 // conv1 + conv2 on v_mfma_f32_16x16x32_bf16 (K = 32; lane l holds
 // A[row l % 16][k 8 (l / 16) + j], B[k 8 (l / 16) + j][col l % 16] and
 // D[row 4 (l / 16) + r][col l % 16]).  The 16 x 8 x IZ output tile of conv2
@@ -451,46 +298,15 @@ __global__ __launch_bounds__(256) void k_pack_w(const float *__restrict__ th, ui
     }
 }
 
-// x / D for 0 <= x < N as one 24-bit multiply and a shift: v_mul_u32_u24 is
-// full rate, while the 32-bit multiplies that a division by a constant
-// otherwise becomes are quarter rate.  Exactness on the range is checked at
-// compile time.
-template <unsigned D, unsigned N>
-struct Div24 {
-    static constexpr unsigned M = (65536u + D - 1) / D;
-    static constexpr bool exact()
-    {
-        for (unsigned x = 0; x < N; x++)
-            if (((x * M) >> 16) != x / D) return false;
-        return (unsigned long long)N * M < (1ull << 32);
-    }
-    static_assert(exact(), "multiply-shift division not exact on the range");
-    __device__ static __forceinline__ int div(int x)
-    {
-        // written out, since the compiler turns a 24-bit multiply whose
-        // operands it can bound back into the quarter-rate v_mul_lo_u32
-        unsigned r;
-        asm("v_mul_u32_u24 %0, %1, %2" : "=v"(r) : "s"(M), "v"((unsigned)x));
-        return (int)(r >> 16);
-    }
-};
-
-// Index of voxel (z, y, x) of an n^3 mesh (n <= 4096): the row index in 24-bit
-// arithmetic, then one 64-bit multiply-add.
-__device__ __forceinline__ int64_t vox_index(int z, int y, int x, int n)
-{
-    return (int64_t)(unsigned)(__mul24(z, n) + y) * (unsigned)n + (unsigned)x;
-}
-
 __device__ __forceinline__ int u1_off(int t) { return ((t / 9) * U1Y + (t / 3) % 3) * U1X + t % 3; }
 __device__ __forceinline__ int x_off(int t) { return ((t / 9) * C2HY + (t / 3) % 3) * C2HX + t % 3; }
 
 // SRC int64_t: the fixed-point density, delta = q qs - 1 formed here; SRC
 // float: the density contrast as the tile paint stores it (the same value).
-template <typename SRC>
-__global__ __launch_bounds__(INF_T) void k_cnn12_inf(const SRC *__restrict__ q, double qs, int n,
-                                                   const float *__restrict__ th, const uint16_t *__restrict__ wpk,
-                                                   uint16_t *a2)
+template <typename SRC, bool KEEP>
+__global__ __launch_bounds__(INF_T) void k_cnn12(const SRC *__restrict__ q, double qs, int n,
+                                                const float *__restrict__ th, const uint16_t *__restrict__ wpk,
+                                                uint16_t *a2, float *z1, uint16_t *a1, float *z2)
 {
     __shared__ __align__(16) uint16_t U[U1N];
     __shared__ __align__(16) uint4 X[2 * IHALO];   // channel planes 0-7 and 8-15
@@ -560,8 +376,17 @@ __global__ __launch_bounds__(INF_T) void k_cnn12_inf(const SRC *__restrict__ q, 
                 uint16_t aa[4];
 #pragma unroll
                 for (int r = 0; r < 4; r++) aa[r] = to_bf16(silu(acc[r] + bias[r]));
-                reinterpret_cast<uint2 *>(X + (kg >> 1) * IHALO + hv)[kg & 1] =
+                const uint2 pk =
                     make_uint2((uint32_t)aa[0] | ((uint32_t)aa[1] << 16), (uint32_t)aa[2] | ((uint32_t)aa[3] << 16));
+                reinterpret_cast<uint2 *>(X + (kg >> 1) * IHALO + hv)[kg & 1] = pk;
+                if constexpr (KEEP) {
+                    if (hx >= 1 && hx <= C2X && hy >= 1 && hy <= C2Y && hz >= 1 && hz <= IZ) {
+                        const int64_t v = vox_index(z0 + hz - 1, y0 + hy - 1, x0 + hx - 1, n) * NET_C + 4 * kg;
+                        *reinterpret_cast<float4 *>(z1 + v) =
+                            make_float4(acc[0] + bias[0], acc[1] + bias[1], acc[2] + bias[2], acc[3] + bias[3]);
+                        *reinterpret_cast<uint2 *>(a1 + v) = pk;
+                    }
+                }
             }
         }
     }
@@ -580,7 +405,9 @@ __global__ __launch_bounds__(INF_T) void k_cnn12_inf(const SRC *__restrict__ q, 
     float bias[4];
 #pragma unroll
     for (int r = 0; r < 4; r++) bias[r] = th[NC2B + 4 * kg + r];
-    uint16_t *out = a2 + ((((int64_t)z0 * n + (y0 + wave)) * n + (x0 + col)) * NET_C + 4 * kg);
+    const int64_t out0 = (((int64_t)z0 * n + (y0 + wave)) * n + (x0 + col)) * NET_C + 4 * kg;
+    uint16_t *out = a2 + out0;
+    float *zout = KEEP ? z2 + out0 : nullptr;
     const int64_t plane_step = (int64_t)n * n * NET_C;
 #pragma unroll
     for (int rz = 0; rz < IZ; rz++) {
@@ -597,6 +424,11 @@ __global__ __launch_bounds__(INF_T) void k_cnn12_inf(const SRC *__restrict__ q, 
         *reinterpret_cast<uint2 *>(out) =
             make_uint2((uint32_t)aa[0] | ((uint32_t)aa[1] << 16), (uint32_t)aa[2] | ((uint32_t)aa[3] << 16));
         out += plane_step;
+        if constexpr (KEEP) {
+            *reinterpret_cast<float4 *>(zout) =
+                make_float4(acc[0] + bias[0], acc[1] + bias[1], acc[2] + bias[2], acc[3] + bias[3]);
+            zout += plane_step;
+        }
     }
 }
 
@@ -700,168 +532,6 @@ __global__ __launch_bounds__(256) void k_conv3_inf(const uint16_t *__restrict__ 
 // thread (63 KB, two per CU) 418 us; one voxel per thread 360 us.
 constexpr int C3TY = 8, C3TZ = 4, C3ZPT = 2;
 
-// phi = phi_f + dpsi on real rows of stride rs.
-__global__ void k_combine(const float *phif, const float *dpsi, int64_t rs, int n, float *out)
-{
-    const int64_t M = (int64_t)n * n * n;
-    for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < M; v += (int64_t)gridDim.x * blockDim.x) {
-        const int64_t o = (v / n) * rs + v % n;
-        out[o] = phif[o] + dpsi[v];
-    }
-}
-
-// ---- reverse mode of the CNN
-// conv3 data: g2[v][ci] = dsilu(z2[v][ci]) sum_t W3[ci][t] phibar(v - o(t)),
-// phibar on real rows of stride rs.
-__global__ __launch_bounds__(256) void k_conv3_bwd_data(const float *__restrict__ phibar, int64_t rs, int n,
-                                                        const float *__restrict__ th,
-                                                        const float *__restrict__ z2, float *g2)
-{
-    __shared__ float W[27 * NET_C];   // [t][ci]
-    for (int e = threadIdx.x; e < 27 * NET_C; e += blockDim.x) {
-        const int t = e / NET_C, ci = e % NET_C;
-        W[e] = bf16r(th[NC3W + ci * 27 + t]);
-    }
-    __syncthreads();
-    const int64_t M = (int64_t)n * n * n;
-    for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < M; v += (int64_t)gridDim.x * blockDim.x) {
-        const int i2 = (int)(v % n), i1 = (int)((v / n) % n), i0 = (int)(v / ((int64_t)n * n));
-        float acc[NET_C];
-#pragma unroll
-        for (int c = 0; c < NET_C; c++) acc[c] = 0.f;
-        for (int t = 0; t < 27; t++) {
-            const int64_t u = nb_voxel(i0, i1, i2, 26 - t, n);   // v - o(t)
-            const float d = phibar[(u / n) * rs + u % n];
-#pragma unroll
-            for (int c = 0; c < NET_C; c++) acc[c] += W[t * NET_C + c] * d;
-        }
-#pragma unroll
-        for (int c = 0; c < NET_C; c += 4) {
-            const float4 z = *reinterpret_cast<const float4 *>(z2 + v * NET_C + c);
-            *reinterpret_cast<float4 *>(g2 + v * NET_C + c) =
-                make_float4(acc[c] * dsilu(z.x), acc[c + 1] * dsilu(z.y), acc[c + 2] * dsilu(z.z),
-                            acc[c + 3] * dsilu(z.w));
-        }
-    }
-}
-
-// conv2 data: g1[v][ci] = dsilu(z1[v][ci]) sum_{co,t} W2[co][ci][t] g2[v - o(t)][co].
-__global__ __launch_bounds__(256) void k_conv2_bwd_data(const float *__restrict__ g2, int n,
-                                                        const float *__restrict__ th,
-                                                        const float *__restrict__ z1, float *g1)
-{
-    __shared__ float W[27 * NET_C * NET_C];   // [t][co][ci]
-    for (int e = threadIdx.x; e < 27 * NET_C * NET_C; e += blockDim.x) {
-        const int t = e / (NET_C * NET_C), co = (e / NET_C) % NET_C, ci = e % NET_C;
-        W[e] = bf16r(th[NC2W + (co * NET_C + ci) * 27 + t]);
-    }
-    __syncthreads();
-    const int64_t M = (int64_t)n * n * n;
-    for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < M; v += (int64_t)gridDim.x * blockDim.x) {
-        const int i2 = (int)(v % n), i1 = (int)((v / n) % n), i0 = (int)(v / ((int64_t)n * n));
-        float acc[NET_C];
-#pragma unroll
-        for (int c = 0; c < NET_C; c++) acc[c] = 0.f;
-        for (int t = 0; t < 27; t++) {
-            const int64_t u = nb_voxel(i0, i1, i2, 26 - t, n);
-            const float4 *gp = reinterpret_cast<const float4 *>(g2 + u * NET_C);
-#pragma unroll
-            for (int q = 0; q < 4; q++) {
-                const float4 gv = gp[q];
-                const float gg[4] = {gv.x, gv.y, gv.z, gv.w};
-#pragma unroll
-                for (int r = 0; r < 4; r++) {
-                    const int co = 4 * q + r;
-#pragma unroll
-                    for (int c = 0; c < NET_C; c++) acc[c] += W[(t * NET_C + co) * NET_C + c] * gg[r];
-                }
-            }
-        }
-#pragma unroll
-        for (int c = 0; c < NET_C; c += 4) {
-            const float4 z = *reinterpret_cast<const float4 *>(z1 + v * NET_C + c);
-            *reinterpret_cast<float4 *>(g1 + v * NET_C + c) =
-                make_float4(acc[c] * dsilu(z.x), acc[c + 1] * dsilu(z.y), acc[c + 2] * dsilu(z.z),
-                            acc[c + 3] * dsilu(z.w));
-        }
-    }
-}
-
-// Weight gradients dW[co][ci][t] += sum_v in_ci(v + o(t)) dout_co(v), db[co] += sum_v dout_co(v).
-// in: KIN 0 = the int64 density mesh as BF16 delta (quantum qs: the conv1 input),
-//     KIN 1 = BF16 [v][16]; dout: KOUT 0 = real rows of stride rs_out (conv3), KOUT 1 = FP32 [v][16].
-// A workgroup walks tiles of 16 x 8 x 4 voxels with LDS copies of the input
-// halo and the output gradient; each thread owns CO CI 27 / 256 entries.
-template <int CI, int CO, int KIN, int KOUT>
-__global__ __launch_bounds__(256) void k_conv_bwd_w(const void *in_, double qs, const void *dout_, int64_t rs_out,
-                                                    int n, float *dW, float *db)
-{
-    constexpr int NE = CO * CI * 27, PER = (NE + 255) / 256;
-    __shared__ float Xs[C2HALO * CI];
-    __shared__ float Gs[C2X * C2Y * C2Z * CO];
-    const int tid = threadIdx.x, m = n - 1;
-    const int ntx = n / C2X, nty = n / C2Y, ntz = n / C2Z, ntiles = ntx * nty * ntz;
-    float acc[PER], bacc = 0.f;
-#pragma unroll
-    for (int k = 0; k < PER; k++) acc[k] = 0.f;
-    for (int tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
-        const int tx = tile % ntx, ty = (tile / ntx) % nty, tz = tile / (ntx * nty);
-        const int x0 = tx * C2X, y0 = ty * C2Y, z0 = tz * C2Z;
-        __syncthreads();
-        for (int e = tid; e < C2HALO * CI; e += 256) {
-            const int hv = e / CI, ci = e % CI;
-            const int hx = hv % C2HX, hy = (hv / C2HX) % C2HY, hz = hv / (C2HX * C2HY);
-            const int64_t g = ((int64_t)((z0 + hz - 1) & m) * n + ((y0 + hy - 1) & m)) * n + ((x0 + hx - 1) & m);
-            float val;
-            if constexpr (KIN == 0)
-                val = from_bf16(delta_bf16(reinterpret_cast<const int64_t *>(in_)[g], qs));
-            else
-                val = from_bf16(reinterpret_cast<const uint16_t *>(in_)[g * CI + ci]);
-            Xs[e] = val;
-        }
-        for (int e = tid; e < C2X * C2Y * C2Z * CO; e += 256) {
-            const int lv = e / CO, co = e % CO;
-            const int lx = lv % C2X, ly = (lv / C2X) % C2Y, lz = lv / (C2X * C2Y);
-            const int64_t g = ((int64_t)(z0 + lz) * n + (y0 + ly)) * n + (x0 + lx);
-            float val;
-            if constexpr (KOUT == 0)
-                val = reinterpret_cast<const float *>(dout_)[(g / n) * rs_out + g % n];
-            else
-                val = reinterpret_cast<const float *>(dout_)[g * CO + co];
-            Gs[e] = val;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int k = 0; k < PER; k++) {
-            const int e = tid + 256 * k;
-            if (e < NE) {
-                const int co = e / (CI * 27), ci = (e / 27) % CI, t = e % 27;
-                const int dz = t / 9, dy = (t / 3) % 3, dx = t % 3;
-                float s = 0.f;
-                for (int lz = 0; lz < C2Z; lz++)
-                    for (int ly = 0; ly < C2Y; ly++)
-                        for (int lx = 0; lx < C2X; lx++) {
-                            const int hv = ((lz + dz) * C2HY + (ly + dy)) * C2HX + (lx + dx);
-                            const int lv = (lz * C2Y + ly) * C2X + lx;
-                            s += Xs[hv * CI + ci] * Gs[lv * CO + co];
-                        }
-                acc[k] += s;
-            }
-        }
-        if (tid < CO) {
-            float s = 0.f;
-            for (int lv = 0; lv < C2X * C2Y * C2Z; lv++) s += Gs[lv * CO + tid];
-            bacc += s;
-        }
-    }
-#pragma unroll
-    for (int k = 0; k < PER; k++) {
-        const int e = tid + 256 * k;
-        if (e < NE) atomicAdd(dW + e, acc[k]);
-    }
-    if (tid < CO) atomicAdd(db + tid, bacc);
-}
-
 // ---- loss and optimiser
 // red[0] += sum (acc - target)^2, red[1] += sum target^2; acc -= target.
 __global__ __launch_bounds__(256) void k_force_loss(float *acc, const float *target, int64_t n3, double *red)
@@ -959,60 +629,34 @@ hipError_t launch_grad3(float2 *F, int64_t nhp, int64_t fs, int n, double scale,
     return hipGetLastError();
 }
 
-hipError_t launch_cnn_fwd(const int64_t *q, double qs, int n, const float *th, float *z1, uint16_t *a1, float *z2,
-                          uint16_t *a2, float *dpsi, hipStream_t s)
-{
-    if (n < C2X || n % C2X) return hipErrorInvalidValue;
-    const int64_t M = (int64_t)n * n * n;
-    hipLaunchKernelGGL(k_conv1_fwd, dim3(grid_for(M, 256)), dim3(256), 0, s, q, qs, n, th, z1, a1);
-    hipLaunchKernelGGL(k_conv2_fwd, dim3((unsigned)(M / (C2X * C2Y * C2Z))), dim3(256), 0, s, a1, n, th, z2, a2);
-    hipLaunchKernelGGL(k_conv3_fwd, dim3(grid_for(M, 256)), dim3(256), 0, s, a2, n, th, dpsi);
-    return hipGetLastError();
-}
-
 hipError_t launch_cnn_inf(const int64_t *q, double qs, const float *delta, const float *phif, int64_t rs, int n,
                           const float *th, uint16_t *wpk, uint16_t *a2, float *out, hipStream_t s)
 {
     if (n < 16 || n % 16 || n > 4096) return hipErrorInvalidValue;
     const int64_t M = (int64_t)n * n * n;
+    const dim3 grid((unsigned)(M / (C2X * C2Y * IZ)));
+    float *z = nullptr;
+    uint16_t *a1 = nullptr;
     hipLaunchKernelGGL(k_pack_w, dim3(PACK_BLOCKS), dim3(256), 0, s, th, wpk);
     if (delta)
-        hipLaunchKernelGGL(k_cnn12_inf<float>, dim3((unsigned)(M / (C2X * C2Y * IZ))), dim3(INF_T), 0, s, delta, qs, n,
-                           th, wpk, a2);
+        hipLaunchKernelGGL((k_cnn12<float, false>), grid, dim3(INF_T), 0, s, delta, qs, n, th, wpk, a2, z, a1, z);
     else
-        hipLaunchKernelGGL(k_cnn12_inf<int64_t>, dim3((unsigned)(M / (C2X * C2Y * IZ))), dim3(INF_T), 0, s, q, qs, n,
-                           th, wpk, a2);
+        hipLaunchKernelGGL((k_cnn12<int64_t, false>), grid, dim3(INF_T), 0, s, q, qs, n, th, wpk, a2, z, a1, z);
     hipLaunchKernelGGL((k_conv3_inf<C3TY, C3TZ, C3ZPT>), dim3((unsigned)(M / (16 * C3TY * C3TZ))), dim3(256), 0, s, a2,
                        n, th, wpk, phif, rs, out);
     return hipGetLastError();
 }
 
-hipError_t launch_combine(const float *phif, const float *dpsi, int64_t rs, int n, float *out, hipStream_t s)
+hipError_t launch_cnn_fwd(const int64_t *q, double qs, const float *phif, int64_t rs, int n, const float *th,
+                          uint16_t *wpk, float *z1, uint16_t *a1, float *z2, uint16_t *a2, float *out, hipStream_t s)
 {
+    if (n < 16 || n % 16 || n > 4096) return hipErrorInvalidValue;
     const int64_t M = (int64_t)n * n * n;
-    hipLaunchKernelGGL(k_combine, dim3(grid_for(M, 256)), dim3(256), 0, s, phif, dpsi, rs, n, out);
-    return hipGetLastError();
-}
-
-hipError_t launch_cnn_bwd(const int64_t *q, double qs, const float *phibar, int64_t rs, int n, const float *th,
-                          const float *z1, const uint16_t *a1, const float *z2, const uint16_t *a2, float *g1,
-                          float *g2, float *dth, hipStream_t s)
-{
-    if (n < C2X || n % C2X) return hipErrorInvalidValue;
-    const int64_t M = (int64_t)n * n * n;
-    const int ntiles = (int)(M / (C2X * C2Y * C2Z));
-    const unsigned gw = (unsigned)(ntiles < 2048 ? ntiles : 2048);
-    // conv3: dW3, db3 from a2 and phibar; g2 = dsilu(z2) W3^T phibar
-    hipLaunchKernelGGL((k_conv_bwd_w<NET_C, 1, 1, 0>), dim3(gw), dim3(256), 0, s, (const void *)a2, 0.0,
-                       (const void *)phibar, rs, n, dth + NC3W, dth + NC3B);
-    hipLaunchKernelGGL(k_conv3_bwd_data, dim3(grid_for(M, 256)), dim3(256), 0, s, phibar, rs, n, th, z2, g2);
-    // conv2
-    hipLaunchKernelGGL((k_conv_bwd_w<NET_C, NET_C, 1, 1>), dim3(gw), dim3(256), 0, s, (const void *)a1, 0.0,
-                       (const void *)g2, (int64_t)0, n, dth + NC2W, dth + NC2B);
-    hipLaunchKernelGGL(k_conv2_bwd_data, dim3(grid_for(M, 256)), dim3(256), 0, s, g2, n, th, z1, g1);
-    // conv1 weights from delta; delta does not depend on the parameters
-    hipLaunchKernelGGL((k_conv_bwd_w<1, NET_C, 0, 1>), dim3(gw), dim3(256), 0, s, (const void *)q, qs,
-                       (const void *)g1, (int64_t)0, n, dth + NC1W, dth + NC1B);
+    hipLaunchKernelGGL(k_pack_w, dim3(PACK_BLOCKS), dim3(256), 0, s, th, wpk);
+    hipLaunchKernelGGL((k_cnn12<int64_t, true>), dim3((unsigned)(M / (C2X * C2Y * IZ))), dim3(INF_T), 0, s, q, qs, n, th,
+                       wpk, a2, z1, a1, z2);
+    hipLaunchKernelGGL((k_conv3_inf<C3TY, C3TZ, C3ZPT>), dim3((unsigned)(M / (16 * C3TY * C3TZ))), dim3(256), 0, s, a2,
+                       n, th, wpk, phif, rs, out);
     return hipGetLastError();
 }
 

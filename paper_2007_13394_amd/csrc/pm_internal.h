@@ -215,8 +215,7 @@ struct Workspace {
     float *net_phif = nullptr;   // filtered potential, real rows of stride 2 Nhp
     float *net_z1 = nullptr, *net_z2 = nullptr;      // CNN pre-activations [N^3][16] FP32
     uint16_t *net_a1 = nullptr, *net_a2 = nullptr;   // CNN activations [N^3][16] BF16
-    float *net_g1 = nullptr, *net_g2 = nullptr;      // reverse-mode buffers [N^3][16]
-    float *net_dpsi = nullptr;   // CNN output [N^3]
+    float *net_g1 = nullptr, *net_g2 = nullptr;      // reverse mode: partial weight gradients, cotangent of z2 [N^3][16]
     float2 *net_dk = nullptr;    // density spectrum kept for the reverse mode
     float *net_acc = nullptr;    // forces on the particles [3][P]
     float *net_table = nullptr;  // radial filter table [NET_NB]
@@ -402,10 +401,6 @@ hipError_t launch_spec_filter_bwd(const float2 *dk, const float2 *pf, int64_t nh
 hipError_t launch_grad3(float2 *F, int64_t nhp, int64_t fs, int n, double scale, bool transpose, hipStream_t s);
 // F_d = -i k_d (F_1 + F_2) scale into fields 0, 1, 2 (the potential given as two spectra).
 hipError_t launch_grad3_sum(float2 *F, int64_t nhp, int64_t fs, int n, double scale, hipStream_t s);
-// CNN input: the int64 density mesh q with quantum qs (delta = q qs - 1).
-hipError_t launch_cnn_fwd(const int64_t *q, double qs, int n, const float *th, float *z1, uint16_t *a1, float *z2,
-                          uint16_t *a2, float *dpsi, hipStream_t s);
-hipError_t launch_combine(const float *phif, const float *dpsi, int64_t rs, int n, float *out, hipStream_t s);
 // Inference CNN fused with the combination: out = phi_f + cnn(delta) on real
 // rows; a2: BF16 [n^3][16] scratch, wpk: NET_WPK_BYTES scratch for the
 // repacked weights.  n a multiple of 16.
@@ -413,9 +408,16 @@ hipError_t launch_combine(const float *phif, const float *dpsi, int64_t rs, int 
 // (optional): added to the CNN output (none: the output is the CNN alone).
 hipError_t launch_cnn_inf(const int64_t *q, double qs, const float *delta, const float *phif, int64_t rs, int n,
                           const float *th, uint16_t *wpk, uint16_t *a2, float *out, hipStream_t s);
+// Training forward, the same CNN on the int64 density mesh q (delta = q qs - 1):
+// also keeps z1, z2 (FP32) and a1, a2 (BF16), each [n^3][16].
+hipError_t launch_cnn_fwd(const int64_t *q, double qs, const float *phif, int64_t rs, int n, const float *th,
+                          uint16_t *wpk, float *z1, uint16_t *a1, float *z2, uint16_t *a2, float *out, hipStream_t s);
+// Reverse mode (net_bwd.hip): dth += the CNN's parameter gradients for the
+// cotangent phibar of its output (real rows of stride rs).  part: scratch of
+// n^3 x 16 floats for the workgroups' partial sums; g2: [n^3][16]; wpk: as above.
 hipError_t launch_cnn_bwd(const int64_t *q, double qs, const float *phibar, int64_t rs, int n, const float *th,
-                          const float *z1, const uint16_t *a1, const float *z2, const uint16_t *a2, float *g1,
-                          float *g2, float *dth, hipStream_t s);
+                          const float *z1, const uint16_t *a1, const float *z2, const uint16_t *a2, float *part,
+                          float *g2, uint16_t *wpk, float *dth, hipStream_t s);
 hipError_t launch_force_loss(float *acc, const float *target, int64_t n3, double *red, hipStream_t s);
 hipError_t launch_adam(float *th, float *m, float *v, const float *g, int64_t n, double lr, double b1, double b2,
                        double eps, int t, hipStream_t s);
