@@ -863,6 +863,14 @@ pm_status pm_kdk_factors(const pm_ctx *c, double a_force, double a_kick0, double
     return PM_OK;
 }
 
+// The spectrum's amplitude depends on the configuration alone: formed by the
+// first call that needs it.
+static double pk_amplitude_of(pm_ctx *c)
+{
+    if (!(c->pk_amp > 0)) c->pk_amp = pm::pk_amplitude(*c);
+    return c->pk_amp;
+}
+
 static pm_status ic_impl(pm_ctx *c, const float *white, const float *u, float *x, float *p, void *stream)
 {
     c->permuted = false;
@@ -881,7 +889,7 @@ static pm_status ic_impl(pm_ctx *c, const float *white, const float *u, float *x
     const double a0 = g.a0;
     const double D0 = pm::growth_D(*c, a0), D1 = pm::growth_D(*c, 1.0), G0 = pm::growth_G(*c, a0);
     pm::IcParams ip{};
-    ip.amp_over_vcell = pm::pk_amplitude(*c) * (D0 / D1) * (D0 / D1) / pow(g.box / nic, 3);
+    ip.amp_over_vcell = pk_amplitude_of(c) * (D0 / D1) * (D0 / D1) / pow(g.box / nic, 3);
     ip.box = g.box;
     ip.omh = g.omega_m * g.h;
     ip.n_s = g.n_s;
@@ -1269,7 +1277,7 @@ pm_status pm_ic_vjp(pm_ctx *c, const float *xbar, const float *pbar, float *wbar
     const double a0 = g.a0;
     const double D0 = pm::growth_D(*c, a0), D1 = pm::growth_D(*c, 1.0), G0 = pm::growth_G(*c, a0);
     pm::IcParams ip{};
-    ip.amp_over_vcell = pm::pk_amplitude(*c) * (D0 / D1) * (D0 / D1) / pow(g.box / nic, 3);
+    ip.amp_over_vcell = pk_amplitude_of(c) * (D0 / D1) * (D0 / D1) / pow(g.box / nic, 3);
     ip.box = g.box;
     ip.omh = g.omega_m * g.h;
     ip.n_s = g.n_s;

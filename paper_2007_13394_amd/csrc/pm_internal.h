@@ -275,6 +275,7 @@ struct Ctx {
     std::vector<float> dirs;      // (2 n_fib + 1) x 3
     std::vector<double> q_cdf;    // pseudo-random sampling: cumulative of q^2 f~ at q = i q_cdf_h
     double q_cdf_h = 0;
+    double pk_amp = 0;            // pk_amplitude of this configuration once a call has needed it
     Workspace ws;
     std::vector<float2> tw_host;
     // particle order: canonical (segments at seg_off) or permuted by the last
