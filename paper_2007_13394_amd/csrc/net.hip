@@ -246,9 +246,7 @@ __global__ void k_grad3_t(float2 *F, int64_t nhp, int64_t fs, int n, float scale
 // Voxel v = (i0 n + i1) n + i2; tap t = (t0 3 + t1) 3 + t2, offset t_e - 1.
 constexpr int C2X = 16, C2Y = 8, C2HX = C2X + 2, C2HY = C2Y + 2;
 
-// ---- forward passes: in inference (KEEP false) no pre-activations are kept and
-// a1 never leaves LDS; training (KEEP true) also stores z1, a1 and z2, each
-// voxel's by the workgroup that owns it
+// ---- inference path: no pre-activations kept, a1 never leaves LDS
 // conv1 + conv2 on v_mfma_f32_16x16x32_bf16 (K = 32; lane l holds
 // A[row l % 16][k 8 (l / 16) + j], B[k 8 (l / 16) + j][col l % 16] and
 // D[row 4 (l / 16) + r][col l % 16]).  The 16 x 8 x IZ output tile of conv2
@@ -274,7 +272,10 @@ constexpr int NG1 = (IHALO + 15) / 16, NPAIR = 14;
 // [t][ci] BF16.
 constexpr int WPK_W2 = 0, WPK_W1 = NPAIR * NET_C * 4 * 8 * 2, WPK_W3 = WPK_W1 + NET_C * 32 * 2,
               WPK_END = WPK_W3 + 27 * NET_C * 2;
+// The training forward's weights (k_pack_wf) around the same conv3 rows.
+constexpr int WPK_W2F = 0, WPK_W1F = ((WPK_END + 63) / 64) * 64;
 static_assert(WPK_END <= NET_WPK_BYTES && WPK_W1 % 16 == 0 && WPK_W3 % 16 == 0, "packed weight layout");
+static_assert(27 * NET_C * NET_C * 2 <= WPK_W3 && WPK_W1F + 27 * NET_C * 4 <= NET_WPK_BYTES, "training weights");
 
 // A grid of PACK_BLOCKS workgroups (one would wait on its strided weight
 // reads for 32 rounds).
@@ -303,10 +304,10 @@ __device__ __forceinline__ int x_off(int t) { return ((t / 9) * C2HY + (t / 3) %
 
 // SRC int64_t: the fixed-point density, delta = q qs - 1 formed here; SRC
 // float: the density contrast as the tile paint stores it (the same value).
-template <typename SRC, bool KEEP>
-__global__ __launch_bounds__(INF_T) void k_cnn12(const SRC *__restrict__ q, double qs, int n,
-                                                const float *__restrict__ th, const uint16_t *__restrict__ wpk,
-                                                uint16_t *a2, float *z1, uint16_t *a1, float *z2)
+template <typename SRC>
+__global__ __launch_bounds__(INF_T) void k_cnn12_inf(const SRC *__restrict__ q, double qs, int n,
+                                                   const float *__restrict__ th, const uint16_t *__restrict__ wpk,
+                                                   uint16_t *a2)
 {
     __shared__ __align__(16) uint16_t U[U1N];
     __shared__ __align__(16) uint4 X[2 * IHALO];   // channel planes 0-7 and 8-15
@@ -376,17 +377,8 @@ __global__ __launch_bounds__(INF_T) void k_cnn12(const SRC *__restrict__ q, doub
                 uint16_t aa[4];
 #pragma unroll
                 for (int r = 0; r < 4; r++) aa[r] = to_bf16(silu(acc[r] + bias[r]));
-                const uint2 pk =
+                reinterpret_cast<uint2 *>(X + (kg >> 1) * IHALO + hv)[kg & 1] =
                     make_uint2((uint32_t)aa[0] | ((uint32_t)aa[1] << 16), (uint32_t)aa[2] | ((uint32_t)aa[3] << 16));
-                reinterpret_cast<uint2 *>(X + (kg >> 1) * IHALO + hv)[kg & 1] = pk;
-                if constexpr (KEEP) {
-                    if (hx >= 1 && hx <= C2X && hy >= 1 && hy <= C2Y && hz >= 1 && hz <= IZ) {
-                        const int64_t v = vox_index(z0 + hz - 1, y0 + hy - 1, x0 + hx - 1, n) * NET_C + 4 * kg;
-                        *reinterpret_cast<float4 *>(z1 + v) =
-                            make_float4(acc[0] + bias[0], acc[1] + bias[1], acc[2] + bias[2], acc[3] + bias[3]);
-                        *reinterpret_cast<uint2 *>(a1 + v) = pk;
-                    }
-                }
             }
         }
     }
@@ -405,9 +397,7 @@ __global__ __launch_bounds__(INF_T) void k_cnn12(const SRC *__restrict__ q, doub
     float bias[4];
 #pragma unroll
     for (int r = 0; r < 4; r++) bias[r] = th[NC2B + 4 * kg + r];
-    const int64_t out0 = (((int64_t)z0 * n + (y0 + wave)) * n + (x0 + col)) * NET_C + 4 * kg;
-    uint16_t *out = a2 + out0;
-    float *zout = KEEP ? z2 + out0 : nullptr;
+    uint16_t *out = a2 + ((((int64_t)z0 * n + (y0 + wave)) * n + (x0 + col)) * NET_C + 4 * kg);
     const int64_t plane_step = (int64_t)n * n * NET_C;
 #pragma unroll
     for (int rz = 0; rz < IZ; rz++) {
@@ -424,11 +414,6 @@ __global__ __launch_bounds__(INF_T) void k_cnn12(const SRC *__restrict__ q, doub
         *reinterpret_cast<uint2 *>(out) =
             make_uint2((uint32_t)aa[0] | ((uint32_t)aa[1] << 16), (uint32_t)aa[2] | ((uint32_t)aa[3] << 16));
         out += plane_step;
-        if constexpr (KEEP) {
-            *reinterpret_cast<float4 *>(zout) =
-                make_float4(acc[0] + bias[0], acc[1] + bias[1], acc[2] + bias[2], acc[3] + bias[3]);
-            zout += plane_step;
-        }
     }
 }
 
@@ -531,6 +516,149 @@ __global__ __launch_bounds__(256) void k_conv3_inf(const uint16_t *__restrict__ 
 // (35 KB of LDS, four workgroups per CU) 306 us; 16 x 16 x 4 with four per
 // thread (63 KB, two per CU) 418 us; one voxel per thread 360 us.
 constexpr int C3TY = 8, C3TZ = 4, C3ZPT = 2;
+
+// ---- training forward: z1, a1, z2 and a2 are stored for the reverse mode.  The
+// activations are rounded to BF16, so a pre-activation that moves by an FP32
+// rounding can move its activation by 2^-8: the sums keep one fixed order
+// (conv1: the taps in turn, from the bias; conv2: one 16x16x16 product per tap
+// in turn, then the bias).
+//
+// conv1: tile 16 x 8 x 4 with delta's halo in LDS, two voxels per thread; the
+// weights are wave-uniform, so a tap is one FMA with a scalar operand per
+// channel (432 per voxel).  Bound by the writes of z1 and a1 (96 bytes per voxel).
+constexpr int T1Y = 8, T1Z = 4;
+template <typename SRC>
+__global__ __launch_bounds__(256) void k_conv1_fwd(const SRC *__restrict__ q, double qs, int n,
+                                                   const float *__restrict__ th, const uint16_t *__restrict__ wpk,
+                                                   float *z1, uint16_t *a1)
+{
+    constexpr int HX = 18, HY = T1Y + 2, HZ = T1Z + 2, NH = HX * HY * HZ, NU = (NH + 255) / 256;
+    __shared__ float U[NH];
+    const int tid = threadIdx.x, m = n - 1;
+    const int tile = xcd_tile(blockIdx.x, gridDim.x), ntx = n / 16, nty = n / T1Y;
+    const int x0 = (tile % ntx) * 16, y0 = ((tile / ntx) % nty) * T1Y, z0 = (tile / (ntx * nty)) * T1Z;
+    SRC qv[NU];
+#pragma unroll
+    for (int k = 0; k < NU; k++) {
+        const int e = min(tid + 256 * k, NH - 1);
+        const int hq = Div24<HX, NH>::div(e), hz = Div24<HY, HY * HZ>::div(hq), hx = e - hq * HX, hy = hq - hz * HY;
+        qv[k] = q[vox_index((z0 + hz - 1) & m, (y0 + hy - 1) & m, (x0 + hx - 1) & m, n)];
+    }
+#pragma unroll
+    for (int k = 0; k < NU; k++) {
+        uint16_t d;
+        if constexpr (std::is_same<SRC, int64_t>::value) d = delta_bf16(qv[k], qs);
+        else d = to_bf16(qv[k]);
+        if (tid + 256 * k < NH) U[tid + 256 * k] = from_bf16(d);
+    }
+    __syncthreads();
+    const int lx = tid & 15, ly = (tid >> 4) & 7, lz = (tid >> 7) * 2;
+    float z[2][NET_C];
+#pragma unroll
+    for (int c = 0; c < NET_C; c++) z[0][c] = z[1][c] = th[NC1B + c];
+    const float *w = reinterpret_cast<const float *>(wpk + WPK_W1F / 2);
+#pragma unroll 3
+    for (int t = 0; t < 27; t++) {
+        const float *u = U + ((lz + t / 9) * HY + ly + (t / 3) % 3) * HX + lx + t % 3;
+        const float u0 = u[0], u1 = u[HY * HX];
+#pragma unroll
+        for (int c = 0; c < NET_C; c++) {
+            const float wc = w[t * NET_C + c];
+            z[0][c] = fmaf(wc, u0, z[0][c]);
+            z[1][c] = fmaf(wc, u1, z[1][c]);
+        }
+    }
+#pragma unroll
+    for (int p = 0; p < 2; p++) {
+        const int64_t v = vox_index(z0 + lz + p, y0 + ly, x0 + lx, n) * NET_C;
+#pragma unroll
+        for (int c = 0; c < NET_C; c += 4) {
+            *reinterpret_cast<float4 *>(z1 + v + c) = make_float4(z[p][c], z[p][c + 1], z[p][c + 2], z[p][c + 3]);
+            const uint32_t lo = (uint32_t)to_bf16(silu(z[p][c])) | ((uint32_t)to_bf16(silu(z[p][c + 1])) << 16);
+            const uint32_t hi = (uint32_t)to_bf16(silu(z[p][c + 2])) | ((uint32_t)to_bf16(silu(z[p][c + 3])) << 16);
+            *reinterpret_cast<uint2 *>(a1 + v + c) = make_uint2(lo, hi);
+        }
+    }
+}
+
+// conv2: tile 16 x 8 x 4 with a1's halo in LDS, the 27 weight fragments in
+// registers.  Per 16-voxel row and tap D[co][vox] += W_t[co][ci] X_t[ci][vox]
+// (lane l holds A[co = l % 16][ci = 4 (l / 16) + r], B[ci = 4 (l / 16) + r][vox =
+// l % 16] and D[co = 4 (l / 16) + r][vox = l % 16]); two rows in flight.  Bound by
+// the writes of z2 and a2 and the read of a1.
+__global__ __launch_bounds__(256, 2) void k_conv2_fwd(const uint16_t *__restrict__ a1, int n,
+                                                     const float *__restrict__ th, const uint16_t *__restrict__ wpk,
+                                                     float *z2, uint16_t *a2)
+{
+    constexpr int HX = 18, HY = 10, HZ = 6, NH = HX * HY * HZ, NX = (2 * NH + 255) / 256;
+    __shared__ __align__(16) uint4 X[2 * NH];
+    const int tid = threadIdx.x, m = n - 1;
+    const int tile = xcd_tile(blockIdx.x, gridDim.x), ntx = n / 16, nty = n / 8;
+    const int x0 = (tile % ntx) * 16, y0 = ((tile / ntx) % nty) * 8, z0 = (tile / (ntx * nty)) * 4;
+    uint4 xv[NX];
+#pragma unroll
+    for (int k = 0; k < NX; k++) {
+        const int e = min(tid + 256 * k, 2 * NH - 1), hv = e >> 1;
+        const int hq = Div24<HX, NH>::div(hv), hz = Div24<HY, HY * HZ>::div(hq), hx = hv - hq * HX, hy = hq - hz * HY;
+        xv[k] = reinterpret_cast<const uint4 *>(
+            a1 + vox_index((z0 + hz - 1) & m, (y0 + hy - 1) & m, (x0 + hx - 1) & m, n) * NET_C)[e & 1];
+    }
+    const int lane = tid & 63, wave = tid >> 6, col = lane & 15, kg = lane >> 4;
+    v4s w[27];
+#pragma unroll
+    for (int t = 0; t < 27; t++)
+        w[t] = *reinterpret_cast<const v4s *>(wpk + WPK_W2F / 2 + (t * NET_C + col) * NET_C + 4 * kg);
+    float bias[4];
+#pragma unroll
+    for (int r = 0; r < 4; r++) bias[r] = th[NC2B + 4 * kg + r];
+#pragma unroll
+    for (int k = 0; k < NX; k++)
+        if (tid + 256 * k < 2 * NH) X[tid + 256 * k] = xv[k];
+    __syncthreads();
+    // wavefront w takes the rows (y = 2 w, 2 w + 1) of each plane
+    const v4s *Xp = reinterpret_cast<const v4s *>(X) + (2 * wave * HX + col) * 4 + kg;
+#pragma unroll 1
+    for (int z = 0; z < 4; z++) {
+        v4f acc[2] = {};
+#pragma unroll
+        for (int t = 0; t < 27; t++) {
+            const v4s *p = Xp + (((z + t / 9) * HY + (t / 3) % 3) * HX + t % 3) * 4;
+            acc[0] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(w[t], p[0], acc[0], 0, 0, 0);
+            acc[1] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(w[t], p[4 * HX], acc[1], 0, 0, 0);
+        }
+#pragma unroll
+        for (int y = 0; y < 2; y++) {
+            const int64_t v = vox_index(z0 + z, y0 + 2 * wave + y, x0 + col, n) * NET_C + 4 * kg;
+            float zz[4];
+            uint16_t aa[4];
+#pragma unroll
+            for (int r = 0; r < 4; r++) {
+                zz[r] = acc[y][r] + bias[r];
+                aa[r] = to_bf16(silu(zz[r]));
+            }
+            *reinterpret_cast<float4 *>(z2 + v) = make_float4(zz[0], zz[1], zz[2], zz[3]);
+            *reinterpret_cast<uint2 *>(a2 + v) =
+                make_uint2((uint32_t)aa[0] | ((uint32_t)aa[1] << 16), (uint32_t)aa[2] | ((uint32_t)aa[3] << 16));
+        }
+    }
+}
+
+// Weights of the training forward: conv1 [t][co] FP32 (BF16-rounded), conv2
+// [t][co][ci] BF16, conv3 [t][ci] BF16 where the inference layout has it.
+__global__ __launch_bounds__(256) void k_pack_wf(const float *__restrict__ th, uint16_t *wpk)
+{
+    float *w1 = reinterpret_cast<float *>(wpk + WPK_W1F / 2);
+    uint16_t *w2 = wpk + WPK_W2F / 2, *w3 = wpk + WPK_W3 / 2;
+    const int e = blockIdx.x * 256 + threadIdx.x;
+    if (e < 27 * NET_C * NET_C) {
+        const int t = e / (NET_C * NET_C), co = (e / NET_C) % NET_C, ci = e % NET_C;
+        w2[e] = to_bf16(th[NC2W + (co * NET_C + ci) * 27 + t]);
+    }
+    if (e < 27 * NET_C) {
+        w1[e] = bf16r(th[NC1W + (e % NET_C) * 27 + e / NET_C]);
+        w3[e] = to_bf16(th[NC3W + (e % NET_C) * 27 + e / NET_C]);
+    }
+}
 
 // ---- loss and optimiser
 // red[0] += sum (acc - target)^2, red[1] += sum target^2; acc -= target.
@@ -635,26 +763,28 @@ hipError_t launch_cnn_inf(const int64_t *q, double qs, const float *delta, const
     if (n < 16 || n % 16 || n > 4096) return hipErrorInvalidValue;
     const int64_t M = (int64_t)n * n * n;
     const dim3 grid((unsigned)(M / (C2X * C2Y * IZ)));
-    float *z = nullptr;
-    uint16_t *a1 = nullptr;
     hipLaunchKernelGGL(k_pack_w, dim3(PACK_BLOCKS), dim3(256), 0, s, th, wpk);
     if (delta)
-        hipLaunchKernelGGL((k_cnn12<float, false>), grid, dim3(INF_T), 0, s, delta, qs, n, th, wpk, a2, z, a1, z);
+        hipLaunchKernelGGL(k_cnn12_inf<float>, grid, dim3(INF_T), 0, s, delta, qs, n, th, wpk, a2);
     else
-        hipLaunchKernelGGL((k_cnn12<int64_t, false>), grid, dim3(INF_T), 0, s, q, qs, n, th, wpk, a2, z, a1, z);
+        hipLaunchKernelGGL(k_cnn12_inf<int64_t>, grid, dim3(INF_T), 0, s, q, qs, n, th, wpk, a2);
     hipLaunchKernelGGL((k_conv3_inf<C3TY, C3TZ, C3ZPT>), dim3((unsigned)(M / (16 * C3TY * C3TZ))), dim3(256), 0, s, a2,
                        n, th, wpk, phif, rs, out);
     return hipGetLastError();
 }
 
-hipError_t launch_cnn_fwd(const int64_t *q, double qs, const float *phif, int64_t rs, int n, const float *th,
-                          uint16_t *wpk, float *z1, uint16_t *a1, float *z2, uint16_t *a2, float *out, hipStream_t s)
+hipError_t launch_cnn_fwd(const int64_t *q, double qs, const float *delta, const float *phif, int64_t rs, int n,
+                          const float *th, uint16_t *wpk, float *z1, uint16_t *a1, float *z2, uint16_t *a2, float *out, hipStream_t s)
 {
     if (n < 16 || n % 16 || n > 4096) return hipErrorInvalidValue;
     const int64_t M = (int64_t)n * n * n;
-    hipLaunchKernelGGL(k_pack_w, dim3(PACK_BLOCKS), dim3(256), 0, s, th, wpk);
-    hipLaunchKernelGGL((k_cnn12<int64_t, true>), dim3((unsigned)(M / (C2X * C2Y * IZ))), dim3(INF_T), 0, s, q, qs, n, th,
-                       wpk, a2, z1, a1, z2);
+    hipLaunchKernelGGL(k_pack_wf, dim3(27), dim3(256), 0, s, th, wpk);
+    const dim3 g1((unsigned)(M / (16 * T1Y * T1Z))), g2((unsigned)(M / (16 * 8 * 4)));
+    if (delta)
+        hipLaunchKernelGGL(k_conv1_fwd<float>, g1, dim3(256), 0, s, delta, qs, n, th, wpk, z1, a1);
+    else
+        hipLaunchKernelGGL(k_conv1_fwd<int64_t>, g1, dim3(256), 0, s, q, qs, n, th, wpk, z1, a1);
+    hipLaunchKernelGGL(k_conv2_fwd, g2, dim3(256), 0, s, a1, n, th, wpk, z2, a2);
     hipLaunchKernelGGL((k_conv3_inf<C3TY, C3TZ, C3ZPT>), dim3((unsigned)(M / (16 * C3TY * C3TZ))), dim3(256), 0, s, a2,
                        n, th, wpk, phif, rs, out);
     return hipGetLastError();

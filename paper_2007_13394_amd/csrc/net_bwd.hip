@@ -322,7 +322,9 @@ __global__ __launch_bounds__(256) void k_pack_w2t(const float *__restrict__ th, 
     wpk[e] = q < 9 ? to_bf16(th[NC2W + (co * NET_C + ci) * 27 + 26 - (dz * 9 + q)]) : (uint16_t)0;
 }
 
-__global__ __launch_bounds__(D2T, 2) void k_conv2_bwd_d(const int64_t *__restrict__ q, double qs,
+// SRC int64_t: the fixed-point density, delta = q qs - 1; float: delta itself.
+template <typename SRC>
+__global__ __launch_bounds__(D2T, 2) void k_conv2_bwd_d(const SRC *__restrict__ q, double qs,
                                                        const float *__restrict__ g2, int n,
                                                        const uint16_t *__restrict__ wpk,
                                                        const float *__restrict__ z1, float *part)
@@ -357,7 +359,7 @@ __global__ __launch_bounds__(D2T, 2) void k_conv2_bwd_d(const int64_t *__restric
         // ahead, behind the products, gained nothing)
         constexpr int NG = (D2HALO * 4 + D2T - 1) / D2T, ND = (D2HALO + D2T - 1) / D2T;
         float4 gv[NG];
-        int64_t qv[ND];
+        SRC qv[ND];
 #pragma unroll
         for (int k = 0; k < NG; k++) {
             const int e = min(tid + D2T * k, D2HALO * 4 - 1);
@@ -389,7 +391,9 @@ __global__ __launch_bounds__(D2T, 2) void k_conv2_bwd_d(const int64_t *__restric
         for (int k = 0; k < ND; k++) {
             const int e = tid + D2T * k, hq = Div24<D2X, D2HALO>::div(min(e, D2HALO - 1)), hx = e - hq * D2X;
             if (e < D2HALO) {
-                const uint16_t d = delta_bf16(qv[k], qs);
+                uint16_t d;
+                if constexpr (std::is_same<SRC, int64_t>::value) d = delta_bf16(qv[k], qs);
+                else d = to_bf16(qv[k]);
 #pragma unroll
                 for (int dx = 0; dx < 3; dx++)
                     if (hx - dx >= 0 && hx - dx < 16) D3[dx][hq * 16 + hx - dx] = d;
@@ -486,8 +490,8 @@ __global__ __launch_bounds__(256) void k_bwd_reduce(const float *__restrict__ pa
 // fewer), and enough to fill the chip.
 static unsigned bwd_grid(int64_t tiles, unsigned most) { return (unsigned)(tiles < most ? tiles : most); }
 
-hipError_t launch_cnn_bwd(const int64_t *q, double qs, const float *phibar, int64_t rs, int n, const float *th,
-                          const float *z1, const uint16_t *a1, const float *z2, const uint16_t *a2, float *part,
+hipError_t launch_cnn_bwd(const int64_t *q, double qs, const float *delta, const float *phibar, int64_t rs, int n,
+                          const float *th, const float *z1, const uint16_t *a1, const float *z2, const uint16_t *a2, float *part,
                           float *g2, uint16_t *wpk, float *dth, hipStream_t s)
 {
     static_assert(DW2_N <= 1024 * NET_C && DW3_N <= 1024 * NET_C && DW1_N <= 16 * D2R * D2Z * NET_C, "a tile's share of the buffer");
@@ -504,7 +508,10 @@ hipError_t launch_cnn_bwd(const int64_t *q, double qs, const float *phibar, int6
     hipLaunchKernelGGL(k_conv2_bwd_w, dim3(gw), dim3(256), 0, s, a1, g2, n, part);
     reduce(gw, DW2_N, NET_C * NET_C * 27, NC2W, NC2B, 1);
     hipLaunchKernelGGL(k_pack_w2t, dim3((D2W_BYTES / 2 + 255) / 256), dim3(256), 0, s, th, wpk);
-    hipLaunchKernelGGL(k_conv2_bwd_d, dim3(gd), dim3(D2T), 0, s, q, qs, g2, n, wpk, z1, part);
+    if (delta)
+        hipLaunchKernelGGL(k_conv2_bwd_d<float>, dim3(gd), dim3(D2T), 0, s, delta, qs, g2, n, wpk, z1, part);
+    else
+        hipLaunchKernelGGL(k_conv2_bwd_d<int64_t>, dim3(gd), dim3(D2T), 0, s, q, qs, g2, n, wpk, z1, part);
     reduce(gd, DW1_N, NET_C * 27, NC1W, NC1B, 0);
     return hipGetLastError();
 }

@@ -263,13 +263,15 @@ hipError_t launch_paint_tiles_add(const float4 *xs, const int *koff, const int64
     return hipGetLastError();
 }
 
-hipError_t launch_paint_tiles_delta(const float4 *xs, const int *koff, const int64_t *quanta, int nseg, int n,
-                                    double scale, double offset, float *delta, int *flag, hipStream_t s)
+hipError_t launch_paint_tiles_delta(const float4 *xs, const int *koff, const int64_t *quanta, int nseg, int seg_lo,
+                                    int seg_hi, int n, double scale, double offset, float *delta, int *flag,
+                                    hipStream_t s)
 {
     const int nt = n / TILE;
-    if (nt < 2) return hipErrorInvalidValue;
+    // rows are stored 16 bytes at a time
+    if (nt < 2 || (reinterpret_cast<uintptr_t>(delta) & 15) != 0) return hipErrorInvalidValue;
     hipLaunchKernelGGL(k_paint_tiles<PAINT_DELTA>, dim3((unsigned)(nt * nt * nt)), dim3(PAINT_T), 0, s, xs, koff, quanta,
-                       nseg, 0, nseg, n, static_cast<void *>(delta), scale, offset, flag);
+                       nseg, seg_lo, seg_hi, n, static_cast<void *>(delta), scale, offset, flag);
     return hipGetLastError();
 }
 

@@ -156,7 +156,9 @@ __device__ __forceinline__ int tile_range_index(int k, const int *rbeg, const in
 }
 
 // Lanes of the wavefront that share this lane's key: the mask and its
-// lowest lane (ballot loop, no memory traffic).
+// lowest lane (ballot loop, no memory traffic).  Stopping after eight keys and
+// letting the lanes left stand for themselves was slower (19 M particles on
+// 512^3: count 381 -> 528 us): device-wide atomics cost more than the loop.
 __device__ __forceinline__ void key_group(bool live, int k, uint64_t &group, int &leader)
 {
     uint64_t todo = __ballot(live);
@@ -288,6 +290,7 @@ struct Ctx {
     // array counts_x); the next sort takes them over and verifies them
     bool counts_ready = false;
     const float *counts_x = nullptr;
+    bool cnt_next_zero = false;   // ws.cnt_next holds zeros (cleared by the scan that took its counts)
     // a verification of taken-over counts still in flight: the flag word is
     // copied to pinned verify_host and verify_ev marks the copy's end
     bool verify_pending = false;
@@ -409,14 +412,13 @@ hipError_t launch_grad3_sum(float2 *F, int64_t nhp, int64_t fs, int n, double sc
 // (optional): added to the CNN output (none: the output is the CNN alone).
 hipError_t launch_cnn_inf(const int64_t *q, double qs, const float *delta, const float *phif, int64_t rs, int n,
                           const float *th, uint16_t *wpk, uint16_t *a2, float *out, hipStream_t s);
-// Training forward, the same CNN on the int64 density mesh q (delta = q qs - 1):
-// also keeps z1, z2 (FP32) and a1, a2 (BF16), each [n^3][16].
-hipError_t launch_cnn_fwd(const int64_t *q, double qs, const float *phif, int64_t rs, int n, const float *th,
+// Training forward, the same CNN on the same inputs: also keeps z1, z2 (FP32) and a1, a2 (BF16), each [n^3][16].
+hipError_t launch_cnn_fwd(const int64_t *q, double qs, const float *delta, const float *phif, int64_t rs, int n, const float *th,
                           uint16_t *wpk, float *z1, uint16_t *a1, float *z2, uint16_t *a2, float *out, hipStream_t s);
 // Reverse mode (net_bwd.hip): dth += the CNN's parameter gradients for the
 // cotangent phibar of its output (real rows of stride rs).  part: scratch of
 // n^3 x 16 floats for the workgroups' partial sums; g2: [n^3][16]; wpk: as above.
-hipError_t launch_cnn_bwd(const int64_t *q, double qs, const float *phibar, int64_t rs, int n, const float *th,
+hipError_t launch_cnn_bwd(const int64_t *q, double qs, const float *delta, const float *phibar, int64_t rs, int n, const float *th,
                           const float *z1, const uint16_t *a1, const float *z2, const uint16_t *a2, float *part,
                           float *g2, uint16_t *wpk, float *dth, hipStream_t s);
 hipError_t launch_force_loss(float *acc, const float *target, int64_t n3, double *red, hipStream_t s);
@@ -433,18 +435,21 @@ hipError_t launch_paint_tiles(const float4 *xs, const int *koff, const int64_t *
 // The same, added to mesh (int64 [N]^3) instead of overwriting its tiles.
 hipError_t launch_paint_tiles_add(const float4 *xs, const int *koff, const int64_t *quanta, int nseg, int seg_lo,
                                   int seg_hi, int n, int64_t *mesh, hipStream_t s);
-// Tile paint of every segment, stored as the float32 density contrast
-// (float)(Q scale + offset) of each cell's exact int64 sum (overflow flag as
-// the transforms raise it).
-hipError_t launch_paint_tiles_delta(const float4 *xs, const int *koff, const int64_t *quanta, int nseg, int n,
-                                    double scale, double offset, float *delta, int *flag, hipStream_t s);
+// Tile paint of segments [seg_lo, seg_hi), stored as the float32 density
+// contrast (float)(Q scale + offset) of each cell's exact int64 sum (overflow
+// flag as the transforms raise it).  delta: 16-byte aligned.
+hipError_t launch_paint_tiles_delta(const float4 *xs, const int *koff, const int64_t *quanta, int nseg, int seg_lo,
+                                    int seg_hi, int n, double scale, double offset, float *delta, int *flag,
+                                    hipStream_t s);
 
 // ---- launchers (sort.hip)
 // Counting sort by tile key: counts per key (cnt zeroed by the caller), an
-// exclusive scan (out2: a second copy, the scatter's cursors), and the
+// exclusive scan of the n - 1 counts and the zero behind them (out2: a second
+// copy, the scatter's cursors; clear: the counts are zeroed), and the
 // scatter of particles to their cursor slots (cursor advanced by the counts).
 hipError_t launch_sort_count(const float *x, int64_t P, int n, int *cnt, hipStream_t s);
-hipError_t launch_scan(const int *in, int *out, int64_t n, int *block_sums, hipStream_t s, int *out2 = nullptr);
+hipError_t launch_scan(int *in, int *out, int64_t n, int *block_sums, hipStream_t s, int *out2 = nullptr,
+                       bool clear = false);
 hipError_t launch_sort_scatter(const float *x, const float *p, const uint8_t *tag_in, int64_t P, int nseg,
                                const int64_t *seg_off, int n, int *cursor, float4 *xs, Mom3 *ps,
                                const uint32_t *ids_in, uint32_t *ids_out, hipStream_t s);

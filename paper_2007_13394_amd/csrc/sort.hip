@@ -27,25 +27,30 @@ inline unsigned grid_for(int64_t n, int block, int64_t cap = 65536LL * 16)
 }
 
 
-// Each workgroup takes SORT_CH consecutive particles, workgroups numbered so
-// that each XCD owns a contiguous run of chunks (the scatter of a nearly
-// sorted state then writes whole cache lines from one L2).
-constexpr int SORT_T = 256, SORT_CH = SORT_T * 8;
+// Each workgroup takes a chunk of NR x SORT_T consecutive particles, workgroups
+// numbered so that each XCD owns a contiguous run of chunks (the scatter of a
+// nearly sorted state then writes whole cache lines from one L2).  Eight rounds
+// per thread where that still gives every CU several workgroups; below
+// SORT_FEW particles one round, since a small sort waits on its chain of
+// rounds and not on memory bandwidth (69 k particles on 64^3: count 27 -> 9 us,
+// scatter 33 -> 11 us; sorted steps 13.3 -> 6.4 us).
+constexpr int SORT_T = 256;
+constexpr int64_t SORT_FEW = 1 << 20;
 // particles per batch in the scatter: two keep it at 38 VGPRs; four and eight
 // (66, 114 VGPRs) gain nothing at 2048^3 and lose at 256^3 (lower occupancy)
 constexpr int SCATTER_SB = 2;
 
-
+template <int NR>
 __global__ __launch_bounds__(SORT_T) void k_sort_count(const float *__restrict__ x, int64_t P, int n, int *cnt)
 {
     const int lane = threadIdx.x & 63;
+    constexpr int SORT_CH = NR * SORT_T;
     const int64_t c0 = (int64_t)xcd_tile(blockIdx.x, gridDim.x) * SORT_CH;
     const int64_t c1 = c0 + SORT_CH < P ? c0 + SORT_CH : P;
     if (c0 >= c1) return;
-    // All rounds' positions are loaded up front (8 per thread; indices past
+    // All rounds' positions are loaded up front (NR per thread; indices past
     // the chunk are clamped to c0, a valid particle); the atomics return
     // nothing, so no round waits on memory after the first.
-    constexpr int NR = SORT_CH / SORT_T;
     float a0[NR], a1[NR], a2[NR];
 #pragma unroll
     for (int r = 0; r < NR; r++) {
@@ -62,6 +67,72 @@ __global__ __launch_bounds__(SORT_T) void k_sort_count(const float *__restrict__
         int leader;
         key_group(live, k, group, leader);
         if (live && lane == leader) atomicAdd(cnt + k, __popcll(group));
+    }
+}
+
+// Exclusive scan of up to SCAN_ONE counts by one workgroup, all loads in
+// flight at once: out[i] = sum of in[0 .. i), out[n - 1] the total (in[n - 1],
+// past the last key, is not read; n - 1 is a multiple of four).  A thread takes
+// four consecutive values of each of R rows; the rows' and wavefronts' totals
+// are scanned by the first wavefront.  clear: zero the counts behind the scan
+// (the next readout adds to them), else out2 may be the counts' own array.  At
+// 32 768 keys (256^3) 8.6 us against 10.3 us and two launches more for the blocked
+// form below.
+constexpr int SCAN_ONE = 32768, ONE_T = 1024;
+
+__device__ __forceinline__ int wave_inclusive(int v, int lane)
+{
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const int t = __shfl_up(v, off);
+        if (lane >= off) v += t;
+    }
+    return v;
+}
+
+template <int R>
+__global__ __launch_bounds__(ONE_T) void k_scan_one(int *in, int *out, int n, int *out2, int clear)
+{
+    constexpr int NW = ONE_T / 64;
+    __shared__ int tot[R * NW + 1];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, m = n - 1;
+    int4 v[R];
+    int incl[R];
+#pragma unroll
+    for (int r = 0; r < R; r++) {
+        const int i = 4 * (r * ONE_T + tid);
+        v[r] = i < m ? *reinterpret_cast<const int4 *>(in + i) : make_int4(0, 0, 0, 0);
+    }
+#pragma unroll
+    for (int r = 0; r < R; r++) {
+        incl[r] = wave_inclusive(v[r].x + v[r].y + v[r].z + v[r].w, lane);
+        if (lane == 63) tot[r * NW + wave] = incl[r];
+    }
+    __syncthreads();
+    if (wave == 0) {
+        static_assert(R * NW <= 128, "two totals per lane");
+        const int a = 2 * lane < R * NW ? tot[2 * lane] : 0, b = 2 * lane + 1 < R * NW ? tot[2 * lane + 1] : 0;
+        const int e = wave_inclusive(a + b, lane) - a - b;
+        if (2 * lane < R * NW) tot[2 * lane] = e;
+        if (2 * lane + 1 < R * NW) tot[2 * lane + 1] = e + a;
+        if (lane == 63) tot[R * NW] = e + a + b;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < R; r++) {
+        const int i = 4 * (r * ONE_T + tid);
+        if (i < m) {
+            const int e = tot[r * NW + wave] + incl[r] - (v[r].x + v[r].y + v[r].z + v[r].w);
+            const int4 o = make_int4(e, e + v[r].x, e + v[r].x + v[r].y, e + v[r].x + v[r].y + v[r].z);
+            *reinterpret_cast<int4 *>(out + i) = o;
+            if (clear) *reinterpret_cast<int4 *>(in + i) = make_int4(0, 0, 0, 0);
+            if (out2) *reinterpret_cast<int4 *>(out2 + i) = o;
+        }
+    }
+    if (tid == 0) {
+        out[m] = tot[R * NW];
+        if (clear) in[m] = 0;
+        if (out2) out2[m] = tot[R * NW];
     }
 }
 
@@ -85,7 +156,7 @@ __device__ __forceinline__ int block_exclusive_scan(int v, int *sh)
     return incl - v;
 }
 
-__global__ __launch_bounds__(SCAN_T) void k_scan_blocks(const int *in, int *out, int64_t n, int *block_sums)
+__global__ __launch_bounds__(SCAN_T) void k_scan_blocks(int *in, int *out, int64_t n, int *block_sums, int clear)
 {
     __shared__ int sh[SCAN_T];
     const int64_t base = (int64_t)blockIdx.x * SCAN_B + (int64_t)threadIdx.x * SCAN_PER;
@@ -99,7 +170,10 @@ __global__ __launch_bounds__(SCAN_T) void k_scan_blocks(const int *in, int *out,
     int run = pre;
 #pragma unroll
     for (int j = 0; j < SCAN_PER; j++) {
-        if (base + j < n) out[base + j] = run;
+        if (base + j < n) {
+            out[base + j] = run;
+            if (clear) in[base + j] = 0;
+        }
         run += v[j];
     }
     if (threadIdx.x == SCAN_T - 1) block_sums[blockIdx.x] = run;
@@ -146,18 +220,17 @@ __global__ void k_scan_add(int *out, int64_t n, const int *sums, int *out2)
 // Scatter into float4 records: one 16-byte store for the position and the
 // segment tag, one for the momentum, so a particle that moves far in the
 // order costs two stores instead of seven partial ones.  The optional arrays
-// are template flags.  A thread takes its eight particles in batches of SB:
+// are template flags.  A thread takes its NR particles in batches of SB:
 // a batch's particles are loaded at once, then its cursor atomics are issued
 // back to back, then its stores (two memory round trips per batch).  The
 // pointers do not alias (caller arrays in, workspace records out).
-template <bool HP, bool HT, bool HI, int SB>
+template <bool HP, bool HT, bool HI, int NR, int SB>
 __device__ __forceinline__ void scatter_chunk(int64_t c0, int64_t c1, const float *__restrict__ x,
                                               const float *__restrict__ p, const uint8_t *__restrict__ tag_in,
                                               int64_t P, int nseg, const int64_t *__restrict__ seg_off, int n,
                                               int *cursor, float4 *__restrict__ xs, Mom3 *__restrict__ ps,
                                               const uint32_t *__restrict__ ids_in, uint32_t *__restrict__ ids_out)
 {
-    constexpr int NR = SORT_CH / SORT_T;
     static_assert(NR % SB == 0, "whole batches");
     const int lane = threadIdx.x & 63;
     for (int r0 = 0; r0 < NR; r0 += SB) {
@@ -212,17 +285,19 @@ __device__ __forceinline__ void scatter_chunk(int64_t c0, int64_t c1, const floa
     }
 }
 
+template <int NR>
 __global__ __launch_bounds__(SORT_T) void k_sort_scatter(const float *__restrict__ x, const float *__restrict__ p,
                                                          const uint8_t *__restrict__ tag_in, int64_t P, int nseg,
                                                          const int64_t *__restrict__ seg_off, int n, int *cursor,
                                                          float4 *xs, Mom3 *ps, const uint32_t *ids_in,
                                                          uint32_t *ids_out)
 {
+    constexpr int SORT_CH = NR * SORT_T;
     const int64_t c0 = (int64_t)xcd_tile(blockIdx.x, gridDim.x) * SORT_CH;
     const int64_t c1 = c0 + SORT_CH < P ? c0 + SORT_CH : P;
     if (c0 >= c1) return;
 #define SCATTER(HP, HT, HI) \
-    scatter_chunk<HP, HT, HI, SCATTER_SB>(c0, c1, x, p, tag_in, P, nseg, seg_off, n, cursor, xs, ps, ids_in, ids_out)
+    scatter_chunk<HP, HT, HI, NR, (NR < SCATTER_SB ? NR : SCATTER_SB)>(c0, c1, x, p, tag_in, P, nseg, seg_off, n, cursor, xs, ps, ids_in, ids_out)
     if (p) {
         if (tag_in) {
             if (ids_in) SCATTER(true, true, true);
@@ -265,17 +340,31 @@ hipError_t launch_sort_verify(const int *cursor, const int *koff, int64_t K, int
 
 hipError_t launch_sort_count(const float *x, int64_t P, int n, int *cnt, hipStream_t s)
 {
-    const int64_t nb = (P + SORT_CH - 1) / SORT_CH;
+    const int nr = P < SORT_FEW ? 1 : 8;
+    const int64_t nb = (P + nr * SORT_T - 1) / (nr * SORT_T);
     if (nb > 0x7fffffff) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_sort_count, dim3((unsigned)(nb > 0 ? nb : 1)), dim3(SORT_T), 0, s, x, P, n, cnt);
+    const dim3 grid((unsigned)(nb > 0 ? nb : 1));
+    if (nr == 1)
+        hipLaunchKernelGGL(k_sort_count<1>, grid, dim3(SORT_T), 0, s, x, P, n, cnt);
+    else
+        hipLaunchKernelGGL(k_sort_count<8>, grid, dim3(SORT_T), 0, s, x, P, n, cnt);
     return hipGetLastError();
 }
 
-hipError_t launch_scan(const int *in, int *out, int64_t n, int *block_sums, hipStream_t s, int *out2)
+hipError_t launch_scan(int *in, int *out, int64_t n, int *block_sums, hipStream_t s, int *out2, bool clear)
 {
+    if (clear && (out2 == in || out == in)) return hipErrorInvalidValue;
+    if (n - 1 <= SCAN_ONE && (n - 1) % 4 == 0 &&
+        ((reinterpret_cast<uintptr_t>(in) | reinterpret_cast<uintptr_t>(out) | reinterpret_cast<uintptr_t>(out2)) & 15) == 0) {
+        if (n - 1 <= 4 * ONE_T)
+            hipLaunchKernelGGL(k_scan_one<1>, dim3(1), dim3(ONE_T), 0, s, in, out, (int)n, out2, clear ? 1 : 0);
+        else
+            hipLaunchKernelGGL(k_scan_one<8>, dim3(1), dim3(ONE_T), 0, s, in, out, (int)n, out2, clear ? 1 : 0);
+        return hipGetLastError();
+    }
     const int64_t nb = (n + SCAN_B - 1) / SCAN_B;
     if (nb > (int64_t)SCAN_B * 4096) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_scan_blocks, dim3((unsigned)nb), dim3(SCAN_T), 0, s, in, out, n, block_sums);
+    hipLaunchKernelGGL(k_scan_blocks, dim3((unsigned)nb), dim3(SCAN_T), 0, s, in, out, n, block_sums, clear ? 1 : 0);
     hipLaunchKernelGGL(k_scan_sums, dim3(1), dim3(SCAN_T), 0, s, block_sums, (int)nb);
     hipLaunchKernelGGL(k_scan_add, dim3(grid_for(n, 256)), dim3(256), 0, s, out, n, block_sums, out2);
     return hipGetLastError();
@@ -285,10 +374,16 @@ hipError_t launch_sort_scatter(const float *x, const float *p, const uint8_t *ta
                                const int64_t *seg_off, int n, int *cursor, float4 *xs, Mom3 *ps,
                                const uint32_t *ids_in, uint32_t *ids_out, hipStream_t s)
 {
-    const int64_t nb = (P + SORT_CH - 1) / SORT_CH;
+    const int nr = P < SORT_FEW ? 1 : 8;
+    const int64_t nb = (P + nr * SORT_T - 1) / (nr * SORT_T);
     if (nb > 0x7fffffff) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_sort_scatter, dim3((unsigned)(nb > 0 ? nb : 1)), dim3(SORT_T), 0, s, x, p, tag_in, P, nseg,
-                       seg_off, n, cursor, xs, ps, ids_in, ids_out);
+    const dim3 grid((unsigned)(nb > 0 ? nb : 1));
+    if (nr == 1)
+        hipLaunchKernelGGL(k_sort_scatter<1>, grid, dim3(SORT_T), 0, s, x, p, tag_in, P, nseg, seg_off, n, cursor, xs, ps,
+                           ids_in, ids_out);
+    else
+        hipLaunchKernelGGL(k_sort_scatter<8>, grid, dim3(SORT_T), 0, s, x, p, tag_in, P, nseg, seg_off, n, cursor, xs, ps,
+                           ids_in, ids_out);
     return hipGetLastError();
 }
 
