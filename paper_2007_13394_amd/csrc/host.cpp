@@ -183,7 +183,7 @@ Layout layout(const pm_config &c)
         L.net_acc = take((size_t)(3 * P) * 4);
         L.net_table = take(pm::NET_NB * 4);
         L.net_tbar = take(pm::NET_NB * 8);
-        L.net_red = take(64);
+        L.net_red = take((size_t)pm::RED_SLOTS * 4 * 8);
         L.net_wpk = take(pm::NET_WPK_BYTES);
     }
     L.total = off;
@@ -281,6 +281,34 @@ pm_status check_guards(pm_ctx *c, hipStream_t s)
 
 bool sorting_on(const pm_ctx *c) { return c->nkeys > 0 && !(c->cfg.flags & PM_FLAG_NO_SORT); }
 
+// Force meshes (planes ps_f, components comp apart) read out at x for
+// particles in the caller's order: by tile from the records paint_density has
+// sorted, else a gather.
+pm_status readout_force(pm_ctx *c, const float *x, int64_t ps_f, int64_t comp, float *acc, hipStream_t s)
+{
+    const int64_t nhp = pm::half_pad(c->n);
+    if (c->nkeys > 0)
+        LAUNCH(pm::K_READOUT, pm::launch_readout_tiles(c->ws.xs, c->ws.ids_tmp, c->P, c->ws.koff, c->ws.f, nhp, ps_f, comp,
+                                                       c->n, acc, s));
+    else
+        LAUNCH(pm::K_READOUT, pm::launch_readout(x, c->P, c->ws.f, nhp, ps_f, comp, c->n, acc, s));
+    return PM_OK;
+}
+
+// The same with the kick and the drift, in place.
+pm_status readout_step(pm_ctx *c, float *x, float *p, int64_t ps_f, int64_t comp, double kick, double drift, hipStream_t s)
+{
+    const int64_t nhp = pm::half_pad(c->n);
+    if (c->nkeys > 0)
+        LAUNCH(pm::K_READOUT_KD,
+               pm::launch_readout_kd_index_tiles(c->ws.xs, c->ws.ids_tmp, c->P, c->ws.koff, c->ws.f, nhp, ps_f, comp, c->n,
+                                                 (float)kick, (float)drift, x, p, c->ws.flag, s));
+    else
+        LAUNCH(pm::K_READOUT_KD, pm::launch_readout_kick_drift(x, p, c->P, c->ws.f, nhp, ps_f, comp, c->n, (float)kick,
+                                                               (float)drift, c->ws.flag, s));
+    return PM_OK;
+}
+
 // Paint segments [lo, hi) of x (in the context's current particle order)
 // into `mesh` with global atomics; the caller zeroes the mesh.
 pm_status paint_atomic(pm_ctx *c, const float *x, int lo, int hi, int64_t *mesh, hipStream_t s)
@@ -370,10 +398,11 @@ pm_status finish_sort(pm_ctx *c, const float *x, const float *p, hipStream_t s, 
 }
 
 // Position records (with segment tags) of x, and with v the records of a
-// particle vector, sorted by tile into xs, ps with the key offsets koff; the caller's arrays and the context's order stay as they
+// particle vector, sorted by tile into xs, ps with the key offsets koff (index:
+// also each record's particle, into ids_tmp); the caller's arrays and the context's order stay as they
 // are, and so do the counts that a sorted step left for the next one.  The
 // count scratch may alias the F region, which must be free.
-pm_status tile_records(pm_ctx *c, const float *x, const float *v, hipStream_t s)
+pm_status tile_records(pm_ctx *c, const float *x, const float *v, bool index, hipStream_t s)
 {
     const int64_t K = c->nkeys;
     LAUNCH(pm::K_FILL, pm::launch_fill_i32(c->ws.cnt, K + 1, s));
@@ -381,7 +410,8 @@ pm_status tile_records(pm_ctx *c, const float *x, const float *v, hipStream_t s)
     LAUNCH(pm::K_SORT_SCAN, pm::launch_scan(c->ws.cnt, c->ws.koff, K + 1, c->ws.bsum, s, c->ws.cnt));
     LAUNCH(pm::K_SORT_SCATTER,
            pm::launch_sort_scatter(x, v, c->permuted ? c->ws.tags : nullptr, c->P, c->nseg, c->ws.seg_off, c->n,
-                                   c->ws.cnt, c->ws.xs, v ? c->ws.ps : nullptr, nullptr, nullptr, s));
+                                   c->ws.cnt, c->ws.xs, v ? c->ws.ps : nullptr, nullptr,
+                                   index ? c->ws.ids_tmp : nullptr, s));
     return PM_OK;
 }
 
@@ -392,14 +422,14 @@ pm_status tile_records(pm_ctx *c, const float *x, const float *v, hipStream_t s)
 // per cell instead of eight scattered 8-byte atomics per particle, which the
 // eight L2s cannot combine (v: also sorted into ps): 19 M particles on 512^3 take 1.3 ms (count, scan,
 // scatter, paint) against 3.9 ms, 69 k on 64^3 40 us against 105 us.
-pm_status paint_density(pm_ctx *c, const float *x, const float *v, hipStream_t s, const float **delta)
+pm_status paint_density(pm_ctx *c, const float *x, const float *v, bool index, hipStream_t s, const float **delta)
 {
     *delta = nullptr;
     if (c->nkeys == 0) {
         LAUNCH(pm::K_FILL, pm::launch_fill_i64(c->ws.q, (int64_t)c->n * c->n * c->n, s));
         return paint_atomic(c, x, 0, c->nseg, c->ws.q, s);
     }
-    pm_status st = tile_records(c, x, v, s);
+    pm_status st = tile_records(c, x, v, index, s);
     if (st != PM_OK) return st;
     float *d = reinterpret_cast<float *>(c->ws.q);
     LAUNCH(pm::K_PAINT, pm::launch_paint_tiles_delta(c->ws.xs, c->ws.koff, c->ws.quanta, c->nseg, 0, c->nseg, c->n,
@@ -480,6 +510,13 @@ pm_status forward_density(pm_ctx *c, int64_t *q, double scale, hipStream_t s)
     return PM_OK;
 }
 
+// Fixed-point unit 1 / S of a cotangent paint: S a power of two such that even
+// all particles' largest cotangent gm in one cell stays below 2^62.
+double cotangent_unit(int64_t P, float gm)
+{
+    return gm > 0 && std::isfinite(gm) ? ldexp(1.0, 61 - (int)ceil(log2((double)P * (double)gm))) : 1.0;
+}
+
 // xbar += gscale (d acc / d x)^T g for the differentiable model (exact
 // segment masses, cloud-in-cell weights): the readout-derivative term from the
 // force meshes at x, then the cotangents painted with the readout weights,
@@ -498,12 +535,12 @@ pm_status force_vjp(pm_ctx *c, const float *x, const float *g, double gscale, fl
     // Either way the integers are the same.
     const bool tiles = c->nkeys > 0;
     const float *delta;
-    pm_status st = paint_density(c, x, g, s, &delta);
+    pm_status st = paint_density(c, x, g, true, s, &delta);
     if (st != PM_OK) return st;
     st = solve(c, c->ws.q, s, delta);
     if (st != PM_OK) return st;
-    // cotangent paint in fixed point, one component at a time through Q (free
-    // after the solve): a unit of 1/S with S a power of two such that even all
+    // cotangent paint in fixed point, in the F region once the forces are read
+    // out (without tiles one component at a time through Q): a unit of 1/S with S a power of two such that even all
     // particles' largest cotangent in one cell stays below 2^62, so the mesh
     // and the gradient are bit-reproducible
     unsigned *gmax = reinterpret_cast<unsigned *>(c->ws.flag) + 8;
@@ -516,21 +553,28 @@ pm_status force_vjp(pm_ctx *c, const float *x, const float *g, double gscale, fl
     float gm;
     memcpy(&gm, &mbits, sizeof gm);
     if (!std::isfinite(gm)) return fail(PM_ERR_NAN, "a cotangent is not finite");
-    const double S = gm > 0 ? ldexp(1.0, 61 - (int)ceil(log2((double)c->P * (double)gm))) : 1.0;
+    const double S = cotangent_unit(c->P, gm);
     // a non-finite cotangent is reported before xbar is touched
     const int64_t fp = pm::force_plane(n);   // the force meshes' plane stride
-    LAUNCH(pm::K_ADJOINT,
-           pm::launch_readout_grad3(x, c->P, g, (float)gscale, Fr, 2 * nhp, 2 * fp, 2 * n * fp, n, xbar, s));
+    if (tiles)
+        LAUNCH(pm::K_ADJOINT, pm::launch_readout_grad3_tiles(c->ws.xs, c->ws.ids_tmp, c->P, c->ws.koff, F, nhp, fp, n * fp,
+                                                             n, c->ws.ps, (float)gscale, xbar, s));
+    else
+        LAUNCH(pm::K_ADJOINT,
+               pm::launch_readout_grad3(x, c->P, g, (float)gscale, Fr, 2 * nhp, 2 * fp, 2 * n * fp, n, xbar, s));
+    if (tiles)
+        LAUNCH(pm::K_ADJOINT, pm::launch_paint_q3_tiles(c->ws.xs, c->ws.ps, c->ws.koff, (float)gscale, S, 1.0 / S, n, Fr,
+                                                        2 * nhp, 2 * cs, s));
     for (int d = 0; d < 3; d++) {
         float2 *Fd = F + d * cs;
         if (tiles) {
-            LAUNCH(pm::K_ADJOINT, pm::launch_paint_q1_tiles(c->ws.xs, c->ws.ps, d, c->ws.koff, (float)gscale, S, n,
-                                                            c->ws.q, s));
+            LAUNCH(pm::K_R2C, pm::launch_r2c_rows_f32(lg, reinterpret_cast<float *>(Fd), 2 * nhp, Fd, nhp, n2, c->ws.tw, s));
         } else {
             LAUNCH(pm::K_FILL, pm::launch_fill_i64(c->ws.q, (int64_t)n * n * n, s));
             LAUNCH(pm::K_ADJOINT, pm::launch_paint_q1(x, c->P, g + d * c->P, (float)gscale, S, n, c->ws.q, s));
+            LAUNCH(pm::K_R2C,
+                   pm::launch_r2c_rows_i64(lg, c->ws.q, n, Fd, nhp, n2, 1.0 / S, 0.0, c->ws.tw, unused_flag, s));
         }
-        LAUNCH(pm::K_R2C, pm::launch_r2c_rows_i64(lg, c->ws.q, n, Fd, nhp, n2, 1.0 / S, 0.0, c->ws.tw, unused_flag, s));
         LAUNCH(pm::K_COLS_FWD, pm::launch_cols(lg, false, Fd, nhp, n * nhp, n, ncb, c->ws.tw, s));
         LAUNCH(pm::K_COLS_FWD, pm::launch_cols(lg, false, Fd, n * nhp, nhp, n, ncb, c->ws.tw, s));
     }
@@ -1063,12 +1107,12 @@ pm_status pm_force(pm_ctx *c, const float *x, float *acc, void *stream)
     if (!c || !x || !acc) return fail(PM_ERR_ARG, "NULL argument to pm_force");
     hipStream_t s = S(stream);
     const float *delta;
-    pm_status st = paint_density(c, x, nullptr, s, &delta);
+    pm_status st = paint_density(c, x, nullptr, true, s, &delta);
     if (st == PM_OK) st = solve(c, c->ws.q, s, delta);
     if (st != PM_OK) return st;
-    const int64_t n = c->n, nhp = pm::half_pad(c->n), fp = pm::force_plane(c->n);
-    LAUNCH(pm::K_READOUT, pm::launch_readout(x, c->P, c->ws.f, nhp, fp, n * fp, c->n, acc, s));
-    return check_guards(c, s);
+    const int64_t fp = pm::force_plane(c->n);
+    st = readout_force(c, x, fp, c->n * fp, acc, s);
+    return st == PM_OK ? check_guards(c, s) : st;
 }
 
 pm_status pm_step(pm_ctx *c, float *x, float *p, double a_force, double a_kick0, double a_kick1, double a_drift1,
@@ -1110,12 +1154,11 @@ pm_status pm_step(pm_ctx *c, float *x, float *p, double a_force, double a_kick0,
         return check_guards(c, s);
     }
     const float *delta;
-    st = paint_density(c, x, nullptr, s, &delta);
+    st = paint_density(c, x, nullptr, true, s, &delta);
     if (st == PM_OK) st = solve(c, c->ws.q, s, delta);
     if (st != PM_OK) return st;
-    LAUNCH(pm::K_READOUT_KD, pm::launch_readout_kick_drift(x, p, c->P, c->ws.f, nhp, fp, n * fp, c->n, (float)kick,
-                                                           (float)drift, c->ws.flag, s));
-    return check_guards(c, s);
+    st = readout_step(c, x, p, fp, n * fp, kick, drift, s);
+    return st == PM_OK ? check_guards(c, s) : st;
 }
 
 pm_status pm_attach_ids(pm_ctx *c, uint32_t *ids)
@@ -1177,7 +1220,7 @@ pm_status pm_power(pm_ctx *c, const float *x, int32_t a_lo, int32_t a_hi, int32_
         LAUNCH(pm::K_FILL, pm::launch_fill_i64(q, M, s));
         return paint_atomic(c, x, lo, hi, q, s);
     };
-    pm_status st = tiles ? tile_records(c, x, nullptr, s) : PM_OK;
+    pm_status st = tiles ? tile_records(c, x, nullptr, false, s) : PM_OK;
     if (st == PM_OK) st = paint(a_lo, a_hi, c->ws.q);
     if (st == PM_OK) st = forward_density(c, c->ws.q, scale_of(a_lo, a_hi), s);
     if (st != PM_OK) return st;
@@ -1258,7 +1301,7 @@ pm_status pm_density(pm_ctx *c, const float *x, float *delta, void *stream)
         // the tile paint stores 16 bytes at a time: a caller's mesh that is not
         // aligned for it is copied to from the workspace.  No cell is refused
         // here (the flag goes to an unused word).
-        pm_status st = tile_records(c, x, nullptr, s);
+        pm_status st = tile_records(c, x, nullptr, false, s);
         if (st != PM_OK) return st;
         const bool aligned = (reinterpret_cast<uintptr_t>(delta) & 15) == 0;
         float *d = aligned ? delta : reinterpret_cast<float *>(c->ws.q);
@@ -1368,12 +1411,12 @@ pm_status pm_learned_force(pm_ctx *c, const float *th, double a, const float *x,
     if (st != PM_OK) return st;
     hipStream_t s = S(stream);
     const float *delta;
-    st = paint_density(c, x, nullptr, s, &delta);
+    st = paint_density(c, x, nullptr, true, s, &delta);
     if (st == PM_OK) st = learned_solve(c, th, a, false, s, delta);
     if (st != PM_OK) return st;
     const int64_t n = c->n, nhp = pm::half_pad(c->n);
-    LAUNCH(pm::K_READOUT, pm::launch_readout(x, c->P, c->ws.f, nhp, n * nhp, n * n * nhp, c->n, acc, s));
-    return check_guards(c, s);
+    st = readout_force(c, x, n * nhp, n * n * nhp, acc, s);
+    return st == PM_OK ? check_guards(c, s) : st;
 }
 
 pm_status pm_learned_step(pm_ctx *c, const float *th, float *x, float *p, double a_force, double a_kick0,
@@ -1413,12 +1456,11 @@ pm_status pm_learned_step(pm_ctx *c, const float *th, float *x, float *p, double
         return check_guards(c, s);
     }
     const float *delta;
-    st = paint_density(c, x, nullptr, s, &delta);
+    st = paint_density(c, x, nullptr, true, s, &delta);
     if (st == PM_OK) st = learned_solve(c, th, a_force, false, s, delta);
     if (st != PM_OK) return st;
-    LAUNCH(pm::K_READOUT_KD, pm::launch_readout_kick_drift(x, p, c->P, c->ws.f, nhp, n * nhp, n * n * nhp, c->n, (float)kick,
-                                                           (float)drift, c->ws.flag, s));
-    return check_guards(c, s);
+    st = readout_step(c, x, p, n * nhp, n * n * nhp, kick, drift, s);
+    return st == PM_OK ? check_guards(c, s) : st;
 }
 
 pm_status pm_learned_loss(pm_ctx *c, const float *th, double a, const float *x, const float *target, double *loss,
@@ -1435,21 +1477,51 @@ pm_status pm_learned_loss(pm_ctx *c, const float *th, double a, const float *x, 
     float2 *F = c->ws.f;
     float *Fr = reinterpret_cast<float *>(F);
     const float *delta;
-    st = paint_density(c, x, nullptr, s, &delta);
+    st = paint_density(c, x, nullptr, true, s, &delta);
     if (st == PM_OK) st = learned_solve(c, th, a, dth != nullptr, s, delta);
     if (st != PM_OK) return st;
-    LAUNCH(pm::K_READOUT, pm::launch_readout(x, c->P, F, nhp, n * nhp, cs, n, c->ws.net_acc, s));
-    LAUNCH(pm::K_NET, pm::launch_force_loss(c->ws.net_acc, target, 3 * c->P, c->ws.net_red, s));
-    double red[2];
-    if (hipMemcpyAsync(red, c->ws.net_red, sizeof(red), hipMemcpyDeviceToHost, s) != hipSuccess ||
+    const bool tiles = c->nkeys > 0;
+    if (tiles) {
+        // the force error goes to the sorted records' vectors
+        LAUNCH(pm::K_FILL, pm::launch_zero_f64(c->ws.net_red, 4 * pm::RED_SLOTS, s));
+        LAUNCH(pm::K_READOUT, pm::launch_readout_loss_tiles(c->ws.xs, c->ws.ids_tmp, c->P, c->ws.koff, F, nhp, n * nhp, cs,
+                                                            n, target, c->ws.ps, c->ws.net_red, s));
+    } else {
+        LAUNCH(pm::K_READOUT, pm::launch_readout(x, c->P, F, nhp, n * nhp, cs, n, c->ws.net_acc, s));
+        LAUNCH(pm::K_NET, pm::launch_force_loss(c->ws.net_acc, target, 3 * c->P, c->ws.net_red, s));
+    }
+    double slots[4 * pm::RED_SLOTS];
+    const int nslots = tiles ? pm::RED_SLOTS : 1;
+    if (hipMemcpyAsync(slots, c->ws.net_red, (tiles ? 4 * nslots : 2) * sizeof(double), hipMemcpyDeviceToHost, s) !=
+            hipSuccess ||
         hipStreamSynchronize(s) != hipSuccess)
         return fail(PM_ERR_DEVICE, "reading the loss back failed");
+    double red[2] = {0.0, 0.0};
+    unsigned ebits = 0;   // the largest force error, as integers order (tiles only)
+    for (int k = 0; k < nslots; k++) {
+        red[0] += slots[4 * k];
+        red[1] += slots[4 * k + 1];
+        unsigned e = 0;
+        if (tiles) memcpy(&e, slots + 4 * k + 2, sizeof e);
+        ebits = e > ebits ? e : ebits;
+    }
     if (!(red[1] > 0)) return fail(PM_ERR_ARG, "the target forces are all zero");
     *loss = red[0] / red[1];
     if (!dth) return check_guards(c, s);
     // readout transpose, gradient transpose, CNN and filter reverse mode
-    LAUNCH(pm::K_FILL, pm::launch_fill_i64(reinterpret_cast<int64_t *>(F), 3 * cs, s));
-    LAUNCH(pm::K_ADJOINT, pm::launch_paint_vec3(x, c->P, c->ws.net_acc, (float)(2.0 / red[1]), Fr, rs, 2 * cs, n, s));
+    if (tiles) {
+        // fixed point as in force_vjp, from the largest error; one that is
+        // not finite makes the whole cotangent NaN (as the transforms would)
+        const float gs = (float)(2.0 / red[1]);
+        float em;
+        memcpy(&em, &ebits, sizeof em);
+        const double S = cotangent_unit(c->P, gs * em);
+        LAUNCH(pm::K_ADJOINT, pm::launch_paint_q3_tiles(c->ws.xs, c->ws.ps, c->ws.koff, gs, S,
+                                                        std::isfinite(gs * em) ? 1.0 / S : (double)NAN, n, Fr, rs, 2 * cs, s));
+    } else {
+        LAUNCH(pm::K_FILL, pm::launch_fill_i64(reinterpret_cast<int64_t *>(F), 3 * cs, s));
+        LAUNCH(pm::K_ADJOINT, pm::launch_paint_vec3(x, c->P, c->ws.net_acc, (float)(2.0 / red[1]), Fr, rs, 2 * cs, n, s));
+    }
     for (int d = 0; d < 3; d++) {
         float2 *Fd = F + d * cs;
         LAUNCH(pm::K_R2C, pm::launch_r2c_rows_f32(lg, reinterpret_cast<float *>(Fd), rs, Fd, nhp, n2, c->ws.tw, s));

@@ -103,47 +103,14 @@ __global__ __launch_bounds__(256) void k_readout_kick_drift(float *x, float *p, 
     if (bad) atomicOr(flag, FLAG_NAN);
 }
 
-// One workgroup per TILE^3 tile: the three force meshes over the tile and its
-// +1 halo are staged in LDS, then every particle sorted into the tile is read
-// out from LDS, kicked and drifted; results go to the caller's arrays at the
-// particle's sorted index (with its id, when ids are attached).
-// 1024 threads: the 77 KB LDS tile allows two workgroups per CU, so the
-// workgroup itself must carry enough waves to hide memory latency (the LDS
-// fill has four loads per thread; 1024 threads took the C3 readout from 46.0
-// to 45.3 ms against 512).  The
-// particle range and each thread's first particle are loaded before the LDS
-// fill, and the next particle is loaded before the current one is stored.
-constexpr int READOUT_T = 1024;
+constexpr int READOUT_T = 1024, FORCE_H = TILE + 1;
 
-__global__ __launch_bounds__(READOUT_T) void k_readout_kd_tiles(const float4 *__restrict__ xs,
-                                                                const Mom3 *__restrict__ ps, int64_t P,
-                                                                const int *__restrict__ koff,
-                                                                const float *__restrict__ F, int64_t rs,
-                                                                int64_t fps, int64_t cs, int n, float kick, float drift,
-                                                                float *x, float *p, uint8_t *tags,
-                                                                const uint32_t *__restrict__ ids_tmp,
-                                                                uint32_t *ids, int *flag, int *cnt_next)
+// The three force meshes over a tile and its +1 halo into LDS, the components of
+// a cell interleaved in one float4 (READOUT_T threads; the caller's barrier).
+__device__ __forceinline__ void stage_force(float4 *fl, const float *__restrict__ F, int64_t rs, int64_t fps, int64_t cs,
+                                            int o0, int o1, int o2, int mask)
 {
-    // LDS: the (TILE + 1)^3 cells of the tile and its +1 halo, the three
-    // force components of a cell interleaved in one float4
-    constexpr int H = TILE + 1, ROWS = H * H, NB = 27 * 8;
-    __shared__ float4 fl[ROWS * H];
-    __shared__ int hist[NB];   // next-step key counts of this tile and its neighbours (cnt_next)
-    const int nt = n / TILE, mask = n - 1;
-    // workgroups walk the tiles in row-major order (consecutive tiles share
-    // rows of the force mesh); particle ranges are looked up by Morton index
-    const int bt = xcd_tile(blockIdx.x, gridDim.x);
-    const int t0 = bt / (nt * nt), t1 = (bt / nt) % nt, t2 = bt % nt;
-    const int t = tile_index(t0, t1, t2);
-    const int o0 = t0 * TILE, o1 = t1 * TILE, o2 = t2 * TILE;
-    const int beg = koff[t * 8], end = koff[t * 8 + 8];
-    int i = beg + threadIdx.x;
-    float4 ur = make_float4(0.f, 0.f, 0.f, 0.f);
-    Mom3 vr{0.f, 0.f, 0.f};
-    if (i < end) {
-        ur = xs[i];
-        vr = ps[i];
-    }
+    constexpr int H = FORCE_H, ROWS = H * H;
     // (row, quad) tasks: one 16-byte load per component (rows start 64-byte
     // aligned), four cells written; then one task per row for the halo cell
     for (int e = threadIdx.x; e < ROWS * 4; e += READOUT_T) {
@@ -163,6 +130,48 @@ __global__ __launch_bounds__(READOUT_T) void k_readout_kd_tiles(const float4 *__
         const float *src = F + (int64_t)((o0 + a) & mask) * fps + (int64_t)((o1 + b) & mask) * rs + ((o2 + TILE) & mask);
         fl[rr * H + TILE] = make_float4(src[0], src[cs], src[2 * cs], 0.f);
     }
+}
+
+// One workgroup per TILE^3 tile: the three force meshes over the tile and its
+// +1 halo are staged in LDS, then every particle sorted into the tile is read
+// out from LDS, kicked and drifted; results go to the caller's arrays at the
+// particle's sorted index (with its id, when ids are attached).
+// 1024 threads: the 77 KB LDS tile allows two workgroups per CU, so the
+// workgroup itself must carry enough waves to hide memory latency (the LDS
+// fill has four loads per thread; 1024 threads took the C3 readout from 46.0
+// to 45.3 ms against 512).  The
+// particle range and each thread's first particle are loaded before the LDS
+// fill, and the next particle is loaded before the current one is stored.
+__global__ __launch_bounds__(READOUT_T) void k_readout_kd_tiles(const float4 *__restrict__ xs,
+                                                                const Mom3 *__restrict__ ps, int64_t P,
+                                                                const int *__restrict__ koff,
+                                                                const float *__restrict__ F, int64_t rs,
+                                                                int64_t fps, int64_t cs, int n, float kick, float drift,
+                                                                float *x, float *p, uint8_t *tags,
+                                                                const uint32_t *__restrict__ ids_tmp,
+                                                                uint32_t *ids, int *flag, int *cnt_next)
+{
+    // LDS: the (TILE + 1)^3 cells of the tile and its +1 halo, the three
+    // force components of a cell interleaved in one float4
+    constexpr int H = FORCE_H, ROWS = H * H, NB = 27 * 8;
+    __shared__ float4 fl[ROWS * H];
+    __shared__ int hist[NB];   // next-step key counts of this tile and its neighbours (cnt_next)
+    const int nt = n / TILE, mask = n - 1;
+    // workgroups walk the tiles in row-major order (consecutive tiles share
+    // rows of the force mesh); particle ranges are looked up by Morton index
+    const int bt = xcd_tile(blockIdx.x, gridDim.x);
+    const int t0 = bt / (nt * nt), t1 = (bt / nt) % nt, t2 = bt % nt;
+    const int t = tile_index(t0, t1, t2);
+    const int o0 = t0 * TILE, o1 = t1 * TILE, o2 = t2 * TILE;
+    const int beg = koff[t * 8], end = koff[t * 8 + 8];
+    int i = beg + threadIdx.x;
+    float4 ur = make_float4(0.f, 0.f, 0.f, 0.f);
+    Mom3 vr{0.f, 0.f, 0.f};
+    if (i < end) {
+        ur = xs[i];
+        vr = ps[i];
+    }
+    stage_force(fl, F, rs, fps, cs, o0, o1, o2, mask);
     if (threadIdx.x < NB) hist[threadIdx.x] = 0;
     __syncthreads();
     const float nf = (float)n;
@@ -235,6 +244,162 @@ __global__ __launch_bounds__(READOUT_T) void k_readout_kd_tiles(const float4 *__
             const int s0 = (t0 + e / 9 - 1 + nt) & (nt - 1), s1 = (t1 + (e / 3) % 3 - 1 + nt) & (nt - 1),
                       s2 = (t2 + e % 3 - 1 + nt) & (nt - 1);
             atomicAdd(cnt_next + tile_index(s0, s1, s2) * 8 + f, hist[b]);
+        }
+    }
+}
+
+// The readouts of particles that keep the caller's order, from records sorted
+// by tile: the same staging, the results scattered (or gathered) at index[i].
+// A gather in the caller's order reads 12 rows of the meshes per particle,
+// which only lattice-ordered particles share; here a tile is read once (19 M
+// particles on 512^3: pm_force's readout 1464 -> 896 us, for 145 us more in the scatter, which writes the indices).
+enum { OUT_FORCE = 0, OUT_KD = 1, OUT_LOSS = 2, OUT_GRAD = 3 };
+struct ReadoutOut {
+    float *x = nullptr, *p = nullptr;   // OUT_FORCE: x the forces; OUT_KD: positions, momenta; OUT_GRAD: x the cotangent
+    const float *target = nullptr;      // OUT_LOSS
+    Mom3 *vals = nullptr;               // OUT_LOSS: written; OUT_GRAD: read
+    double *red = nullptr;              // OUT_LOSS
+    float kick = 0.f, drift = 0.f;      // OUT_KD; OUT_GRAD: kick the scale
+    int *flag = nullptr;                // OUT_KD
+};
+
+template <int OUT>
+__global__ __launch_bounds__(READOUT_T) void k_readout_tiles(const float4 *__restrict__ xs,
+                                                             const uint32_t *__restrict__ index, int64_t P,
+                                                             const int *__restrict__ koff, const float *__restrict__ F,
+                                                             int64_t rs, int64_t fps, int64_t cs, int n, ReadoutOut o)
+{
+    constexpr int H = FORCE_H;
+    __shared__ float4 fl[H * H * H];
+    __shared__ double sum[2][READOUT_T / 64];
+    __shared__ unsigned wmax[READOUT_T / 64];
+    const int nt = n / TILE, mask = n - 1;
+    const int bt = xcd_tile(blockIdx.x, gridDim.x);
+    const int t0 = bt / (nt * nt), t1 = (bt / nt) % nt, t2 = bt % nt;
+    const int t = tile_index(t0, t1, t2);
+    const int o0 = t0 * TILE, o1 = t1 * TILE, o2 = t2 * TILE;
+    const int beg = koff[t * 8], end = koff[t * 8 + 8];
+    int i = beg + threadIdx.x;
+    float4 ur = make_float4(0.f, 0.f, 0.f, 0.f);
+    uint32_t id = 0;
+    if (i < end) {
+        ur = xs[i];
+        id = index[i];
+    }
+    stage_force(fl, F, rs, fps, cs, o0, o1, o2, mask);
+    __syncthreads();
+    const float nf = (float)n;
+    bool bad = false;
+    double la = 0.0, lb = 0.0;
+    unsigned em = 0;
+    while (i < end) {
+        const float u0 = ur.x, u1 = ur.y, u2 = ur.z;
+        const int64_t at = id;
+        // the caller's values at this particle, loaded before the sums
+        float v0 = 0.f, v1 = 0.f, v2 = 0.f;
+        if constexpr (OUT == OUT_KD || OUT == OUT_LOSS) {
+            const float *src = OUT == OUT_KD ? o.p : o.target;
+            v0 = src[at];
+            v1 = src[P + at];
+            v2 = src[2 * P + at];
+        }
+        if constexpr (OUT == OUT_GRAD) {
+            const Mom3 g = o.vals[i];
+            v0 = o.kick * g.x;
+            v1 = o.kick * g.y;
+            v2 = o.kick * g.z;
+        }
+        const float f0 = floorf(u0), f1 = floorf(u1), f2 = floorf(u2);
+        const float d0 = u0 - f0, d1 = u1 - f1, d2 = u2 - f2;
+        const int a0 = ((int)f0 - o0) & mask, a1 = ((int)f1 - o1) & mask, a2 = ((int)f2 - o2) & mask;
+        const float w0[2] = {1.f - d0, d0}, w1[2] = {1.f - d1, d1}, w2[2] = {1.f - d2, d2};
+        float s0 = 0.f, s1 = 0.f, s2 = 0.f;
+#pragma unroll
+        for (int a = 0; a < 2; a++)
+#pragma unroll
+            for (int b = 0; b < 2; b++) {
+                const int row = ((a0 + a) * H + (a1 + b)) * H + a2;
+                const float wab = w0[a] * w1[b];
+#pragma unroll
+                for (int c = 0; c < 2; c++) {
+                    const float4 f = fl[row + c];
+                    if constexpr (OUT == OUT_GRAD) {
+                        // dW/dx_e times the contraction of the force with the cotangent
+                        float q = v0 * f.x;
+                        q += v1 * f.y;
+                        q += v2 * f.z;
+                        s0 += (a ? 1.f : -1.f) * w1[b] * w2[c] * q;
+                        s1 += w0[a] * (b ? 1.f : -1.f) * w2[c] * q;
+                        s2 += wab * (c ? 1.f : -1.f) * q;
+                    } else {
+                        const float w = wab * w2[c];
+                        s0 += w * f.x;
+                        s1 += w * f.y;
+                        s2 += w * f.z;
+                    }
+                }
+            }
+        const int inext = i + READOUT_T;
+        const int icur = i;
+        if (inext < end) {
+            ur = xs[inext];
+            id = index[inext];
+        }
+        if constexpr (OUT == OUT_FORCE) {
+            o.x[at] = s0;
+            o.x[P + at] = s1;
+            o.x[2 * P + at] = s2;
+        } else if constexpr (OUT == OUT_KD) {
+            const float p0 = v0 + o.kick * s0, p1 = v1 + o.kick * s1, p2 = v2 + o.kick * s2;
+            const float x0 = wrapf(u0 + o.drift * p0, nf), x1 = wrapf(u1 + o.drift * p1, nf),
+                        x2 = wrapf(u2 + o.drift * p2, nf);
+            bad |= !(isfinite(p0) && isfinite(p1) && isfinite(p2) && isfinite(x0) && isfinite(x1) && isfinite(x2));
+            o.p[at] = p0;
+            o.p[P + at] = p1;
+            o.p[2 * P + at] = p2;
+            o.x[at] = x0;
+            o.x[P + at] = x1;
+            o.x[2 * P + at] = x2;
+        } else if constexpr (OUT == OUT_LOSS) {
+            const float e0 = s0 - v0, e1 = s1 - v1, e2 = s2 - v2;
+            la += (double)e0 * e0 + (double)e1 * e1 + (double)e2 * e2;
+            lb += (double)v0 * v0 + (double)v1 * v1 + (double)v2 * v2;
+            // integer maximum of the bits: NaN above infinity above all else
+            em = max(em, max(__float_as_uint(fabsf(e0)), max(__float_as_uint(fabsf(e1)), __float_as_uint(fabsf(e2)))));
+            o.vals[icur] = Mom3{e0, e1, e2};
+        } else {
+            o.x[at] += s0;
+            o.x[P + at] += s1;
+            o.x[2 * P + at] += s2;
+        }
+        i = inext;
+    }
+    if constexpr (OUT == OUT_KD) {
+        if (bad) atomicOr(o.flag, FLAG_NAN);
+    }
+    if constexpr (OUT == OUT_LOSS) {
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) {
+            la += __shfl_xor(la, off);
+            lb += __shfl_xor(lb, off);
+            em = max(em, (unsigned)__shfl_xor((int)em, off));
+        }
+        if ((threadIdx.x & 63) == 0) {
+            sum[0][threadIdx.x >> 6] = la;
+            sum[1][threadIdx.x >> 6] = lb;
+            wmax[threadIdx.x >> 6] = em;
+        }
+        __syncthreads();
+        if (threadIdx.x < 2 && beg < end) {
+            double v = 0.0;
+            for (int k = 0; k < READOUT_T / 64; k++) v += sum[threadIdx.x][k];
+            // spread over RED_SLOTS: atomics to one address are taken one by one
+            double *red = o.red + 4 * (blockIdx.x % RED_SLOTS);
+            atomicAdd(red + threadIdx.x, v);
+            if (threadIdx.x == 0) {
+                for (int k = 0; k < READOUT_T / 64; k++) em = max(em, wmax[k]);
+                atomicMax(reinterpret_cast<unsigned *>(red + 2), em);
+            }
         }
     }
 }
@@ -476,6 +641,60 @@ hipError_t launch_readout_kd_tiles(const float4 *xs, const Mom3 *ps, int64_t P, 
                        reinterpret_cast<const float *>(f), 2 * rs_f, 2 * ps_f, 2 * comp_stride, n, kick, drift, x, p, tags,
                        ids_tmp, ids, flag, cnt_next);
     return hipGetLastError();
+}
+
+template <int OUT>
+static hipError_t readout_tiles(const float4 *xs, const uint32_t *index, int64_t P, const int *koff, const float2 *f,
+                                int64_t rs_f, int64_t ps_f, int64_t comp_stride, int n, const ReadoutOut &o, hipStream_t s)
+{
+    const int nt = n / TILE;
+    if (nt < 2) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_readout_tiles<OUT>, dim3((unsigned)(nt * nt * nt)), dim3(READOUT_T), 0, s, xs, index, P, koff,
+                       reinterpret_cast<const float *>(f), 2 * rs_f, 2 * ps_f, 2 * comp_stride, n, o);
+    return hipGetLastError();
+}
+
+hipError_t launch_readout_tiles(const float4 *xs, const uint32_t *index, int64_t P, const int *koff, const float2 *f,
+                                int64_t rs_f, int64_t ps_f, int64_t comp_stride, int n, float *acc, hipStream_t s)
+{
+    ReadoutOut o;
+    o.x = acc;
+    return readout_tiles<OUT_FORCE>(xs, index, P, koff, f, rs_f, ps_f, comp_stride, n, o, s);
+}
+
+hipError_t launch_readout_kd_index_tiles(const float4 *xs, const uint32_t *index, int64_t P, const int *koff,
+                                         const float2 *f, int64_t rs_f, int64_t ps_f, int64_t comp_stride, int n,
+                                         float kick, float drift, float *x, float *p, int *flag, hipStream_t s)
+{
+    ReadoutOut o;
+    o.x = x;
+    o.p = p;
+    o.kick = kick;
+    o.drift = drift;
+    o.flag = flag;
+    return readout_tiles<OUT_KD>(xs, index, P, koff, f, rs_f, ps_f, comp_stride, n, o, s);
+}
+
+hipError_t launch_readout_loss_tiles(const float4 *xs, const uint32_t *index, int64_t P, const int *koff,
+                                     const float2 *f, int64_t rs_f, int64_t ps_f, int64_t comp_stride, int n,
+                                     const float *target, Mom3 *vals, double *red, hipStream_t s)
+{
+    ReadoutOut o;
+    o.target = target;
+    o.vals = vals;
+    o.red = red;
+    return readout_tiles<OUT_LOSS>(xs, index, P, koff, f, rs_f, ps_f, comp_stride, n, o, s);
+}
+
+hipError_t launch_readout_grad3_tiles(const float4 *xs, const uint32_t *index, int64_t P, const int *koff,
+                                      const float2 *f, int64_t rs_f, int64_t ps_f, int64_t comp_stride, int n,
+                                      const Mom3 *vals, float gscale, float *xbar, hipStream_t s)
+{
+    ReadoutOut o;
+    o.x = xbar;
+    o.vals = const_cast<Mom3 *>(vals);
+    o.kick = gscale;
+    return readout_tiles<OUT_GRAD>(xs, index, P, koff, f, rs_f, ps_f, comp_stride, n, o, s);
 }
 
 hipError_t launch_fill_i32(int *p, int64_t count, hipStream_t s)

@@ -208,7 +208,7 @@ struct Workspace {
     float4 *xs = nullptr;        // tile-sorted records (u0, u1, u2, segment tag as int bits) [P]
     Mom3 *ps = nullptr;          // tile-sorted momenta (p0, p1, p2) [P], 12 bytes each
     uint8_t *tags = nullptr;     // segment tag per particle in the caller's current order [P]
-    uint32_t *ids_tmp = nullptr; // tile-sorted ids [P]
+    uint32_t *ids_tmp = nullptr; // tile-sorted ids, or indices of the records [P]
     int *cnt = nullptr;          // counts per key (K + 1), then the scatter's cursors (aliases the F region)
     int *cnt_next = nullptr;     // counts per key of the positions the last tile readout wrote (K + 1)
     int *koff = nullptr;         // exclusive offsets per key (K + 1)
@@ -222,7 +222,7 @@ struct Workspace {
     float *net_acc = nullptr;    // forces on the particles [3][P]
     float *net_table = nullptr;  // radial filter table [NET_NB]
     double *net_tbar = nullptr;  // its cotangent [NET_NB]
-    double *net_red = nullptr;   // loss reductions [2]
+    double *net_red = nullptr;   // loss reductions [RED_SLOTS][4]
     uint16_t *net_wpk = nullptr; // inference weights in LDS layout [NET_WPK_BYTES]
 };
 
@@ -242,6 +242,7 @@ __device__ __forceinline__ float table_at(const float *table, float kt, int &b, 
     return (1.f - w) * table[b] + w * table[b + 1];
 }
 constexpr int NET_WPK_BYTES = 32768;
+constexpr int RED_SLOTS = 64;   // slots of the loss reductions
 constexpr int NW0 = 0, NB0 = NW0 + NET_H * 2, NW1 = NB0 + NET_H, NB1 = NW1 + NET_H * NET_H, NW2 = NB1 + NET_H,
               NB2 = NW2 + NET_H * NET_H, NW3 = NB2 + NET_H, NB3 = NW3 + NET_H, NC1W = NB3 + 1,
               NC1B = NC1W + NET_C * 27, NC2W = NC1B + NET_C, NC2B = NC2W + NET_C * NET_C * 27,
@@ -381,10 +382,12 @@ hipError_t launch_paint_vec3(const float *x, int64_t P, const float *g, float gs
 // max |gscale g| over count values into *out as float bits (zero *out first).
 hipError_t launch_absmax(const float *g, int64_t count, float gscale, unsigned *out, hipStream_t s);
 // Q (int64 [N]^3, added to) += llrint(S w gscale g_d) per particle and corner.
-hipError_t launch_paint_q1_tiles(const float4 *xs, const Mom3 *vals, int comp, const int *koff, float gscale,
-                                 double S, int n, int64_t *Q, hipStream_t s);
 hipError_t launch_paint_q1(const float *x, int64_t P, const float *gd, float gscale, double S, int n, int64_t *Q,
                            hipStream_t s);
+// The same integers by tile for the three components of vals (sorted records),
+// written as float32 rows (row stride rs, component stride cs) times inv_s.
+hipError_t launch_paint_q3_tiles(const float4 *xs, const Mom3 *vals, const int *koff, float gscale, double S,
+                                 double inv_s, int n, float *G, int64_t rs, int64_t cs, hipStream_t s);
 hipError_t launch_green_adj(float2 *F, int64_t nhp, int64_t fs, int n, double coef, hipStream_t s);
 hipError_t launch_density_grad(const float *x, int64_t P, const float *mesh, int64_t rs, int n, int nseg,
                                const int64_t *seg_off, const uint8_t *tags, const int64_t *quanta, float qscale,
@@ -421,6 +424,7 @@ hipError_t launch_cnn_fwd(const int64_t *q, double qs, const float *delta, const
 hipError_t launch_cnn_bwd(const int64_t *q, double qs, const float *delta, const float *phibar, int64_t rs, int n, const float *th,
                           const float *z1, const uint16_t *a1, const float *z2, const uint16_t *a2, float *part,
                           float *g2, uint16_t *wpk, float *dth, hipStream_t s);
+hipError_t launch_zero_f64(double *p, int n, hipStream_t s);
 hipError_t launch_force_loss(float *acc, const float *target, int64_t n3, double *red, hipStream_t s);
 hipError_t launch_adam(float *th, float *m, float *v, const float *g, int64_t n, double lr, double b1, double b2,
                        double eps, int t, hipStream_t s);
@@ -447,6 +451,8 @@ hipError_t launch_paint_tiles_delta(const float4 *xs, const int *koff, const int
 // exclusive scan of the n - 1 counts and the zero behind them (out2: a second
 // copy, the scatter's cursors; clear: the counts are zeroed), and the
 // scatter of particles to their cursor slots (cursor advanced by the counts).
+// ids_out (optional): ids_in[i], or the particle's index i without ids_in, in
+// sorted order.
 hipError_t launch_sort_count(const float *x, int64_t P, int n, int *cnt, hipStream_t s);
 hipError_t launch_scan(int *in, int *out, int64_t n, int *block_sums, hipStream_t s, int *out2 = nullptr,
                        bool clear = false);
@@ -470,6 +476,22 @@ hipError_t launch_readout_kd_tiles(const float4 *xs, const Mom3 *ps, int64_t P, 
                                    int64_t rs_f, int64_t ps_f, int64_t comp_stride, int n, float kick, float drift,
                                    float *x, float *p, uint8_t *tags, const uint32_t *ids_tmp, uint32_t *ids, int *flag,
                                    int *cnt_next, hipStream_t s);
+// The same tile by tile from sorted records (index: each record's particle),
+// for particles that keep the caller's order: acc = F (launch_readout_tiles);
+// kick and drift of the caller's x and p; vals = F - target with red[0] += sum
+// (F - target)^2, red[1] += sum target^2, red[2] the largest |F - target| as
+// float bits, in each of RED_SLOTS slots of four doubles (zeroed); xbar += gscale sum_d vals_d grad F_d.
+hipError_t launch_readout_tiles(const float4 *xs, const uint32_t *index, int64_t P, const int *koff, const float2 *f,
+                                int64_t rs_f, int64_t ps_f, int64_t comp_stride, int n, float *acc, hipStream_t s);
+hipError_t launch_readout_kd_index_tiles(const float4 *xs, const uint32_t *index, int64_t P, const int *koff,
+                                         const float2 *f, int64_t rs_f, int64_t ps_f, int64_t comp_stride, int n,
+                                         float kick, float drift, float *x, float *p, int *flag, hipStream_t s);
+hipError_t launch_readout_loss_tiles(const float4 *xs, const uint32_t *index, int64_t P, const int *koff,
+                                     const float2 *f, int64_t rs_f, int64_t ps_f, int64_t comp_stride, int n,
+                                     const float *target, Mom3 *vals, double *red, hipStream_t s);
+hipError_t launch_readout_grad3_tiles(const float4 *xs, const uint32_t *index, int64_t P, const int *koff,
+                                      const float2 *f, int64_t rs_f, int64_t ps_f, int64_t comp_stride, int n,
+                                      const Mom3 *vals, float gscale, float *xbar, hipStream_t s);
 hipError_t launch_fill_i32(int *p, int64_t count, hipStream_t s);
 hipError_t launch_add_i64(const int64_t *src, int64_t *dst, int64_t count, hipStream_t s);
 hipError_t launch_tags_canonical(uint8_t *tags, int64_t P, int nseg, const int64_t *seg_off, hipStream_t s);

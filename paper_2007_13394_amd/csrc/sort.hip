@@ -220,11 +220,11 @@ __global__ void k_scan_add(int *out, int64_t n, const int *sums, int *out2)
 // Scatter into float4 records: one 16-byte store for the position and the
 // segment tag, one for the momentum, so a particle that moves far in the
 // order costs two stores instead of seven partial ones.  The optional arrays
-// are template flags.  A thread takes its NR particles in batches of SB:
+// are template flags (HI 1: the caller's ids, 2: the particle's index).  A thread takes its NR particles in batches of SB:
 // a batch's particles are loaded at once, then its cursor atomics are issued
 // back to back, then its stores (two memory round trips per batch).  The
 // pointers do not alias (caller arrays in, workspace records out).
-template <bool HP, bool HT, bool HI, int NR, int SB>
+template <bool HP, bool HT, int HI, int NR, int SB>
 __device__ __forceinline__ void scatter_chunk(int64_t c0, int64_t c1, const float *__restrict__ x,
                                               const float *__restrict__ p, const uint8_t *__restrict__ tag_in,
                                               int64_t P, int nseg, const int64_t *__restrict__ seg_off, int n,
@@ -259,7 +259,8 @@ __device__ __forceinline__ void scatter_chunk(int64_t c0, int64_t c1, const floa
                 t[r] = g0;
             }
             id[r] = 0;
-            if constexpr (HI) id[r] = ids_in[ic];
+            if constexpr (HI == 1) id[r] = ids_in[ic];
+            if constexpr (HI == 2) id[r] = (uint32_t)ic;
         }
         uint64_t group[SB];
         int leader[SB], base[SB];
@@ -300,19 +301,23 @@ __global__ __launch_bounds__(SORT_T) void k_sort_scatter(const float *__restrict
     scatter_chunk<HP, HT, HI, NR, (NR < SCATTER_SB ? NR : SCATTER_SB)>(c0, c1, x, p, tag_in, P, nseg, seg_off, n, cursor, xs, ps, ids_in, ids_out)
     if (p) {
         if (tag_in) {
-            if (ids_in) SCATTER(true, true, true);
-            else SCATTER(true, true, false);
+            if (ids_in) SCATTER(true, true, 1);
+            else if (ids_out) SCATTER(true, true, 2);
+            else SCATTER(true, true, 0);
         } else {
-            if (ids_in) SCATTER(true, false, true);
-            else SCATTER(true, false, false);
+            if (ids_in) SCATTER(true, false, 1);
+            else if (ids_out) SCATTER(true, false, 2);
+            else SCATTER(true, false, 0);
         }
     } else {
         if (tag_in) {
-            if (ids_in) SCATTER(false, true, true);
-            else SCATTER(false, true, false);
+            if (ids_in) SCATTER(false, true, 1);
+            else if (ids_out) SCATTER(false, true, 2);
+            else SCATTER(false, true, 0);
         } else {
-            if (ids_in) SCATTER(false, false, true);
-            else SCATTER(false, false, false);
+            if (ids_in) SCATTER(false, false, 1);
+            else if (ids_out) SCATTER(false, false, 2);
+            else SCATTER(false, false, 0);
         }
     }
 #undef SCATTER
@@ -376,7 +381,7 @@ hipError_t launch_sort_scatter(const float *x, const float *p, const uint8_t *ta
 {
     const int nr = P < SORT_FEW ? 1 : 8;
     const int64_t nb = (P + nr * SORT_T - 1) / (nr * SORT_T);
-    if (nb > 0x7fffffff) return hipErrorInvalidValue;
+    if (nb > 0x7fffffff || (ids_in && !ids_out)) return hipErrorInvalidValue;
     const dim3 grid((unsigned)(nb > 0 ? nb : 1));
     if (nr == 1)
         hipLaunchKernelGGL(k_sort_scatter<1>, grid, dim3(SORT_T), 0, s, x, p, tag_in, P, nseg, seg_off, n, cursor, xs, ps,

@@ -40,3 +40,21 @@ def test_cnn_gradient_blocks_vs_oracle(dev, mesh):
     # the gradient adds to what dtheta holds
     pm.pm_learned_loss(ctx, th, 0.6, x, t, d)
     assert rel_l2(d.cpu().numpy(), 2.0 * g) < 1e-5
+
+
+@pytest.mark.parametrize("mesh", [16, 32])
+def test_non_finite_force_gives_a_non_finite_gradient(dev, mesh):
+    """A NaN that reaches the forces is not turned into numbers by the
+    fixed-point cotangent paint (meshes of tiles) or the float one (16)."""
+    from paper_2007_13394_amd import pm
+    cfg = I.config("C5_fd16", n_mesh=mesh, n_cdm=8)
+    ctx = pm.Ctx(pm.make_config(cfg, flags=pm.PM_FLAG_LEARNED | pm.PM_FLAG_NO_SORT))
+    x32, _ = I.synthetic_state(cfg, seed=84)
+    th32 = _params(85)
+    th32[O.NET_OFF["B3"][0]] = np.nan
+    th, x = torch.from_numpy(th32).to(dev), torch.from_numpy(x32).to(dev)
+    d = torch.zeros_like(th)
+    loss = pm.pm_learned_loss(ctx, th, 0.6, x, torch.ones_like(x), d)
+    assert np.isnan(loss)
+    o, n = O.NET_OFF["C3W"]
+    assert torch.isnan(d[o:o + n]).all()
