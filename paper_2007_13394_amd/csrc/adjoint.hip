@@ -293,11 +293,15 @@ __global__ __launch_bounds__(256) void k_density_grad(const float *__restrict__ 
     }
 }
 
-// delta = Q scale - 1 into a dense float mesh.
-__global__ void k_q_to_delta(const int64_t *q, int64_t m, double scale, float *delta)
+// delta = Q scale - 1 into a dense float mesh (flag, optional: overflow guard).
+__global__ void k_q_to_delta(const int64_t *q, int64_t m, double scale, float *delta, int *flag)
 {
-    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < m; i += (int64_t)gridDim.x * blockDim.x)
+    bool bad = false;
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < m; i += (int64_t)gridDim.x * blockDim.x) {
+        bad |= q[i] < GUARD_MIN_Q;
         delta[i] = (float)((double)q[i] * scale - 1.0);
+    }
+    if (flag && bad) atomicOr(flag, FLAG_OVERFLOW);
 }
 
 // Initial-condition transpose, CDM: sbar_d(t) = xbar_{d,t} + vfac pbar_{d,t}
@@ -400,9 +404,9 @@ hipError_t launch_density_grad(const float *x, int64_t P, const float *mesh, int
     return hipGetLastError();
 }
 
-hipError_t launch_q_to_delta(const int64_t *q, int64_t m, double scale, float *delta, hipStream_t s)
+hipError_t launch_q_to_delta(const int64_t *q, int64_t m, double scale, float *delta, hipStream_t s, int *flag)
 {
-    hipLaunchKernelGGL(k_q_to_delta, dim3(grid_for(m, 256)), dim3(256), 0, s, q, m, scale, delta);
+    hipLaunchKernelGGL(k_q_to_delta, dim3(grid_for(m, 256)), dim3(256), 0, s, q, m, scale, delta, flag);
     return hipGetLastError();
 }
 

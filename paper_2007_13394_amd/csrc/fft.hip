@@ -24,6 +24,7 @@
 #include <type_traits>
 
 #include "pm_internal.h"
+#include "power_bins.h"
 
 namespace pm {
 namespace {
@@ -786,6 +787,80 @@ __global__ __launch_bounds__(X0Cfg<N>::T, 2) void k_x0_learned(const float2 *src
     }
 }
 
+// Pass B of the power spectrum: the axis-0 transform of one field (or two: a
+// cross power) is completed in registers and each mode's power goes to the
+// workgroup's histogram, so no spectrum is written and read again.  Workgroups
+// walk tiles of 64 plane offsets of one m; the histogram leaves once at the end.
+template <int N, bool CROSS>
+__global__ __launch_bounds__(X0Cfg<N>::T, 2) void k_x0_power(const float2 *srca, const float2 *srcb, int64_t plane, int nhp,
+                                                          int nbins, int compensate, double norm, double *partial,
+                                                          const float2 *__restrict__ tw)
+{
+    using X = X0Cfg<N>;
+    constexpr int N2 = X::N2, R2 = X::R2, C = X::C, SPT = X::SPT, T = X::T;
+    __shared__ float2 lds[16 * R2 * C];
+    __shared__ double hist[MAX_BINS];
+    __shared__ double win[N / 2 + 1];
+    const int c = threadIdx.x % C, g = __builtin_amdgcn_readfirstlane((int)threadIdx.x / C);
+    for (int i = threadIdx.x; i < nbins; i += T) hist[i] = 0.0;
+    if (compensate) window_table(win, N, T);
+    __syncthreads();
+    const int64_t pstep = (int64_t)R2 * plane;
+    const float2 *twN2 = tw + N2;
+    const int ncol = (int)(((int64_t)N * nhp) / C), ntiles = 16 * ncol;
+    float2 v[16], w[16];
+    for (int tile = xcd_tile(blockIdx.x, gridDim.x); tile < ntiles; tile += gridDim.x) {
+        const int m = tile / ncol;
+        const int64_t e = (int64_t)(tile % ncol) * C + c;
+        const int64_t pbase = (int64_t)(N2 * m + g) * plane + e;
+        auto forward = [&](const float2 *src, float2 (&u)[16]) {
+#pragma unroll
+            for (int i = 0; i < 16; i++) u[i] = src[pbase + i * pstep];
+            Dft<16, false>::run(u);
+            if constexpr (R2 > 1) {
+#pragma unroll
+                for (int a = 1; a < 16; a++) u[a] = cmul(u[a], twN2[g * a]);
+            }
+#pragma unroll
+            for (int a = 0; a < 16; a++) lds[(a * R2 + g) * C + c] = u[a];
+            __syncthreads();
+#pragma unroll
+            for (int s = 0; s < SPT; s++) {
+                const int a = g + R2 * s;
+#pragma unroll
+                for (int l = 0; l < R2; l++) u[s * R2 + l] = lds[(a * R2 + l) * C + c];
+                Dft<R2, false>::run(u + s * R2);
+            }
+            __syncthreads();
+        };
+        forward(srca, v);
+        if constexpr (CROSS) forward(srcb, w);
+        const int k1 = (int)(e / nhp), n2 = (int)(e - (int64_t)k1 * nhp);
+        const int n1 = k1 <= N / 2 ? k1 : N - k1;
+        const int perp = n1 * n1 + n2 * n2;
+        double wgt = norm * ((n2 == 0 || n2 == N / 2) ? 1.0 : 2.0);
+        if (compensate && n2 <= N / 2) wgt *= win[n1] * win[n2];
+#pragma unroll
+        for (int s = 0; s < SPT; s++)
+#pragma unroll
+            for (int l = 0; l < R2; l++) {
+                const int k0 = m + 16 * (g + R2 * s + 16 * l), n0 = k0 <= N / 2 ? k0 : N - k0;
+                const int nn = n0 * n0 + perp;
+                int b = isqrt24(nn);
+                if (nn == 0 || b >= nbins || n2 > N / 2) b = -1;
+                const float2 p = v[s * R2 + l];
+                float2 q = p;
+                if constexpr (CROSS) q = w[s * R2 + l];
+                double val = ((double)p.x * q.x + (double)p.y * q.y) * wgt;
+                if (compensate) val *= win[n0];
+                const int next = __shfl_down(b, 1);
+                bin_runs(hist, b, next, c == C - 1, b >= 0 ? val : 0.0);
+            }
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < nbins; i += T) partial[(int64_t)blockIdx.x * nbins + i] = hist[i];
+}
+
 // Rows fused with pass A: one workgroup takes the 16 rows (plane j1 + N2 j,
 // row x1), j < 16, of a field, so the 16-point axis-0 DFT across them costs
 // no HBM pass of its own.  Forward: real-to-complex of the 16 int64 rows,
@@ -1092,6 +1167,29 @@ hipError_t launch_x0_learned(int logn, const float2 *srcd, const float2 *srcc, f
     default: X0L(2048); break;
     }
 #undef X0L
+    return hipGetLastError();
+}
+
+hipError_t launch_x0_power(int logn, const float2 *srca, const float2 *srcb, int64_t plane, int nhp, int nbins,
+                           int compensate, double norm, double *partial, int blocks, const float2 *tw, hipStream_t s)
+{
+    if (logn < 8 || logn > 11 || plane < ((int64_t)nhp << logn)) return hipErrorInvalidValue;
+#define X0P(NN)                                                                                      \
+    {                                                                                                \
+        if (srca != srcb)                                                                            \
+            hipLaunchKernelGGL((k_x0_power<NN, true>), dim3((unsigned)blocks), dim3(X0Cfg<NN>::T), 0, s, srca, srcb, \
+                               plane, nhp, nbins, compensate, norm, partial, tw);                    \
+        else                                                                                         \
+            hipLaunchKernelGGL((k_x0_power<NN, false>), dim3((unsigned)blocks), dim3(X0Cfg<NN>::T), 0, s, srca, srcb, \
+                               plane, nhp, nbins, compensate, norm, partial, tw);                    \
+    }
+    switch (logn) {
+    case 8: X0P(256); break;
+    case 9: X0P(512); break;
+    case 10: X0P(1024); break;
+    default: X0P(2048); break;
+    }
+#undef X0P
     return hipGetLastError();
 }
 

@@ -134,7 +134,7 @@ Layout layout(const pm_config &c)
     L.flag = off;
     off = align256(off + 256);
     L.partial = off;
-    off = align256(off + (size_t)(pm::POWER_BLOCKS + 1) * 3 * pm::MAX_BINS * 8);
+    off = align256(off + (size_t)(pm::POWER_OUT + 3 * pm::MAX_BINS) * 8);
     L.tables = off;
     off = align256(off + (size_t)(3 * (2 * c.n_fib + 1) + 2 * c.n_shell + ((c.flags & PM_FLAG_NU_PSEUDO) ? 4097 : 0)) * 4);
     L.segtab = off;
@@ -496,17 +496,57 @@ pm_status solve(pm_ctx *c, const int64_t *src, hipStream_t s, const float *delta
     return PM_OK;
 }
 
-// Forward spectrum of a density painted into the int64 mesh `q` (in place,
-// row stride n complex), contrast delta = Q scale - 1.
-pm_status forward_density(pm_ctx *c, int64_t *q, double scale, hipStream_t s)
+// Spectrum of a float32 density contrast (dense [N]^3), up to the last axis-0
+// pass at N >= 256 (which power_bins completes), else in natural order; rows of
+// half_pad(N) complex, unpadded planes.
+pm_status power_spectrum_field(pm_ctx *c, const float *delta, float2 *S, hipStream_t s)
 {
     const int n = c->n, lg = c->logn;
     const int64_t nhp = pm::half_pad(n), n2 = (int64_t)n * n;
     const int ncb = (int)(pm::half_cols(n) / pm::TILE_W);
-    float2 *S = reinterpret_cast<float2 *>(q);
-    LAUNCH(pm::K_R2C, pm::launch_r2c_rows_i64(lg, q, n, S, n, n2, scale, -1.0, c->ws.tw, c->ws.flag, s));
-    LAUNCH(pm::K_COLS_FWD, pm::launch_cols(lg, false, S, n, n2, n, ncb, c->ws.tw, s));
-    LAUNCH(pm::K_AXIS0, pm::launch_axis0(lg, pm::MULT_NONE, S, n2, n, S, nullptr, nullptr, n2, n, ncb, 0.0, nullptr, c->ws.tw, s));
+    if (lg >= 8) {
+        LAUNCH(pm::K_R2C_X0, pm::launch_r2c_x0_f32(lg, delta, n, S, (int)nhp, n * nhp, c->ws.tw, s));
+        LAUNCH(pm::K_COLS_FWD, pm::launch_cols(lg, false, S, nhp, n * nhp, n, ncb, c->ws.tw, s));
+        return PM_OK;
+    }
+    LAUNCH(pm::K_R2C, pm::launch_r2c_rows_f32(lg, delta, n, S, nhp, n2, c->ws.tw, s));
+    LAUNCH(pm::K_COLS_FWD, pm::launch_cols(lg, false, S, nhp, n * nhp, n, ncb, c->ws.tw, s));
+    LAUNCH(pm::K_AXIS0, pm::launch_axis0(lg, pm::MULT_NONE, S, n * nhp, nhp, S, nullptr, nullptr, n * nhp, nhp, ncb, 0.0,
+                                         nullptr, c->ws.tw, s));
+    return PM_OK;
+}
+
+// Binned cross power of two such spectra (A == B: auto), read back to the host.
+pm_status power_bins(pm_ctx *c, const float2 *A, const float2 *B, int nbins, int compensate, double *k_mean, double *pk,
+                     double *n_modes, hipStream_t s)
+{
+    const int n = c->n, lg = c->logn;
+    const int64_t nhp = pm::half_pad(n);
+    const double M = (double)n * n * n, norm = pow(c->cfg.box, 3) / (M * M);
+    double *part = c->ws.partial, *geom = part + pm::POWER_PART, *out = part + pm::POWER_OUT;
+    // workgroups: enough waves for the chip, as long as their partials fit
+    int64_t most = pm::POWER_PART / nbins;
+    if (most > 4096) most = 4096;
+    const int64_t tiles = lg >= 8 ? n * nhp / 4 : (int64_t)n * n * (n / 2 + 1) / 2048 + 1;
+    const int blocks = (int)(tiles < most ? tiles : most);
+    if (lg >= 8)
+        LAUNCH(pm::K_POWER_BIN, pm::launch_x0_power(lg, A, B, n * nhp, (int)nhp, nbins, compensate, norm, part, blocks,
+                                                    c->ws.tw, s));
+    else
+        LAUNCH(pm::K_POWER_BIN, pm::launch_power_bin(A, B, nhp, n, nbins, compensate, norm, part, blocks, s));
+    const int rows = (n / 2 + 1) * (n / 2 + 1) / 4 + 1, gb = rows < pm::POWER_GEOM ? rows : pm::POWER_GEOM;
+    LAUNCH(pm::K_POWER_BIN, pm::launch_power_geom(n, nbins, 2.0 * M_PI / c->cfg.box, geom, gb, s));
+    LAUNCH(pm::K_POWER_REDUCE, pm::launch_power_reduce(part, blocks, nbins, out, s));
+    LAUNCH(pm::K_POWER_REDUCE, pm::launch_power_reduce(geom, gb, 2 * nbins, out + nbins, s));
+    std::vector<double> h(3 * (size_t)nbins);
+    HIPCHK(hipMemcpyAsync(h.data(), out, sizeof(double) * h.size(), hipMemcpyDeviceToHost, s));
+    HIPCHK(hipStreamSynchronize(s));
+    for (int b = 0; b < nbins; b++) {
+        const double w = h[nbins + b];
+        n_modes[b] = w;
+        pk[b] = w > 0 ? h[b] / w : 0.0;
+        k_mean[b] = w > 0 ? h[2 * (size_t)nbins + b] / w : 0.0;
+    }
     return PM_OK;
 }
 
@@ -1209,44 +1249,30 @@ pm_status pm_power(pm_ctx *c, const float *x, int32_t a_lo, int32_t a_hi, int32_
         for (int g = lo; g < hi; g++) tot += (double)(c->seg_off[g + 1] - c->seg_off[g]) * (double)c->seg_q[g];
         return (double)M / tot;
     };
-    // int64 mesh of one segment range: by tile from one sort of the records
-    // where the configuration can, else with global atomics
+    // density contrast of one segment range: by tile from one sort of the
+    // records where the configuration can, else with global atomics
+    const int64_t cs = (int64_t)n * n * pm::half_pad(n);
+    float2 *SA = c->ws.f, *SB = c->ws.f + cs;
+    float *delta = reinterpret_cast<float *>(c->ws.f + 2 * cs);
     const bool tiles = c->nkeys > 0;
-    auto paint = [&](int lo, int hi, int64_t *q) -> pm_status {
+    auto field = [&](int lo, int hi, float2 *S) -> pm_status {
         if (tiles) {
-            LAUNCH(pm::K_PAINT, pm::launch_paint_tiles(c->ws.xs, c->ws.koff, c->ws.quanta, c->nseg, lo, hi, n, q, s));
-            return PM_OK;
+            LAUNCH(pm::K_PAINT, pm::launch_paint_tiles_delta(c->ws.xs, c->ws.koff, c->ws.quanta, c->nseg, lo, hi, n,
+                                                             scale_of(lo, hi), -1.0, delta, c->ws.flag, s));
+            return power_spectrum_field(c, delta, S, s);
         }
-        LAUNCH(pm::K_FILL, pm::launch_fill_i64(q, M, s));
-        return paint_atomic(c, x, lo, hi, q, s);
+        LAUNCH(pm::K_FILL, pm::launch_fill_i64(c->ws.q, M, s));
+        pm_status st = paint_atomic(c, x, lo, hi, c->ws.q, s);
+        if (st != PM_OK) return st;
+        LAUNCH(pm::K_COPY, pm::launch_q_to_delta(c->ws.q, M, scale_of(lo, hi), delta, s, c->ws.flag));
+        return power_spectrum_field(c, delta, S, s);
     };
     pm_status st = tiles ? tile_records(c, x, nullptr, false, s) : PM_OK;
-    if (st == PM_OK) st = paint(a_lo, a_hi, c->ws.q);
-    if (st == PM_OK) st = forward_density(c, c->ws.q, scale_of(a_lo, a_hi), s);
-    if (st != PM_OK) return st;
-    const float2 *A = reinterpret_cast<const float2 *>(c->ws.q), *B = A;
-    if (a_lo != b_lo || a_hi != b_hi) {
-        int64_t *qb = reinterpret_cast<int64_t *>(c->ws.f);
-        st = paint(b_lo, b_hi, qb);
-        if (st == PM_OK) st = forward_density(c, qb, scale_of(b_lo, b_hi), s);
-        if (st != PM_OK) return st;
-        B = reinterpret_cast<const float2 *>(qb);
-    }
-    const double V = pow(c->cfg.box, 3);
-    double *out = c->ws.partial + (size_t)pm::POWER_BLOCKS * 3 * pm::MAX_BINS;
-    LAUNCH(pm::K_POWER_BIN, pm::launch_power_bin(A, B, n, n, nbins, compensate, V / ((double)M * (double)M), 2.0 * M_PI / c->cfg.box,
-                                c->ws.partial, s));
-    LAUNCH(pm::K_POWER_REDUCE, pm::launch_power_reduce(c->ws.partial, nbins, out, s));
-    std::vector<double> h(3 * (size_t)nbins);
-    HIPCHK(hipMemcpyAsync(h.data(), out, sizeof(double) * h.size(), hipMemcpyDeviceToHost, s));
-    HIPCHK(hipStreamSynchronize(s));
-    for (int b = 0; b < nbins; b++) {
-        const double w = h[3 * b + 2];
-        n_modes[b] = w;
-        pk[b] = w > 0 ? h[3 * b] / w : 0.0;
-        k_mean[b] = w > 0 ? h[3 * b + 1] / w : 0.0;
-    }
-    return check_guards(c, s);
+    if (st == PM_OK) st = field(a_lo, a_hi, SA);
+    const bool cross = a_lo != b_lo || a_hi != b_hi;
+    if (st == PM_OK && cross) st = field(b_lo, b_hi, SB);
+    if (st == PM_OK) st = power_bins(c, SA, cross ? SB : SA, nbins, compensate, k_mean, pk, n_modes, s);
+    return st == PM_OK ? check_guards(c, s) : st;
 }
 
 pm_status pm_power_mesh(pm_ctx *c, const float *da, const float *db, int32_t nbins, int32_t compensate,
@@ -1255,38 +1281,11 @@ pm_status pm_power_mesh(pm_ctx *c, const float *da, const float *db, int32_t nbi
     if (!c || !da || !db || !k_mean || !pk || !n_modes) return fail(PM_ERR_ARG, "NULL argument to pm_power_mesh");
     if (nbins < 1 || nbins > pm::MAX_BINS) return fail(PM_ERR_ARG, "nbins must be in [1, %d]", pm::MAX_BINS);
     hipStream_t s = S(stream);
-    const int n = c->n, lg = c->logn;
-    const int64_t M = (int64_t)n * n * n, n2 = (int64_t)n * n, nhp = pm::half_pad(n);
-    const int ncb = (int)(pm::half_cols(n) / pm::TILE_W);
-    auto spectrum = [&](const float *d, float2 *S) -> pm_status {
-        LAUNCH(pm::K_R2C, pm::launch_r2c_rows_f32(lg, d, n, S, n, n2, c->ws.tw, s));
-        LAUNCH(pm::K_COLS_FWD, pm::launch_cols(lg, false, S, n, n2, n, ncb, c->ws.tw, s));
-        LAUNCH(pm::K_AXIS0, pm::launch_axis0(lg, pm::MULT_NONE, S, n2, n, S, nullptr, nullptr, n2, n, ncb, 0.0,
-                                             nullptr, c->ws.tw, s));
-        return PM_OK;
-    };
-    float2 *A = reinterpret_cast<float2 *>(c->ws.q), *B = A;
-    pm_status st = spectrum(da, A);
-    if (st == PM_OK && db != da) {
-        B = reinterpret_cast<float2 *>(c->ws.f);
-        st = spectrum(db, B);
-    }
-    if (st != PM_OK) return st;
-    const double V = pow(c->cfg.box, 3);
-    double *out = c->ws.partial + (size_t)pm::POWER_BLOCKS * 3 * pm::MAX_BINS;
-    LAUNCH(pm::K_POWER_BIN, pm::launch_power_bin(A, B, n, n, nbins, compensate, V / ((double)M * (double)M),
-                                                 2.0 * M_PI / c->cfg.box, c->ws.partial, s));
-    LAUNCH(pm::K_POWER_REDUCE, pm::launch_power_reduce(c->ws.partial, nbins, out, s));
-    std::vector<double> h(3 * (size_t)nbins);
-    HIPCHK(hipMemcpyAsync(h.data(), out, sizeof(double) * h.size(), hipMemcpyDeviceToHost, s));
-    HIPCHK(hipStreamSynchronize(s));
-    for (int b = 0; b < nbins; b++) {
-        const double w = h[3 * b + 2];
-        n_modes[b] = w;
-        pk[b] = w > 0 ? h[3 * b] / w : 0.0;
-        k_mean[b] = w > 0 ? h[3 * b + 1] / w : 0.0;
-    }
-    return PM_OK;
+    const int64_t cs = (int64_t)c->n * c->n * pm::half_pad(c->n);
+    float2 *SA = c->ws.f, *SB = c->ws.f + cs;
+    pm_status st = power_spectrum_field(c, da, SA, s);
+    if (st == PM_OK && db != da) st = power_spectrum_field(c, db, SB, s);
+    return st == PM_OK ? power_bins(c, SA, db != da ? SB : SA, nbins, compensate, k_mean, pk, n_modes, s) : st;
 }
 
 // ---- reverse mode

@@ -1,6 +1,7 @@
 // Particle-side kernels: force readout fused with the FastPM kick and drift,
 // Zel'dovich initial conditions, power-spectrum binning and layout copies.
 #include "pm_internal.h"
+#include "power_bins.h"
 
 namespace pm {
 namespace {
@@ -549,61 +550,86 @@ __global__ void k_ic_nu_pseudo(const float *__restrict__ F, int64_t rs, int64_t 
     }
 }
 
-__device__ __forceinline__ int isqrt_i(int64_t v)
-{
-    int64_t b = (int64_t)sqrt((double)v);
-    while (b * b > v) b--;
-    while ((b + 1) * (b + 1) <= v) b++;
-    return (int)b;
-}
-
-__device__ __forceinline__ double sinc(double x) { return x == 0.0 ? 1.0 : sin(x) / x; }
-
-// Per-block partial sums over the half spectrum: (sum w P, sum w |k|, sum w)
-// per bin, w = 2 for 0 < k2 < N/2 (the mode and its conjugate), else 1.
+// Power sums over a natural-order half spectrum (row stride rs): per workgroup
+// sum w P per bin, w = 2 for 0 < k2 < N/2 (the mode and its conjugate), else 1.
 __global__ __launch_bounds__(256) void k_power_bin(const float2 *__restrict__ A, const float2 *__restrict__ B,
                                                    int64_t rs, int n, int nbins, int compensate, double norm,
-                                                   double kf, double *partial)
+                                                   double *partial)
 {
-    __shared__ double sh[3 * MAX_BINS];
-    for (int i = threadIdx.x; i < 3 * nbins; i += blockDim.x) sh[i] = 0.0;
+    __shared__ double hist[MAX_BINS];
+    __shared__ double win[MAX_BINS / 2 + 1];
+    for (int i = threadIdx.x; i < nbins; i += 256) hist[i] = 0.0;
+    if (compensate) window_table(win, n, 256);
     __syncthreads();
-    const int nh = n / 2 + 1;
+    const int nh = n / 2 + 1, lane = threadIdx.x & 63;
     const int64_t m = (int64_t)n * n * nh;
-    for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < m; t += (int64_t)gridDim.x * blockDim.x) {
-        const int k2 = (int)(t % nh);
-        const int64_t row = t / nh;
-        const int k1 = (int)(row % n), k0 = (int)(row / n);
-        const int64_t n0 = k0 < n / 2 ? k0 : k0 - n, n1 = k1 < n / 2 ? k1 : k1 - n, n2 = k2;
-        const int64_t nn2 = n0 * n0 + n1 * n1 + n2 * n2;
-        if (nn2 == 0) continue;
-        const int b = isqrt_i(nn2);
-        if (b >= nbins) continue;
-        const double w = (k2 == 0 || k2 == n / 2) ? 1.0 : 2.0;
-        const float2 a = A[row * rs + k2], c = B[row * rs + k2];
-        double v = ((double)a.x * c.x + (double)a.y * c.y) * norm;
-        if (compensate) {
-            const double pi_n = 3.141592653589793238 / n;
-            const double s0 = sinc(pi_n * n0), s1 = sinc(pi_n * n1), s2 = sinc(pi_n * n2);
-            const double win = s0 * s0 * s1 * s1 * s2 * s2;
-            v /= win * win;
+    for (int64_t t0 = (int64_t)blockIdx.x * 256; t0 < m; t0 += (int64_t)gridDim.x * 256) {
+        const int64_t t = t0 + threadIdx.x;
+        int b = -1;
+        double v = 0.0;
+        if (t < m) {
+            const int64_t row = t / nh;
+            const int n2 = (int)(t - row * nh), k1 = (int)(row & (n - 1)), k0 = (int)(row / n);
+            const int n0 = k0 <= n / 2 ? k0 : n - k0, n1 = k1 <= n / 2 ? k1 : n - k1;
+            const int nn = n0 * n0 + n1 * n1 + n2 * n2;
+            b = isqrt24(nn);
+            if (nn == 0 || b >= nbins) b = -1;
+            if (b >= 0) {
+                const float2 p = A[row * rs + n2], q = B[row * rs + n2];
+                v = ((double)p.x * q.x + (double)p.y * q.y) * norm * ((n2 == 0 || n2 == n / 2) ? 1.0 : 2.0);
+                if (compensate) v *= win[n0] * win[n1] * win[n2];
+            }
         }
-        atomicAdd(&sh[3 * b], w * v);
-        atomicAdd(&sh[3 * b + 1], w * kf * sqrt((double)nn2));
-        atomicAdd(&sh[3 * b + 2], w);
+        const int next = __shfl_down(b, 1);
+        bin_runs(hist, b, next, lane == 63, v);
     }
     __syncthreads();
-    for (int i = threadIdx.x; i < 3 * nbins; i += blockDim.x) partial[(int64_t)blockIdx.x * 3 * nbins + i] = sh[i];
+    for (int i = threadIdx.x; i < nbins; i += 256) partial[(int64_t)blockIdx.x * nbins + i] = hist[i];
 }
 
-// Sum the block partials in block order (deterministic).
-__global__ void k_power_reduce(const double *partial, int nblocks, int nbins, double *out)
+// The bins' geometry: sum w and sum w |k| over the full mesh, from the modes 0
+// <= n1 <= n0 <= N/2, 0 <= n2 <= N/2 with their multiplicities (an eighth of the
+// half spectrum).  One wavefront per (n0, n1) row.
+__global__ __launch_bounds__(256) void k_power_geom(int n, int nbins, double kf, double *partial)
 {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= 3 * nbins) return;
+    __shared__ double hist[2 * MAX_BINS];
+    for (int i = threadIdx.x; i < 2 * nbins; i += 256) hist[i] = 0.0;
+    __syncthreads();
+    const int nh = n / 2 + 1, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    for (int r = blockIdx.x * 4 + wave; r < nh * nh; r += gridDim.x * 4) {
+        const int n0 = r / nh, n1 = r - n0 * nh;
+        if (n1 > n0) continue;   // uniform over the wavefront
+        const double wr = ((n0 == 0 || n0 == n / 2) ? 1.0 : 2.0) * ((n1 == 0 || n1 == n / 2) ? 1.0 : 2.0) *
+                          (n1 < n0 ? 2.0 : 1.0);
+        for (int c = 0; c < nh; c += 64) {
+            const int n2 = c + lane, nn = n0 * n0 + n1 * n1 + n2 * n2;
+            int b = n2 < nh ? isqrt24(nn) : -1;
+            if (nn == 0 || b >= nbins) b = -1;
+            const double w = b >= 0 ? wr * ((n2 == 0 || n2 == n / 2) ? 1.0 : 2.0) : 0.0;
+            const int next = __shfl_down(b, 1);
+            bin_runs(hist, b, next, lane == 63, w);
+            bin_runs(hist + nbins, b, next, lane == 63, w * (kf * sqrt((double)nn)));
+        }
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < 2 * nbins; i += 256) partial[(int64_t)blockIdx.x * 2 * nbins + i] = hist[i];
+}
+
+// out[i] = the sum of ne-long partials over np workgroups, each value's 32
+// strided sums added in order (deterministic).
+__global__ __launch_bounds__(256) void k_power_reduce(const double *__restrict__ partial, int np, int ne, double *out)
+{
+    __shared__ double sh[32][9];
+    const int c = threadIdx.x & 7, g = threadIdx.x >> 3, i = blockIdx.x * 8 + c;
     double s = 0.0;
-    for (int b = 0; b < nblocks; b++) s += partial[(int64_t)b * 3 * nbins + i];
-    out[i] = s;
+    if (i < ne)
+        for (int b = g; b < np; b += 32) s += partial[(int64_t)b * ne + i];
+    sh[g][c] = s;
+    __syncthreads();
+    if (g == 0 && i < ne) {
+        for (int k = 1; k < 32; k++) s += sh[k][c];
+        out[i] = s;
+    }
 }
 
 }  // namespace
@@ -767,17 +793,21 @@ hipError_t launch_ic_nu_pseudo(const float2 *f, int64_t rs, int64_t comp_stride,
 }
 
 hipError_t launch_power_bin(const float2 *A, const float2 *B, int64_t rs, int n, int nbins, int compensate,
-                            double norm, double kf, double *partial, hipStream_t s)
+                            double norm, double *partial, int blocks, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_power_bin, dim3(POWER_BLOCKS), dim3(256), 0, s, A, B, rs, n, nbins, compensate, norm, kf,
-                       partial);
+    hipLaunchKernelGGL(k_power_bin, dim3((unsigned)blocks), dim3(256), 0, s, A, B, rs, n, nbins, compensate, norm, partial);
     return hipGetLastError();
 }
 
-hipError_t launch_power_reduce(const double *partial, int nbins, double *out, hipStream_t s)
+hipError_t launch_power_geom(int n, int nbins, double kf, double *partial, int blocks, hipStream_t s)
 {
-    const int m = 3 * nbins;
-    hipLaunchKernelGGL(k_power_reduce, dim3((m + 255) / 256), dim3(256), 0, s, partial, POWER_BLOCKS, nbins, out);
+    hipLaunchKernelGGL(k_power_geom, dim3((unsigned)blocks), dim3(256), 0, s, n, nbins, kf, partial);
+    return hipGetLastError();
+}
+
+hipError_t launch_power_reduce(const double *partial, int np, int ne, double *out, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_power_reduce, dim3((unsigned)((ne + 7) / 8)), dim3(256), 0, s, partial, np, ne, out);
     return hipGetLastError();
 }
 

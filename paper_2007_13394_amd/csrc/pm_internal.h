@@ -53,7 +53,10 @@ constexpr int TILE = 16;
 
 constexpr int MAX_SEG = 65;
 constexpr int MAX_BINS = 2048;
-constexpr int POWER_BLOCKS = 512;
+// Power-spectrum partials (doubles): POWER_PART for the powers, then those of the
+// geometry, POWER_GEOM workgroups of two values per bin, then the results.
+constexpr int POWER_GEOM = 256;
+constexpr int64_t POWER_PART = 1024LL * MAX_BINS, POWER_OUT = POWER_PART + 2LL * POWER_GEOM * MAX_BINS;
 
 // Workgroups are dispatched round-robin over the eight XCDs (b mod 8), each
 // with its own L2.  Renumbering them so that each XCD owns a contiguous range
@@ -367,6 +370,10 @@ hipError_t launch_r2c_x0_f32(int logn, const float *src, int64_t src_rs, float2 
 hipError_t launch_x0_learned(int logn, const float2 *srcd, const float2 *srcc, float2 *out0, float2 *out1,
                              int64_t plane, int nhp, double coef, double inv_m, const float *table, const float2 *tw,
                              hipStream_t s);
+// Pass B of one or two fields (srcb == srca: an auto power) after rows, first
+// digit and axis 1, completed and binned: no spectrum is written.
+hipError_t launch_x0_power(int logn, const float2 *srca, const float2 *srcb, int64_t plane, int nhp, int nbins,
+                           int compensate, double norm, double *partial, int blocks, const float2 *tw, hipStream_t s);
 hipError_t launch_c2r_x0(int logn, const float2 *src, float *dst, int64_t dst_stride, int64_t dst_plane, int nhp,
                          int64_t plane, const float2 *tw, hipStream_t s);
 
@@ -392,7 +399,8 @@ hipError_t launch_green_adj(float2 *F, int64_t nhp, int64_t fs, int n, double co
 hipError_t launch_density_grad(const float *x, int64_t P, const float *mesh, int64_t rs, int n, int nseg,
                                const int64_t *seg_off, const uint8_t *tags, const int64_t *quanta, float qscale,
                                float scale, float *xbar, hipStream_t s);
-hipError_t launch_q_to_delta(const int64_t *q, int64_t m, double scale, float *delta, hipStream_t s);
+hipError_t launch_q_to_delta(const int64_t *q, int64_t m, double scale, float *delta, hipStream_t s,
+                             int *flag = nullptr);
 hipError_t launch_ic_adj_gather_cdm(const float *xbar, const float *pbar, int64_t P, int nic, float vfac, float *F,
                                     int64_t rs, int64_t cs, hipStream_t s);
 hipError_t launch_ic_adj_gather_nu(const float *xbar, const float *pbar, int64_t P, int64_t nc, int nic, int ns,
@@ -508,8 +516,12 @@ hipError_t launch_ic_nu(const float2 *f, int64_t rs, int64_t comp_stride, int ni
 hipError_t launch_ic_nu_pseudo(const float2 *f, int64_t rs, int64_t comp_stride, int nic, int n, int ns,
                                const float *cdf, int nq, double hq, double pth_unit, double vfac, const float *u,
                                float *x, float *p, int64_t P, int64_t nc, hipStream_t s);
+// Binned power of natural-order half spectra into `blocks` partials of nbins
+// values; the bins' sums of weights and of weight x |k| (partials of 2 nbins);
+// and the sum of np partials of ne values.
 hipError_t launch_power_bin(const float2 *A, const float2 *B, int64_t rs, int n, int nbins, int compensate,
-                            double norm, double kf, double *partial, hipStream_t s);
-hipError_t launch_power_reduce(const double *partial, int nbins, double *out, hipStream_t s);
+                            double norm, double *partial, int blocks, hipStream_t s);
+hipError_t launch_power_geom(int n, int nbins, double kf, double *partial, int blocks, hipStream_t s);
+hipError_t launch_power_reduce(const double *partial, int np, int ne, double *out, hipStream_t s);
 
 }  // namespace pm
