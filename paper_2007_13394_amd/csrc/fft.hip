@@ -399,27 +399,22 @@ __device__ __forceinline__ int signed_mode(int k, int n) { return k <= n / 2 ? k
 // Zel'dovich displacement of component d from a white-noise mode (FP64):
 // i k_d / k^2 sqrt(A P(k) / V_cell) [1 + (k/k_fs)^2]^-1 exp(i k.h) / M_ic,
 // P(k) = k^n_s T_BBKS^2(k / (Omega_m h)); zero at k = 0 and on every Nyquist plane.
-__device__ __forceinline__ float2 mult_ic(float2 v, int d, int l, int o, int k2, int n, const IcParams &p)
+// The radial factor depends on the integer |n|^2 alone and the phase k.h on
+// n0 + n1 + n2: both come from tables (IcTables), since a logarithm, two powers
+// and a sine and cosine per component and mode took 480 us of a 256^3 pass
+// whose memory traffic takes 60 (200 now).
+__device__ __forceinline__ float2 mult_ic(float2 v, int d, int l, int o, int k2, int n, const IcTables &p)
 {
     if (k2 >= n / 2) return make_float2(0.f, 0.f);
     const int n0 = signed_mode(l, n), n1 = signed_mode(o, n), n2 = k2;
     if (n0 == -n / 2 || n0 == n / 2 || n1 == -n / 2 || n1 == n / 2) return make_float2(0.f, 0.f);
-    if (n0 == 0 && n1 == 0 && n2 == 0) return make_float2(0.f, 0.f);
-    const double s = 6.283185307179586476925 / p.box;
-    const double k0 = s * n0, k1 = s * n1, kz = s * n2;
-    const double kk = k0 * k0 + k1 * k1 + kz * kz, k = sqrt(kk);
-    const double q = k / p.omh;
-    const double poly = 1.0 + 3.89 * q + (16.1 * q) * (16.1 * q) + (5.46 * q) * (5.46 * q) * (5.46 * q) +
-                        (6.71 * q) * (6.71 * q) * (6.71 * q) * (6.71 * q);
-    const double T = log(1.0 + 2.34 * q) / (2.34 * q) * pow(poly, -0.25);
-    double amp = sqrt(p.amp_over_vcell * pow(k, p.n_s)) * T * p.scale;
-    if (p.kfs > 0) amp /= 1.0 + (k / p.kfs) * (k / p.kfs);
-    const double kd = d == 0 ? k0 : (d == 1 ? k1 : kz);
-    const double g = amp * kd / kk;
+    const double g = p.radial[n0 * n0 + n1 * n1 + n2 * n2] * (double)(d == 0 ? n0 : (d == 1 ? n1 : n2));
     double re = -g * v.y, im = g * v.x;   // i g v
-    if (p.half_cell != 0) {
-        const double ph = (k0 + k1 + kz) * p.half_cell;
-        const double c = cos(ph), sn = sin(ph);
+    if (p.shifted) {
+        // exp(i pi m / n), tabulated for 0 <= m < n
+        const int m = (n0 + n1 + n2) & (2 * n - 1);
+        const double2 e = p.phase[m & (n - 1)];
+        const double sg = m < n ? 1.0 : -1.0, c = sg * e.x, sn = sg * e.y;
         const double r2 = re * c - im * sn, i2 = re * sn + im * c;
         re = r2;
         im = i2;
@@ -427,10 +422,30 @@ __device__ __forceinline__ float2 mult_ic(float2 v, int d, int l, int o, int k2,
     return make_float2((float)re, (float)im);
 }
 
+// radial[i] = amp(k) k_1 / k^2 at k = k_1 sqrt(i), k_1 the fundamental (0 at i = 0),
+// i <= 3 (n/2)^2; phase[m] = exp(i pi m / n), m < n.
+__global__ __launch_bounds__(256) void k_ic_tables(IcParams p, int n, double *radial, double2 *phase)
+{
+    const int i = blockIdx.x * 256 + threadIdx.x, count = 3 * (n / 2) * (n / 2) + 1;
+    if (i < n) {
+        double s, c;
+        sincospi((double)i / n, &s, &c);
+        phase[i] = make_double2(c, s);
+    }
+    if (i >= count) return;
+    const double s = 6.283185307179586476925 / p.box, kk = s * s * i, k = sqrt(kk), q = k / p.omh;
+    const double poly = 1.0 + 3.89 * q + (16.1 * q) * (16.1 * q) + (5.46 * q) * (5.46 * q) * (5.46 * q) +
+                        (6.71 * q) * (6.71 * q) * (6.71 * q) * (6.71 * q);
+    const double T = i ? log(1.0 + 2.34 * q) / (2.34 * q) * pow(poly, -0.25) : 0.0;
+    double amp = sqrt(p.amp_over_vcell * pow(k, p.n_s)) * T * p.scale;
+    if (p.kfs > 0) amp /= 1.0 + (k / p.kfs) * (k / p.kfs);
+    radial[i] = i ? amp * s / kk : 0.0;
+}
+
 // Transpose of the initial-condition transfer: acc (+)= sum_d conj(M_d) G_d
 // over three natural-order half spectra G_d (row stride nhp, field stride
 // fs); conj(M) v = conj(M conj(v)).
-__global__ void k_ic_adj_mult(const float2 *G, int64_t nhp, int64_t fs, int n, IcParams icp, float2 *acc,
+__global__ void k_ic_adj_mult(const float2 *G, int64_t nhp, int64_t fs, int n, IcTables icp, float2 *acc,
                               int accumulate)
 {
     const int64_t tot = (int64_t)n * n * nhp;
@@ -451,7 +466,7 @@ template <int LOGN, int MODE, int NOUT>
 __global__ __launch_bounds__(Ax0Cfg<LOGN>::T) void k_axis0(const float2 *src, int64_t s_l, int64_t s_o,
                                                            float2 *out0, float2 *out1, float2 *out2,
                                                            int64_t o_l, int64_t o_o, int n_cb, float coef,
-                                                           IcParams icp, const float2 *__restrict__ tw)
+                                                           IcTables icp, const float2 *__restrict__ tw)
 {
     using C = Ax0Cfg<LOGN>;
     constexpr int N = C::N, W = C::W, E = C::E, T = C::T, PER = C::PER;
@@ -1105,14 +1120,15 @@ hipError_t launch_cols(int logn, bool inverse, float2 *base, int64_t stride_l, i
 
 hipError_t launch_axis0(int logn, int mode, const float2 *src, int64_t s_l, int64_t s_o, float2 *out0,
                         float2 *out1, float2 *out2, int64_t o_l, int64_t o_o, int n_cb, double coef,
-                        const IcParams *ic, const float2 *tw, hipStream_t s)
+                        const IcTables *ic, const float2 *tw, hipStream_t s)
 {
     const int n = 1 << logn;
     if (mode == MULT_FORCE && n < 16) return hipErrorInvalidValue;
     const unsigned nb = (unsigned)n * (unsigned)n_cb;
     if (mode == MULT_FORCE && logn >= 8) return hipErrorInvalidValue;   // two-pass path (launch_x0_*)
-    IcParams icp{};
+    IcTables icp{};
     if (ic) icp = *ic;
+    if (mode == MULT_IC && (!icp.radial || !icp.phase)) return hipErrorInvalidValue;
     const float fc = (float)coef;
 #define AX0(LG)                                                                                      \
     {                                                                                                \
@@ -1252,7 +1268,20 @@ hipError_t launch_c2r_x0(int logn, const float2 *src, float *dst, int64_t dst_st
     return hipGetLastError();
 }
 
-hipError_t launch_ic_adj_mult(const float2 *G, int64_t nhp, int64_t fs, int n, const IcParams *ic, float2 *acc,
+hipError_t launch_ic_tables(const IcParams *ic, int n, double *buf, IcTables *out, hipStream_t s)
+{
+    if (n < 2 || n > 2048 || n % 2) return hipErrorInvalidValue;
+    const int count = 3 * (n / 2) * (n / 2) + 1;
+    out->radial = buf;
+    out->phase = reinterpret_cast<double2 *>(buf + count + (count & 1));
+    out->shifted = ic->half_cell != 0;
+    const int most = count > n ? count : n;
+    hipLaunchKernelGGL(k_ic_tables, dim3((unsigned)((most + 255) / 256)), dim3(256), 0, s, *ic, n, buf,
+                       const_cast<double2 *>(out->phase));
+    return hipGetLastError();
+}
+
+hipError_t launch_ic_adj_mult(const float2 *G, int64_t nhp, int64_t fs, int n, const IcTables *ic, float2 *acc,
                               bool accumulate, hipStream_t s)
 {
     const int64_t tot = (int64_t)n * n * nhp;

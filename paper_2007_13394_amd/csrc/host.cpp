@@ -1005,7 +1005,9 @@ static pm_status ic_impl(pm_ctx *c, const float *white, const float *u, float *x
             ip.kfs = 0.82 * sqrt(c->omega_L + g.omega_m / (a0 * a0 * a0)) * a0 * a0 * c->m1;
             ip.half_cell = 0.5 * g.box / nic;
         }
-        LAUNCH(pm::K_AXIS0, pm::launch_axis0(lg, pm::MULT_IC, S0, n2, nic, F, F + cs, F + 2 * cs, nic * nhp, nhp, ncb, 0.0, &ip,
+        pm::IcTables it;
+        LAUNCH(pm::K_AXIS0, pm::launch_ic_tables(&ip, nic, c->ws.partial, &it, s));
+        LAUNCH(pm::K_AXIS0, pm::launch_axis0(lg, pm::MULT_IC, S0, n2, nic, F, F + cs, F + 2 * cs, nic * nhp, nhp, ncb, 0.0, &it,
                                 c->ws.tw, s));
         for (int d = 0; d < 3; d++) {
             LAUNCH(pm::K_COLS_INV, pm::launch_cols(lg, true, F + d * cs, nhp, nic * nhp, nic, ncb, c->ws.tw, s));
@@ -1390,7 +1392,9 @@ pm_status pm_ic_vjp(pm_ctx *c, const float *xbar, const float *pbar, float *wbar
             LAUNCH(pm::K_COLS_FWD, pm::launch_cols(lg, false, Fd, nhp, nic * nhp, nic, ncb, c->ws.tw, s));
             LAUNCH(pm::K_COLS_FWD, pm::launch_cols(lg, false, Fd, nic * nhp, nhp, nic, ncb, c->ws.tw, s));
         }
-        LAUNCH(pm::K_ADJOINT, pm::launch_ic_adj_mult(F, nhp, cs, nic, &ip, A, pass > 0, s));
+        pm::IcTables it;
+        LAUNCH(pm::K_ADJOINT, pm::launch_ic_tables(&ip, nic, c->ws.partial, &it, s));
+        LAUNCH(pm::K_ADJOINT, pm::launch_ic_adj_mult(F, nhp, cs, nic, &it, A, pass > 0, s));
     }
     LAUNCH(pm::K_COLS_INV, pm::launch_cols(lg, true, A, nic * nhp, nhp, nic, ncb, c->ws.tw, s));
     LAUNCH(pm::K_COLS_INV, pm::launch_cols(lg, true, A, nhp, nic * nhp, nic, ncb, c->ws.tw, s));

@@ -328,9 +328,20 @@ struct IcParams {
     double omh;              // Omega_m h
     double n_s;
     double kfs;              // free-streaming wavenumber (h/Mpc), <= 0: none
-    double half_cell;        // phase shift (Mpc/h) or 0
+    double half_cell;        // phase shift of half a cell of the lattice (Mpc/h), or 0
     double scale;            // 1/M_ic x mesh cells per Mpc/h
 };
+
+// Tables of the transfer on an n^3 lattice: by |n|^2 and by n0 + n1 + n2.  buf:
+// 3 (n/2)^2 + 2 + 2 n doubles, 16-byte aligned (IC_TABLE for the largest n).
+constexpr int64_t IC_TABLE = 3LL * 1024 * 1024 + 2 + 2 * 2048;
+static_assert(IC_TABLE <= POWER_OUT + 3 * MAX_BINS, "the tables fit the power partials");
+struct IcTables {
+    const double *radial = nullptr;
+    const double2 *phase = nullptr;
+    int shifted = 0;         // multiply by exp(i k.h)
+};
+hipError_t launch_ic_tables(const IcParams *ic, int n, double *buf, IcTables *out, hipStream_t s);
 
 hipError_t launch_r2c_rows_i64(int logn, const int64_t *src, int64_t src_stride, float2 *dst,
                                int64_t dst_stride, int64_t nrows, double scale, double offset,
@@ -347,7 +358,7 @@ hipError_t launch_cols(int logn, bool inverse, float2 *base, int64_t stride_l, i
 enum { MULT_FORCE = 0, MULT_IC = 1, MULT_NONE = 2 };
 hipError_t launch_axis0(int logn, int mode, const float2 *src, int64_t s_l, int64_t s_o, float2 *out0,
                         float2 *out1, float2 *out2, int64_t o_l, int64_t o_o, int n_cb, double coef,
-                        const IcParams *ic, const float2 *tw, hipStream_t s);
+                        const IcTables *ic, const float2 *tw, hipStream_t s);
 // Axis 0 of the force solve at N >= 256 as two passes (N = 16 x N/16), on
 // fields of nhp-padded half spectra whose planes hold `plane` = N nhp complex:
 // pass A (16-point DFTs over planes N/16 apart, twiddled; or its inverse) on
@@ -377,7 +388,7 @@ hipError_t launch_x0_power(int logn, const float2 *srca, const float2 *srcb, int
 hipError_t launch_c2r_x0(int logn, const float2 *src, float *dst, int64_t dst_stride, int64_t dst_plane, int nhp,
                          int64_t plane, const float2 *tw, hipStream_t s);
 
-hipError_t launch_ic_adj_mult(const float2 *G, int64_t nhp, int64_t fs, int n, const IcParams *ic, float2 *acc,
+hipError_t launch_ic_adj_mult(const float2 *G, int64_t nhp, int64_t fs, int n, const IcTables *ic, float2 *acc,
                               bool accumulate, hipStream_t s);
 
 // ---- launchers (adjoint.hip)
