@@ -326,13 +326,16 @@ __device__ __forceinline__ float col_factor(int mul, int row, int col)
 
 // V2: a thread moves two adjacent columns of a row per access (16 bytes;
 // base and dst 16-byte aligned, strides even), else one (8 bytes).
-// mul != 0 scales every element by col_factor before the transform; the
-// result goes to dst (the same offsets; dst == base: in place).
+// blockIdx.y: one of several fields fs apart.  mul != 0 scales every element by
+// col_factor before the transform; the result goes to dst (the same offsets;
+// dst == base: in place).
 template <int LOGN, bool INV, int WW, bool V2>
 __global__ __launch_bounds__((ColCfg<LOGN, WW>::T)) void k_cols(float2 *base, int64_t stride_l, int64_t stride_o,
-                                                              int n_cb, const float2 *__restrict__ tw, int mul,
-                                                              float2 *dst)
+                                                              int n_cb, const float2 *__restrict__ tw, int64_t fs,
+                                                              int mul, float2 *dst)
 {
+    base += blockIdx.y * fs;
+    dst += blockIdx.y * fs;
     using C = ColCfg<LOGN, WW>;
     constexpr int N = C::N, W = C::W, E = C::E, T = C::T;
     __shared__ float2 buf[E];
@@ -390,6 +393,58 @@ __global__ __launch_bounds__((ColCfg<LOGN, WW>::T)) void k_cols(float2 *base, in
         fft_from<N, 1, W, T, true, W, 1, INV, 4, SW>(buf, twl);
 #pragma unroll
         for (int i = 0; i < C::PER; i++) q[i * step] = buf[pad<SW>(tid + i * T)];
+    }
+}
+
+// The force solve's inverse axis-1 pass over its two spectra, k0 T (f0) and T
+// (f1), to the three components in one launch: a workgroup of blockIdx.y 0 forms
+// components 2 and 1 from its tile of T (times k2 and k1 on load), which it reads
+// again for the second while the caches hold it; blockIdx.y 1 transforms k0 T.
+// Against k_cols on each component 76 to 94 us at 256^3, but 720 to 745 at 512^3
+// with the row passes after it 8 % slower (a component no longer follows its own
+// columns through the last-level cache), and 6055 to 5390 at 1024^3 (three
+// streams gigabytes apart instead of two): for 256^3 alone.  (Keeping T in
+// registers instead takes 136 of the 128 there are.)
+template <int LOGN>
+__global__ __launch_bounds__((ColCfg<LOGN>::T)) void k_cols_grad(float2 *f0, float2 *f1, float2 *f2, int64_t stride_l,
+                                                               int64_t stride_o, int n_cb, const float2 *__restrict__ tw)
+{
+    using C = ColCfg<LOGN>;
+    constexpr int N = C::N, W = C::W, E = C::E, T = C::T, HW = W / 2, NV = C::PER / 2, RSTEP = T / HW;
+    constexpr int SW = -(3 + C::R1);
+    static_assert(C::PER % 2 == 0 && T % HW == 0, "pairs per thread");
+    __shared__ float2 buf[E];
+    __shared__ float2 twl[N];
+    const int tile = xcd_tile(blockIdx.x, gridDim.x);
+    const int o = tile / n_cb, cb = tile % n_cb;
+    const int tid = threadIdx.x, col = cb * W + 2 * (tid % HW), row0 = tid / HW;
+    for (int i = tid; i < N; i += T) twl[i] = tw[N + i];
+    const int64_t off = (int64_t)o * stride_o + col + (int64_t)row0 * stride_l, step = (int64_t)RSTEP * stride_l;
+    const bool both = blockIdx.y == 0;
+    const float ka = both ? col_factor<N>(2, 0, col) : 1.f, kb = both ? col_factor<N>(2, 0, col + 1) : 1.f;
+    // pass 0: component 2 (or 0); pass 1: component 1
+#pragma unroll 1
+    for (int pass = 0; pass < (both ? 2 : 1); pass++) {
+        const float2 *src = (both ? f1 : f0) + off;
+        float2 *dst = (pass ? f1 : (both ? f2 : f0)) + off;
+#pragma unroll
+        for (int i = 0; i < NV; i++) {
+            const float4 v = *reinterpret_cast<const float4 *>(src + i * step);
+            const float f = pass ? col_factor<N>(1, row0 + i * RSTEP, 0) : 1.f;
+            const float fa = pass ? f : ka, fb = pass ? f : kb;
+            const int e = 2 * (tid + i * T);
+            buf[pad<SW>(e)] = make_float2(fa * v.x, fa * v.y);
+            buf[pad<SW>(e + 1)] = make_float2(fb * v.z, fb * v.w);
+        }
+        __syncthreads();
+        fft_from<N, 1, W, T, true, W, 1, true, 4, SW>(buf, twl);
+#pragma unroll
+        for (int i = 0; i < NV; i++) {
+            // a thread's own slots: the next pass overwrites them without a barrier
+            const int e = 2 * (tid + i * T);
+            const float2 a = buf[pad<SW>(e)], b = buf[pad<SW>(e + 1)];
+            *reinterpret_cast<float4 *>(dst + i * step) = make_float4(a.x, a.y, b.x, b.y);
+        }
     }
 }
 
@@ -961,9 +1016,11 @@ __global__ __launch_bounds__(1 << (LOGN - 1)) void k_r2c_x0(const SRC *src, int6
 template <int LOGN>
 __global__ __launch_bounds__(1 << (LOGN - 1)) void k_c2r_x0(const float2 *src, float *dst, int64_t dst_stride,
                                                             int64_t dst_plane, int nhp, int64_t plane,
-                                                            const float2 *__restrict__ tw)
+                                                            const float2 *__restrict__ tw, int64_t fs)
 {
     constexpr int N = 1 << LOGN, L = N / 2, T = L, N2 = N / 16, RB = 16, LS = L, PS = SWZ_ROWS;
+    src += blockIdx.y * fs;         // fields fs complex apart
+    dst += blockIdx.y * (2 * fs);
     __shared__ float2 buf[padded(RB * LS, PS)];
     __shared__ float2 twl[L];   // the row stages' twiddles (one per thread)
     __shared__ float2 xnq[RB];  // the Nyquist column X_L of the 16 rows
@@ -1089,22 +1146,22 @@ hipError_t launch_c2r_rows(int logn, const float2 *src, int64_t src_stride, floa
 }
 
 hipError_t launch_cols(int logn, bool inverse, float2 *base, int64_t stride_l, int64_t stride_o, int n_o,
-                       int n_cb, const float2 *tw, hipStream_t s, int mul, float2 *dst)
+                       int n_cb, const float2 *tw, hipStream_t s, int nf, int64_t fs, int mul, float2 *dst)
 {
-    const unsigned nb = (unsigned)n_o * (unsigned)n_cb;
-    if (mul < 0 || mul > 2) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)n_o * (unsigned)n_cb, (unsigned)nf);
+    if (nf < 1 || mul < 0 || mul > 2) return hipErrorInvalidValue;
     if (!dst) dst = base;
     // 16-byte accesses where the layout allows them
     const bool v2 = logn >= 4 && ((reinterpret_cast<uintptr_t>(base) | reinterpret_cast<uintptr_t>(dst)) & 15) == 0 &&
-                    stride_l % 2 == 0 && stride_o % 2 == 0;
+                    stride_l % 2 == 0 && stride_o % 2 == 0 && fs % 2 == 0;
 #define COLS_V(LG, V)                                                                                \
     {                                                                                                \
         if (inverse)                                                                                 \
-            hipLaunchKernelGGL((k_cols<LG, true, TILE_W, V>), dim3(nb), dim3(ColCfg<LG>::T), 0, s, base, \
-                               stride_l, stride_o, n_cb, tw, mul, dst);                             \
+            hipLaunchKernelGGL((k_cols<LG, true, TILE_W, V>), grid, dim3(ColCfg<LG>::T), 0, s, base, \
+                               stride_l, stride_o, n_cb, tw, fs, mul, dst);                         \
         else                                                                                         \
-            hipLaunchKernelGGL((k_cols<LG, false, TILE_W, V>), dim3(nb), dim3(ColCfg<LG>::T), 0, s, base, \
-                               stride_l, stride_o, n_cb, tw, mul, dst);                             \
+            hipLaunchKernelGGL((k_cols<LG, false, TILE_W, V>), grid, dim3(ColCfg<LG>::T), 0, s, base, \
+                               stride_l, stride_o, n_cb, tw, fs, mul, dst);                         \
     }
 #define COLS(LG)                                                                                     \
     {                                                                                                \
@@ -1115,6 +1172,16 @@ hipError_t launch_cols(int logn, bool inverse, float2 *base, int64_t stride_l, i
         }                                                                                            \
     }
     PM_DISPATCH_LOGN(logn, COLS)
+    return hipGetLastError();
+}
+
+hipError_t launch_cols_grad(int logn, float2 *F, int64_t fs, int64_t nhp, int64_t plane, const float2 *tw, hipStream_t s)
+{
+    if (logn != 8 || (reinterpret_cast<uintptr_t>(F) & 15) != 0 || nhp % TILE_W || plane % 2 || fs % 2)
+        return hipErrorInvalidValue;
+    const int n = 1 << logn, ncb = (int)(half_cols(n) / TILE_W);
+    hipLaunchKernelGGL(k_cols_grad<8>, dim3((unsigned)n * (unsigned)ncb, 2), dim3(ColCfg<8>::T), 0, s, F, F + fs, F + 2 * fs,
+                       nhp, plane, ncb, tw);
     return hipGetLastError();
 }
 
@@ -1247,17 +1314,17 @@ hipError_t launch_r2c_x0_f32(int logn, const float *src, int64_t src_rs, float2 
 }
 
 hipError_t launch_c2r_x0(int logn, const float2 *src, float *dst, int64_t dst_stride, int64_t dst_plane, int nhp,
-                         int64_t plane, const float2 *tw, hipStream_t s)
+                         int64_t plane, const float2 *tw, hipStream_t s, int nf, int64_t fs)
 {
-    if (logn < 8 || logn > 11 || plane < ((int64_t)nhp << logn)) return hipErrorInvalidValue;
+    if (logn < 8 || logn > 11 || nf < 1 || plane < ((int64_t)nhp << logn)) return hipErrorInvalidValue;
     // the rows are stored 16 bytes at a time
     if ((reinterpret_cast<uintptr_t>(dst) & 15) != 0 || dst_stride % 4 != 0 || dst_plane % 4 != 0 ||
-        dst_plane < (dst_stride << logn))
+        (nf > 1 && fs % 2 != 0) || dst_plane < (dst_stride << logn))
         return hipErrorInvalidValue;
     const unsigned nb = (unsigned)((1 << logn) / 16) << logn;
 #define C2RX(LG)                                                                                     \
-    hipLaunchKernelGGL((k_c2r_x0<LG>), dim3(nb), dim3(1 << (LG - 1)), 0, s, src, dst, dst_stride, dst_plane, nhp, \
-                       plane, tw)
+    hipLaunchKernelGGL((k_c2r_x0<LG>), dim3(nb, (unsigned)nf), dim3(1 << (LG - 1)), 0, s, src, dst, dst_stride, \
+                       dst_plane, nhp, plane, tw, fs)
     switch (logn) {
     case 8: C2RX(8); break;
     case 9: C2RX(9); break;

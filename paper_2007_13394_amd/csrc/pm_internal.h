@@ -350,10 +350,14 @@ hipError_t launch_r2c_rows_f32(int logn, const float *src, int64_t src_stride, f
                                int64_t dst_stride, int64_t nrows, const float2 *tw, hipStream_t s);
 hipError_t launch_c2r_rows(int logn, const float2 *src, int64_t src_stride, float *dst,
                            int64_t dst_stride, int64_t nrows, const float2 *tw, hipStream_t s);
-// mul: 0, or the k1 (1) / k2 (2) factor of a force component applied before
-// the transform; dst: output at the same offsets (nullptr: in place).
-hipError_t launch_cols(int logn, bool inverse, float2 *base, int64_t stride_l, int64_t stride_o,
-                       int n_o, int n_cb, const float2 *tw, hipStream_t s, int mul = 0, float2 *dst = nullptr);
+// nf fields fs apart; mul: 0, or the k1 (1) / k2 (2) factor of a force component
+// applied before the transform; dst: output at the same offsets (nullptr: in
+// place).
+hipError_t launch_cols(int logn, bool inverse, float2 *base, int64_t stride_l, int64_t stride_o, int n_o, int n_cb,
+                       const float2 *tw, hipStream_t s, int nf = 1, int64_t fs = 0, int mul = 0, float2 *dst = nullptr);
+// Inverse axis-1 pass of the force solve at N = 256: fields F (k0 T) and F + fs (T),
+// as launch_x0_green leaves them, to the three components fs apart.
+hipError_t launch_cols_grad(int logn, float2 *F, int64_t fs, int64_t nhp, int64_t plane, const float2 *tw, hipStream_t s);
 // axis-0 pass: forward FFT, then per output a multiplier and an inverse FFT.
 enum { MULT_FORCE = 0, MULT_IC = 1, MULT_NONE = 2 };
 hipError_t launch_axis0(int logn, int mode, const float2 *src, int64_t s_l, int64_t s_o, float2 *out0,
@@ -365,7 +369,7 @@ hipError_t launch_axis0(int logn, int mode, const float2 *src, int64_t s_l, int6
 // nf fields field_stride apart, and pass B fused with the gradient of the
 // inverse Laplacian: out0 <- k0 T, out1 <- T, T = coef i S / k^2 (src may
 // alias out0; the k1 and k2 factors are applied by the inverse column passes,
-// launch_cols mul 1 and 2; outputs digit-reversed until the inverse of pass A).
+// launch_cols mul 1 and 2 or launch_cols_grad; outputs digit-reversed until the inverse of pass A).
 hipError_t launch_x0_green(int logn, const float2 *src, float2 *out0, float2 *out1, int64_t plane, int nhp,
                            double coef, const float2 *tw, hipStream_t s);
 // Row transforms fused with pass A (forward: int64 density rows -> twiddled
@@ -386,7 +390,7 @@ hipError_t launch_x0_learned(int logn, const float2 *srcd, const float2 *srcc, f
 hipError_t launch_x0_power(int logn, const float2 *srca, const float2 *srcb, int64_t plane, int nhp, int nbins,
                            int compensate, double norm, double *partial, int blocks, const float2 *tw, hipStream_t s);
 hipError_t launch_c2r_x0(int logn, const float2 *src, float *dst, int64_t dst_stride, int64_t dst_plane, int nhp,
-                         int64_t plane, const float2 *tw, hipStream_t s);
+                         int64_t plane, const float2 *tw, hipStream_t s, int nf = 1, int64_t fs = 0);
 
 hipError_t launch_ic_adj_mult(const float2 *G, int64_t nhp, int64_t fs, int n, const IcTables *ic, float2 *acc,
                               bool accumulate, hipStream_t s);
