@@ -27,47 +27,79 @@ inline unsigned grid_for(int64_t n, int block, int64_t cap = 65536LL * 16)
 }
 
 
-// Each workgroup takes a chunk of NR x SORT_T consecutive particles, workgroups
-// numbered so that each XCD owns a contiguous run of chunks (the scatter of a
-// nearly sorted state then writes whole cache lines from one L2).  Eight rounds
-// per thread where that still gives every CU several workgroups; below
-// SORT_FEW particles one round, since a small sort waits on its chain of
-// rounds and not on memory bandwidth (69 k particles on 64^3: count 27 -> 9 us,
-// scatter 33 -> 11 us; sorted steps 13.3 -> 6.4 us).
+// Each workgroup takes a chunk of consecutive particles, workgroups numbered so
+// that each XCD owns a contiguous run of chunks (the scatter of a nearly
+// sorted state then writes whole cache lines from one L2).  Below SORT_FEW
+// particles one per thread: a small sort waits on its chain of rounds and not
+// on memory bandwidth or atomics (69 k particles on 64^3, against eight per
+// thread: count 27 -> 9 us, scatter 33 -> 11 us; sorted steps 13.3 -> 6.4 us).
 constexpr int SORT_T = 256;
 constexpr int64_t SORT_FEW = 1 << 20;
-// particles per batch in the scatter: two keep it at 38 VGPRs; four and eight
-// (66, 114 VGPRs) gain nothing at 2048^3 and lose at 256^3 (lower occupancy)
-constexpr int SCATTER_SB = 2;
 
-template <int NR>
 __global__ __launch_bounds__(SORT_T) void k_sort_count(const float *__restrict__ x, int64_t P, int n, int *cnt)
 {
     const int lane = threadIdx.x & 63;
-    constexpr int SORT_CH = NR * SORT_T;
-    const int64_t c0 = (int64_t)xcd_tile(blockIdx.x, gridDim.x) * SORT_CH;
-    const int64_t c1 = c0 + SORT_CH < P ? c0 + SORT_CH : P;
-    if (c0 >= c1) return;
-    // All rounds' positions are loaded up front (NR per thread; indices past
-    // the chunk are clamped to c0, a valid particle); the atomics return
-    // nothing, so no round waits on memory after the first.
-    float a0[NR], a1[NR], a2[NR];
+    const int64_t i = (int64_t)xcd_tile(blockIdx.x, gridDim.x) * SORT_T + threadIdx.x;
+    const bool live = i < P;
+    const int k = live ? tile_key(x[i], x[P + i], x[2 * P + i], n) : -1;
+    uint64_t group;
+    int leader;
+    key_group(live, k, group, leader);
+    if (live && lane == leader) atomicAdd(cnt + k, __popcll(group));
+}
+
+// The same for large particle sets: a workgroup of WG_R x SORT_T particles first
+// gathers its counts per key in an LDS hash table (open addressing, twice as
+// many slots as particles, so that a probe always ends), then adds each key
+// once.  Device-wide atomics do not combine across the eight L2s and set the pace of
+// the sort: a chunk of lattice-ordered CDM has about 150 keys, its 32 wavefronts
+// 600.  19 M particles on 512^3: count 381 -> 234 us,
+// scatter of a sorted state 404 -> 248 us, of canonical order 604 -> 458 us
+// (with indices).
+constexpr int WG_R = 8, HASH = 2 * WG_R * SORT_T;
+
+__device__ __forceinline__ int hash_slot(int *keys, int key)
+{
+    static_assert(HASH == 4096, "12 hash bits");
+    unsigned h = ((unsigned)key * 2654435761u) >> 20;
+    for (;;) {
+        int old = __hip_atomic_load(keys + h, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        if (old == -1) old = atomicCAS(keys + h, -1, key);
+        if (old == -1 || old == key) return (int)h;
+        h = (h + 1) & (HASH - 1);
+    }
+}
+
+__device__ __forceinline__ void hash_clear(int *keys, int *cnt)
+{
+    for (int i = threadIdx.x; i < HASH; i += SORT_T) {
+        keys[i] = -1;
+        cnt[i] = 0;
+    }
+}
+
+__global__ __launch_bounds__(SORT_T) void k_sort_count_wg(const float *__restrict__ x, int64_t P, int n, int *cnt)
+{
+    __shared__ int hkey[HASH], hcnt[HASH];
+    const int64_t c0 = (int64_t)blockIdx.x * (WG_R * SORT_T);
+    float a0[WG_R], a1[WG_R], a2[WG_R];
 #pragma unroll
-    for (int r = 0; r < NR; r++) {
-        const int64_t i = c0 + threadIdx.x + r * SORT_T, ic = i < c1 ? i : c0;
+    for (int r = 0; r < WG_R; r++) {
+        const int64_t i = c0 + threadIdx.x + r * SORT_T, ic = i < P ? i : P - 1;
         a0[r] = x[ic];
         a1[r] = x[P + ic];
         a2[r] = x[2 * P + ic];
     }
+    hash_clear(hkey, hcnt);
+    __syncthreads();
 #pragma unroll
-    for (int r = 0; r < NR; r++) {
-        const bool live = c0 + threadIdx.x + r * SORT_T < c1;
-        const int k = live ? tile_key(a0[r], a1[r], a2[r], n) : -1;
-        uint64_t group;
-        int leader;
-        key_group(live, k, group, leader);
-        if (live && lane == leader) atomicAdd(cnt + k, __popcll(group));
+    for (int r = 0; r < WG_R; r++) {
+        const bool live = c0 + threadIdx.x + r * SORT_T < P;
+        if (live) atomicAdd(hcnt + hash_slot(hkey, tile_key(a0[r], a1[r], a2[r], n)), 1);
     }
+    __syncthreads();
+    for (int i = threadIdx.x; i < HASH; i += SORT_T)
+        if (hcnt[i] > 0) atomicAdd(cnt + hkey[i], hcnt[i]);
 }
 
 // Exclusive scan of up to SCAN_ONE counts by one workgroup, all loads in
@@ -220,107 +252,134 @@ __global__ void k_scan_add(int *out, int64_t n, const int *sums, int *out2)
 // Scatter into float4 records: one 16-byte store for the position and the
 // segment tag, one for the momentum, so a particle that moves far in the
 // order costs two stores instead of seven partial ones.  The optional arrays
-// are template flags (HI 1: the caller's ids, 2: the particle's index).  A thread takes its NR particles in batches of SB:
-// a batch's particles are loaded at once, then its cursor atomics are issued
-// back to back, then its stores (two memory round trips per batch).  The
+// are template flags (HI 1: the caller's ids, 2: the particle's index).  The
 // pointers do not alias (caller arrays in, workspace records out).
-template <bool HP, bool HT, int HI, int NR, int SB>
-__device__ __forceinline__ void scatter_chunk(int64_t c0, int64_t c1, const float *__restrict__ x,
-                                              const float *__restrict__ p, const uint8_t *__restrict__ tag_in,
-                                              int64_t P, int nseg, const int64_t *__restrict__ seg_off, int n,
-                                              int *cursor, float4 *__restrict__ xs, Mom3 *__restrict__ ps,
-                                              const uint32_t *__restrict__ ids_in, uint32_t *__restrict__ ids_out)
+template <bool HP, bool HT, int HI>
+__global__ __launch_bounds__(SORT_T) void k_sort_scatter(const float *__restrict__ x, const float *__restrict__ p,
+                                                         const uint8_t *__restrict__ tag_in, int64_t P, int nseg,
+                                                         const int64_t *__restrict__ seg_off, int n, int *cursor,
+                                                         float4 *__restrict__ xs, Mom3 *__restrict__ ps,
+                                                         const uint32_t *__restrict__ ids_in,
+                                                         uint32_t *__restrict__ ids_out)
 {
-    static_assert(NR % SB == 0, "whole batches");
     const int lane = threadIdx.x & 63;
-    for (int r0 = 0; r0 < NR; r0 += SB) {
-        // indices past the chunk are clamped to c0, a valid particle, and dropped
-        float a0[SB], a1[SB], a2[SB], b0[SB], b1[SB], b2[SB];
-        int t[SB];
-        uint32_t id[SB];
+    const int64_t i = (int64_t)xcd_tile(blockIdx.x, gridDim.x) * SORT_T + threadIdx.x, ic = i < P ? i : P - 1;
+    const bool live = i < P;
+    const float a0 = x[ic], a1 = x[P + ic], a2 = x[2 * P + ic];
+    Mom3 b{0.f, 0.f, 0.f};
+    if constexpr (HP) b = Mom3{p[ic], p[P + ic], p[2 * P + ic]};
+    int t = 0;
+    if constexpr (HT) {
+        t = tag_in[ic];
+    } else {   // canonical order: segment from the offsets
+        for (int g = 1; g < nseg; g++) t += (ic >= seg_off[g]) ? 1 : 0;
+    }
+    uint32_t id = 0;
+    if constexpr (HI == 1) id = ids_in[ic];
+    if constexpr (HI == 2) id = (uint32_t)ic;
+    const int k = live ? tile_key(a0, a1, a2, n) : -1;
+    uint64_t group;
+    int leader, base = 0;
+    key_group(live, k, group, leader);
+    if (live && lane == leader) base = atomicAdd(cursor + k, __popcll(group));
+    const int64_t d = (int64_t)__shfl(base, leader) + __popcll(group & ((1ull << lane) - 1));
+    if (live && d < P) {   // d >= P only with counts that do not match x (k_sort_verify reports it)
+        xs[d] = make_float4(a0, a1, a2, __int_as_float(t));
+        if constexpr (HP) ps[d] = b;
+        if constexpr (HI) ids_out[d] = id;
+    }
+}
+
+constexpr int CHUNK_RUN = 32;
+__device__ __forceinline__ int run_tile(int b, int nb)
+{
+    // full rounds of 8 x CHUNK_RUN chunks, the rest in plain order
+    const int round = 8 * CHUNK_RUN, full = nb / round * round;
+    if (b >= full) return b;
+    const int x = b % 8, i = b / 8;
+    return (i / CHUNK_RUN) * round + x * CHUNK_RUN + i % CHUNK_RUN;
+}
+
+// The scatter with a chunk's slots taken key by key (see k_sort_count_wg): all of
+// a thread's particles are loaded at once and ranked within the chunk, each
+// key's cursor is advanced once, then the records are stored.
+template <bool HP, bool HT, int HI>
+__device__ __forceinline__ void scatter_wg(int *hkey, int *hcnt, int64_t c0, const float *__restrict__ x,
+                                           const float *__restrict__ p, const uint8_t *__restrict__ tag_in, int64_t P,
+                                           int nseg, const int64_t *__restrict__ seg_off, int n, int *cursor,
+                                           float4 *__restrict__ xs, Mom3 *__restrict__ ps,
+                                           const uint32_t *__restrict__ ids_in, uint32_t *__restrict__ ids_out)
+{
+    float a0[WG_R], a1[WG_R], a2[WG_R], b0[WG_R], b1[WG_R], b2[WG_R];
+    int t[WG_R];
+    uint32_t id[WG_R];
 #pragma unroll
-        for (int r = 0; r < SB; r++) {
-            const int64_t i = c0 + threadIdx.x + (r0 + r) * SORT_T, ic = i < c1 ? i : c0;
-            a0[r] = x[ic];
-            a1[r] = x[P + ic];
-            a2[r] = x[2 * P + ic];
-            if constexpr (HP) {
-                b0[r] = p[ic];
-                b1[r] = p[P + ic];
-                b2[r] = p[2 * P + ic];
-            } else {
-                b0[r] = b1[r] = b2[r] = 0.f;
-            }
+    for (int r = 0; r < WG_R; r++) {
+        const int64_t i = c0 + threadIdx.x + r * SORT_T, ic = i < P ? i : P - 1;
+        a0[r] = x[ic];
+        a1[r] = x[P + ic];
+        a2[r] = x[2 * P + ic];
+        if constexpr (HT) t[r] = tag_in[ic];
+        if constexpr (HI == 1) id[r] = ids_in[ic];
+    }
+    hash_clear(hkey, hcnt);
+    __syncthreads();
+    int at[WG_R];   // slot and rank within the chunk's particles of the key
+#pragma unroll
+    for (int r = 0; r < WG_R; r++) {
+        const bool live = c0 + threadIdx.x + r * SORT_T < P;
+        at[r] = 0;
+        if (live) {
+            const int h = hash_slot(hkey, tile_key(a0[r], a1[r], a2[r], n));
+            at[r] = (h << 16) | atomicAdd(hcnt + h, 1);
+        }
+    }
+    if constexpr (HP) {
+#pragma unroll
+        for (int r = 0; r < WG_R; r++) {
+            const int64_t i = c0 + threadIdx.x + r * SORT_T, ic = i < P ? i : P - 1;
+            b0[r] = p[ic];
+            b1[r] = p[P + ic];
+            b2[r] = p[2 * P + ic];
+        }
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < HASH; i += SORT_T)
+        if (hcnt[i] > 0) hcnt[i] = atomicAdd(cursor + hkey[i], hcnt[i]);
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < WG_R; r++) {
+        const int64_t i = c0 + threadIdx.x + r * SORT_T;
+        const int64_t d = (int64_t)hcnt[at[r] >> 16] + (at[r] & 0xffff);
+        if (i < P && d < P) {   // d >= P only with counts that do not match x (k_sort_verify reports it)
+            int g = 0;
             if constexpr (HT) {
-                t[r] = tag_in[ic];
+                g = t[r];
             } else {   // canonical order: segment from the offsets
-                int g0 = 0;
-                for (int g = 1; g < nseg; g++) g0 += (ic >= seg_off[g]) ? 1 : 0;
-                t[r] = g0;
+                for (int k = 1; k < nseg; k++) g += (i >= seg_off[k]) ? 1 : 0;
             }
-            id[r] = 0;
-            if constexpr (HI == 1) id[r] = ids_in[ic];
-            if constexpr (HI == 2) id[r] = (uint32_t)ic;
-        }
-        uint64_t group[SB];
-        int leader[SB], base[SB];
-#pragma unroll
-        for (int r = 0; r < SB; r++) {
-            const bool live = c0 + threadIdx.x + (r0 + r) * SORT_T < c1;
-            const int k = live ? tile_key(a0[r], a1[r], a2[r], n) : -1;
-            key_group(live, k, group[r], leader[r]);
-            base[r] = 0;
-            if (live && lane == leader[r]) base[r] = atomicAdd(cursor + k, __popcll(group[r]));
-        }
-#pragma unroll
-        for (int r = 0; r < SB; r++) {
-            const bool live = c0 + threadIdx.x + (r0 + r) * SORT_T < c1;
-            const int b = __shfl(base[r], leader[r]);
-            const int64_t d = (int64_t)b + __popcll(group[r] & ((1ull << lane) - 1));
-            if (live && d < P) {   // d >= P only with counts that do not match x (k_sort_verify reports it)
-                xs[d] = make_float4(a0[r], a1[r], a2[r], __int_as_float(t[r]));
-                if constexpr (HP) ps[d] = Mom3{b0[r], b1[r], b2[r]};
-                if constexpr (HI) ids_out[d] = id[r];
-            }
+            xs[d] = make_float4(a0[r], a1[r], a2[r], __int_as_float(g));
+            if constexpr (HP) ps[d] = Mom3{b0[r], b1[r], b2[r]};
+            if constexpr (HI == 1) ids_out[d] = id[r];
+            if constexpr (HI == 2) ids_out[d] = (uint32_t)i;
         }
     }
 }
 
-template <int NR>
-__global__ __launch_bounds__(SORT_T) void k_sort_scatter(const float *__restrict__ x, const float *__restrict__ p,
-                                                         const uint8_t *__restrict__ tag_in, int64_t P, int nseg,
-                                                         const int64_t *__restrict__ seg_off, int n, int *cursor,
-                                                         float4 *xs, Mom3 *ps, const uint32_t *ids_in,
-                                                         uint32_t *ids_out)
+template <bool HP, bool HT, int HI>
+__global__ __launch_bounds__(SORT_T) void k_sort_scatter_wg(const float *__restrict__ x, const float *__restrict__ p,
+                                                            const uint8_t *__restrict__ tag_in, int64_t P, int nseg,
+                                                            const int64_t *__restrict__ seg_off, int n, int *cursor,
+                                                            float4 *xs, Mom3 *ps, const uint32_t *ids_in,
+                                                            uint32_t *ids_out)
 {
-    constexpr int SORT_CH = NR * SORT_T;
-    const int64_t c0 = (int64_t)xcd_tile(blockIdx.x, gridDim.x) * SORT_CH;
-    const int64_t c1 = c0 + SORT_CH < P ? c0 + SORT_CH : P;
-    if (c0 >= c1) return;
-#define SCATTER(HP, HT, HI) \
-    scatter_chunk<HP, HT, HI, NR, (NR < SCATTER_SB ? NR : SCATTER_SB)>(c0, c1, x, p, tag_in, P, nseg, seg_off, n, cursor, xs, ps, ids_in, ids_out)
-    if (p) {
-        if (tag_in) {
-            if (ids_in) SCATTER(true, true, 1);
-            else if (ids_out) SCATTER(true, true, 2);
-            else SCATTER(true, true, 0);
-        } else {
-            if (ids_in) SCATTER(true, false, 1);
-            else if (ids_out) SCATTER(true, false, 2);
-            else SCATTER(true, false, 0);
-        }
-    } else {
-        if (tag_in) {
-            if (ids_in) SCATTER(false, true, 1);
-            else if (ids_out) SCATTER(false, true, 2);
-            else SCATTER(false, true, 0);
-        } else {
-            if (ids_in) SCATTER(false, false, 1);
-            else if (ids_out) SCATTER(false, false, 2);
-            else SCATTER(false, false, 0);
-        }
-    }
-#undef SCATTER
+    __shared__ int hkey[HASH], hcnt[HASH];
+    // Sorted input (tags): contiguous runs of chunks per XCD, whose stores meet in
+    // one L2.  Canonical order: runs of CHUNK_RUN chunks dealt to the XCDs in
+    // turn, else the last of them gets all the neutrinos, the slowest chunks.
+    const int b = HT ? xcd_tile(blockIdx.x, gridDim.x) : run_tile(blockIdx.x, gridDim.x);
+    const int64_t c0 = (int64_t)b * (WG_R * SORT_T);
+    scatter_wg<HP, HT, HI>(hkey, hcnt, c0, x, p, tag_in, P, nseg, seg_off, n, cursor, xs, ps, ids_in, ids_out);
 }
 
 // After a scatter from counts computed elsewhere (the previous readout):
@@ -345,14 +404,13 @@ hipError_t launch_sort_verify(const int *cursor, const int *koff, int64_t K, int
 
 hipError_t launch_sort_count(const float *x, int64_t P, int n, int *cnt, hipStream_t s)
 {
-    const int nr = P < SORT_FEW ? 1 : 8;
-    const int64_t nb = (P + nr * SORT_T - 1) / (nr * SORT_T);
+    const int64_t ch = P < SORT_FEW ? SORT_T : WG_R * SORT_T, nb = (P + ch - 1) / ch;
     if (nb > 0x7fffffff) return hipErrorInvalidValue;
     const dim3 grid((unsigned)(nb > 0 ? nb : 1));
-    if (nr == 1)
-        hipLaunchKernelGGL(k_sort_count<1>, grid, dim3(SORT_T), 0, s, x, P, n, cnt);
+    if (P < SORT_FEW)
+        hipLaunchKernelGGL(k_sort_count, grid, dim3(SORT_T), 0, s, x, P, n, cnt);
     else
-        hipLaunchKernelGGL(k_sort_count<8>, grid, dim3(SORT_T), 0, s, x, P, n, cnt);
+        hipLaunchKernelGGL(k_sort_count_wg, grid, dim3(SORT_T), 0, s, x, P, n, cnt);
     return hipGetLastError();
 }
 
@@ -379,16 +437,34 @@ hipError_t launch_sort_scatter(const float *x, const float *p, const uint8_t *ta
                                const int64_t *seg_off, int n, int *cursor, float4 *xs, Mom3 *ps,
                                const uint32_t *ids_in, uint32_t *ids_out, hipStream_t s)
 {
-    const int nr = P < SORT_FEW ? 1 : 8;
-    const int64_t nb = (P + nr * SORT_T - 1) / (nr * SORT_T);
+    const int64_t ch = P < SORT_FEW ? SORT_T : WG_R * SORT_T, nb = (P + ch - 1) / ch;
     if (nb > 0x7fffffff || (ids_in && !ids_out)) return hipErrorInvalidValue;
     const dim3 grid((unsigned)(nb > 0 ? nb : 1));
-    if (nr == 1)
-        hipLaunchKernelGGL(k_sort_scatter<1>, grid, dim3(SORT_T), 0, s, x, p, tag_in, P, nseg, seg_off, n, cursor, xs, ps,
-                           ids_in, ids_out);
-    else
-        hipLaunchKernelGGL(k_sort_scatter<8>, grid, dim3(SORT_T), 0, s, x, p, tag_in, P, nseg, seg_off, n, cursor, xs, ps,
-                           ids_in, ids_out);
+    const int hi = ids_in ? 1 : (ids_out ? 2 : 0);
+#define SCATTER_K(HP, HT, HI)                                                                         \
+    {                                                                                                \
+        if (P < SORT_FEW)                                                                            \
+            hipLaunchKernelGGL((k_sort_scatter<HP, HT, HI>), grid, dim3(SORT_T), 0, s, x, p, tag_in, P, nseg, seg_off, \
+                               n, cursor, xs, ps, ids_in, ids_out);                                  \
+        else                                                                                         \
+            hipLaunchKernelGGL((k_sort_scatter_wg<HP, HT, HI>), grid, dim3(SORT_T), 0, s, x, p, tag_in, P, nseg, seg_off, \
+                               n, cursor, xs, ps, ids_in, ids_out);                                  \
+    }
+#define SCATTER_I(HP, HT)                                                                             \
+    {                                                                                                \
+        if (hi == 0) SCATTER_K(HP, HT, 0)                                                            \
+        else if (hi == 1) SCATTER_K(HP, HT, 1)                                                       \
+        else SCATTER_K(HP, HT, 2)                                                                    \
+    }
+    if (p) {
+        if (tag_in) SCATTER_I(true, true)
+        else SCATTER_I(true, false)
+    } else {
+        if (tag_in) SCATTER_I(false, true)
+        else SCATTER_I(false, false)
+    }
+#undef SCATTER_I
+#undef SCATTER_K
     return hipGetLastError();
 }
 
