@@ -79,10 +79,9 @@ enum {
     PM_FLAG_NU_PSEUDO = 16, /* pseudo-random neutrino velocities, one particle per
                                site (n_shell 1, n_fib 0): initial conditions by
                                pm_ic_pseudo instead of pm_ic */
-    PM_FLAG_DEFER_GUARDS = 32 /* check each call's device flags without waiting for
-                                 it: the copy is queued at the end of the call and
-                                 read by the next guarded call after that call has
-                                 queued its own work, or by pm_sync.  The next call
+    PM_FLAG_DEFER_GUARDS = 32 /* check each call's guard words without waiting for
+                                 it: they are read by the next guarded call after
+                                 that call has queued its own work, or by pm_sync.  The next call
                                  (or pm_sync) returns the error; the failing call
                                  returns PM_OK.  No host wait per call. */
 };
@@ -259,10 +258,10 @@ pm_status pm_force(pm_ctx *ctx, const float *x, float *acc, void *stream);
  * PM_FLAG_DEFER_GUARDS reported by the next guarded call or pm_sync).
  * On a sorting context the readout also counts the tile keys of the
  * positions it writes; the next call on the same x array sorts with those
- * counts and checks them after its scatter.  The check (a 4-byte copy) is
- * read back just before the readout, the paint and the force solve having
- * been queued behind it: if the caller changed x in between, the sort is
- * redone from a fresh count and the paint and the solve are queued again.
+ * counts and checks them after its scatter.  The check is read in the wait
+ * that ends the call (with PM_FLAG_DEFER_GUARDS just before the readout is
+ * queued): if the caller changed x in between, the readout has left the
+ * particles alone and the step is done again from a fresh count.
  * With PM_FLAG_NO_GUARDS every call counts afresh instead. */
 pm_status pm_step(pm_ctx *ctx, float *x, float *p, double a_force, double a_kick0, double a_kick1,
                   double a_drift1, void *stream);

@@ -301,7 +301,7 @@ __global__ void k_q_to_delta(const int64_t *q, int64_t m, double scale, float *d
         bad |= q[i] < GUARD_MIN_Q;
         delta[i] = (float)((double)q[i] * scale - 1.0);
     }
-    if (flag && bad) atomicOr(flag, FLAG_OVERFLOW);
+    if (flag && bad) raise(flag);
 }
 
 // Initial-condition transpose, CDM: sbar_d(t) = xbar_{d,t} + vfac pbar_{d,t}

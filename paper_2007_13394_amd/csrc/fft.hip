@@ -255,7 +255,7 @@ __global__ __launch_bounds__(256) void k_r2c_rows(const SRC *src, int64_t src_st
         }
         buf[e] = make_float2(a, b);
     }
-    if (bad) atomicOr(flag, FLAG_OVERFLOW);
+    if (bad) raise(flag);
     __syncthreads();
     fft_from<L, 1, RB, T, false, 1, L, false, 4>(buf, tw + L);
     // X_k = (Z_k + conj Z_{L-k}) / 2 - i w^k (Z_k - conj Z_{L-k}) / 2, w = exp(-2 pi i / N)
@@ -984,7 +984,7 @@ __global__ __launch_bounds__(1 << (LOGN - 1)) void k_r2c_x0(const SRC *src, int6
 #pragma unroll
         for (int r = 0; r < 16; r++) buf[pad<PS>(r * L + tid)] = q[r];
     }
-    if (bad) atomicOr(flag, FLAG_OVERFLOW);
+    if (bad) raise(flag);
     __syncthreads();
     fft_from<L, 1, RB, T, false, 1, L, false, 4, PS>(buf, twl);
     float2 *d0 = dst + (int64_t)j1 * plane + (int64_t)x1 * nhp;

@@ -5,6 +5,7 @@
 #include <stdio.h>
 #include <string.h>
 
+#include <algorithm>
 #include <cmath>
 
 #include <mutex>
@@ -232,51 +233,48 @@ void counts(const pm_config &c, int64_t *P, int64_t *nc, int64_t *nn, int *nseg)
 
 inline hipStream_t S(void *s) { return reinterpret_cast<hipStream_t>(s); }
 
-// The guard bits of a flag word read back as a status.
-static pm_status guard_status(int h, const char *which)
+// Guard word `which` for a call's kernels.
+static int *guard(pm_ctx *c, int which)
 {
-    if (h & pm::FLAG_NAN) return fail(PM_ERR_NAN, "a particle position or momentum became non-finite%s", which);
-    if (h & pm::FLAG_OVERFLOW) return fail(PM_ERR_OVERFLOW, "a density cell left the fixed-point range%s", which);
+    return c->cfg.flags & PM_FLAG_NO_GUARDS ? c->ws.flag + which : c->guards + c->guard_set * pm::FLAG_WORDS + which;
+}
+
+// A set of guard words as a status, cleared for its next use.  Its kernels have ended.
+static pm_status guard_status(pm_ctx *c, int set, const char *which)
+{
+    volatile int *w = c->guards + set * pm::FLAG_WORDS;
+    const bool nan = w[pm::FLAG_NAN], over = w[pm::FLAG_OVERFLOW] || w[pm::FLAG_RECORDS];
+    w[pm::FLAG_NAN] = w[pm::FLAG_OVERFLOW] = w[pm::FLAG_RECORDS] = 0;
+    if (nan) return fail(PM_ERR_NAN, "a particle position or momentum became non-finite%s", which);
+    if (over) return fail(PM_ERR_OVERFLOW, "a density cell left the fixed-point range%s", which);
     return PM_OK;
 }
 
-// PM_FLAG_DEFER_GUARDS: waits for the previous guarded call's flag copy (that
-// call's end only) and returns its status.
+// PM_FLAG_DEFER_GUARDS: waits for the previous guarded call (that call's end
+// only) and returns its status.
 static pm_status settle_guard(pm_ctx *c)
 {
     if (!c->guard_pending) return PM_OK;
     c->guard_pending = false;
-    HIPCHK(hipEventSynchronize(c->guard_ev[c->guard_slot]));
-    return guard_status(c->guard_host[c->guard_slot], " (in the previous call)");
+    const int set = c->guard_set ^ 1;
+    HIPCHK(hipEventSynchronize(c->guard_ev[set]));
+    return guard_status(c, set, " (in the previous call)");
 }
 
 pm_status check_guards(pm_ctx *c, hipStream_t s)
 {
     if (c->cfg.flags & PM_FLAG_NO_GUARDS) return PM_OK;
     if (c->cfg.flags & PM_FLAG_DEFER_GUARDS) {
-        // this call's word goes to the other pinned slot and is cleared on the
-        // device behind the copy, so each copy holds one call's bits; then the
-        // previous call's copy, long done, is read
-        const int slot = c->guard_slot ^ 1;
-        HIPCHK(hipMemcpyAsync(c->guard_host + slot, c->ws.flag, sizeof(int), hipMemcpyDeviceToHost, s));
-        LAUNCH(pm::K_FILL, pm::launch_fill_i32(c->ws.flag, 1, s));
-        HIPCHK(hipEventRecord(c->guard_ev[slot], s));
+        // the previous call, long done, is read; this call's words stay in
+        // their set and the next call's kernels get the one just read
+        HIPCHK(hipEventRecord(c->guard_ev[c->guard_set], s));
         const pm_status prev = settle_guard(c);
-        c->guard_slot = slot;
+        c->guard_set ^= 1;
         c->guard_pending = true;
         return prev;
     }
-    // through the pinned word (free here: a deferred sort verification is
-    // settled before any readout)
-    HIPCHK(hipMemcpyAsync(c->verify_host, c->ws.flag, sizeof(int), hipMemcpyDeviceToHost, s));
     HIPCHK(hipStreamSynchronize(s));
-    const int h = *c->verify_host;
-    if (h) {
-        HIPCHK(hipMemsetAsync(c->ws.flag, 0, sizeof(int), s));
-        HIPCHK(hipStreamSynchronize(s));
-        return guard_status(h, "");
-    }
-    return PM_OK;
+    return guard_status(c, c->guard_set, "");
 }
 
 bool sorting_on(const pm_ctx *c) { return c->nkeys > 0 && !(c->cfg.flags & PM_FLAG_NO_SORT); }
@@ -302,10 +300,10 @@ pm_status readout_step(pm_ctx *c, float *x, float *p, int64_t ps_f, int64_t comp
     if (c->nkeys > 0)
         LAUNCH(pm::K_READOUT_KD,
                pm::launch_readout_kd_index_tiles(c->ws.xs, c->ws.ids_tmp, c->P, c->ws.koff, c->ws.f, nhp, ps_f, comp, c->n,
-                                                 (float)kick, (float)drift, x, p, c->ws.flag, s));
+                                                 (float)kick, (float)drift, x, p, guard(c, pm::FLAG_NAN), s));
     else
         LAUNCH(pm::K_READOUT_KD, pm::launch_readout_kick_drift(x, p, c->P, c->ws.f, nhp, ps_f, comp, c->n, (float)kick,
-                                                               (float)drift, c->ws.flag, s));
+                                                               (float)drift, guard(c, pm::FLAG_NAN), s));
     return PM_OK;
 }
 
@@ -323,6 +321,24 @@ pm_status paint_atomic(pm_ctx *c, const float *x, int lo, int hi, int64_t *mesh,
     return PM_OK;
 }
 
+// Reads a verification that has ended.  Stale: the words are cleared, with what
+// a paint of the stale records may have set; the counts left for the next step
+// are still the zeros that the scan wrote.
+pm_status settle_sort(pm_ctx *c, hipStream_t s, bool *stale)
+{
+    c->verify_pending = false;
+    volatile int *w = c->guards;
+    *stale = w[pm::FLAG_STALE];
+    if (!*stale) return PM_OK;
+    HIPCHK(hipStreamSynchronize(s));
+    w[pm::FLAG_STALE] = 0;
+    *guard(c, pm::FLAG_RECORDS) = 0;
+    LAUNCH(pm::K_FILL, pm::launch_fill_i32(c->ws.flag + pm::FLAG_STALE, 1, s));
+    c->counts_ready = false;
+    c->cnt_next_zero = true;
+    return PM_OK;
+}
+
 // Counting sort of (x, p, tags, ids) by tile key into the workspace records
 // xs (position and tag), ps, ids_tmp and the key offsets koff.  p may be
 // NULL.  The tag array itself keeps the caller's order until a readout
@@ -335,10 +351,10 @@ pm_status paint_atomic(pm_ctx *c, const float *x, int lo, int hi, int64_t *mesh,
 // x in between, the check fails and the sort is redone from a fresh count
 // (the scatter never writes past the record arrays).  The check waits for the
 // stream, so it is used only when the end-of-call guards wait anyway.
-// With `defer`, a verification of taken-over counts is left in flight (the
-// flag word on its way to pinned host memory) and finish_sort settles it: the
-// caller may queue work that writes only the workspace in between, which is
-// redone when the counts were stale.
+// With `defer`, a verification of taken-over counts is left in flight and
+// finish_sort settles it: the caller may queue work in between that writes
+// only the workspace, or that does nothing while ws.flag[FLAG_STALE] is set;
+// it is redone when the counts were stale.
 pm_status tile_sort(pm_ctx *c, const float *x, const float *p, hipStream_t s, bool defer = false)
 {
     const int64_t K = c->nkeys;
@@ -350,21 +366,17 @@ pm_status tile_sort(pm_ctx *c, const float *x, const float *p, hipStream_t s, bo
         LAUNCH(pm::K_SORT_SCATTER,
                pm::launch_sort_scatter(x, p, tin, c->P, c->nseg, c->ws.seg_off, c->n, c->ws.cnt, c->ws.xs,
                                        p ? c->ws.ps : nullptr, c->ids, c->ids ? c->ws.ids_tmp : nullptr, s));
-        LAUNCH(pm::K_SORT_VERIFY, pm::launch_sort_verify(c->ws.cnt, c->ws.koff, K, c->ws.flag, s));
+        LAUNCH(pm::K_SORT_VERIFY, pm::launch_sort_verify(c->ws.cnt, c->ws.koff, K, c->ws.flag + pm::FLAG_STALE,
+                                                         c->guards + pm::FLAG_STALE, s));
+        c->verify_pending = true;
         if (defer) {
-            HIPCHK(hipMemcpyAsync(c->verify_host, c->ws.flag, sizeof(int), hipMemcpyDeviceToHost, s));
-            HIPCHK(hipEventRecord(c->verify_ev, s));
-            c->verify_pending = true;
+            if (c->cfg.flags & PM_FLAG_DEFER_GUARDS) HIPCHK(hipEventRecord(c->verify_ev, s));
             return PM_OK;
         }
-        int h = 0;
-        HIPCHK(hipMemcpyAsync(&h, c->ws.flag, sizeof(int), hipMemcpyDeviceToHost, s));
         HIPCHK(hipStreamSynchronize(s));
-        if (!(h & pm::FLAG_STALE)) return PM_OK;
-        h &= ~pm::FLAG_STALE;
-        HIPCHK(hipMemcpyAsync(c->ws.flag, &h, sizeof(int), hipMemcpyHostToDevice, s));
-        HIPCHK(hipStreamSynchronize(s));
-        c->counts_ready = false;
+        bool stale;
+        pm_status st = settle_sort(c, s, &stale);
+        if (st != PM_OK || !stale) return st;
     }
     LAUNCH(pm::K_FILL, pm::launch_fill_i32(c->ws.cnt, K + 1, s));
     LAUNCH(pm::K_SORT_COUNT, pm::launch_sort_count(x, c->P, c->n, c->ws.cnt, s));
@@ -376,25 +388,68 @@ pm_status tile_sort(pm_ctx *c, const float *x, const float *p, hipStream_t s, bo
     return PM_OK;
 }
 
-// Settles a deferred verification.  Stale counts: the stale bit is cleared
-// (with any guard bit that the work queued on the stale sort set) and the
-// particles are sorted again from a fresh count; *redo tells the caller to
-// queue that work again.  The flag value restored is the one read at the
-// verification, so guard bits from before it survive.
+// Settles a deferred verification: with deferred guards a wait for its own end,
+// else for the stream, which the call then ends with anyway.  Stale counts: the
+// particles are sorted again from a fresh count and *redo tells the caller to
+// queue its work again.
 pm_status finish_sort(pm_ctx *c, const float *x, const float *p, hipStream_t s, bool *redo)
 {
     *redo = false;
     if (!c->verify_pending) return PM_OK;
-    c->verify_pending = false;
-    HIPCHK(hipEventSynchronize(c->verify_ev));
-    int h = *c->verify_host;
-    if (!(h & pm::FLAG_STALE)) return PM_OK;
-    h &= ~pm::FLAG_STALE;
-    HIPCHK(hipMemcpyAsync(c->ws.flag, &h, sizeof(int), hipMemcpyHostToDevice, s));
-    HIPCHK(hipStreamSynchronize(s));
-    c->counts_ready = false;
-    *redo = true;
-    return tile_sort(c, x, p, s);
+    if (c->cfg.flags & PM_FLAG_DEFER_GUARDS)
+        HIPCHK(hipEventSynchronize(c->verify_ev));
+    else
+        HIPCHK(hipStreamSynchronize(s));
+    pm_status st = settle_sort(c, s, redo);
+    return st == PM_OK && *redo ? tile_sort(c, x, p, s) : st;
+}
+
+// One sorted step: sort by tile, paint tile by tile, solve, read out tile by
+// tile into the caller's arrays, which then hold the particles in sorted order.
+// The tile paint stores each cell's exact int64 sum as its float32 density
+// contrast, the value the transform would form from it; solve_delta queues the
+// solve of that to the three force meshes (row stride half_pad(N) complex,
+// planes `plane` complex apart).  Everything is queued before a check of
+// taken-over counts is settled: paint and solve write only the workspace and the
+// readout leaves the particles alone if the counts were stale, so the host waits
+// once, at the end of the call (eleven 64^3 steps: 1149 us with two waits and two
+// copies of the flags, 1018 us so).  Without that wait (deferred guards) the
+// check is settled before the readout is queued.
+template <class Solve>
+pm_status sorted_step(pm_ctx *c, float *x, float *p, double kick, double drift, int64_t plane, hipStream_t s,
+                      Solve solve_delta)
+{
+    const int64_t n = c->n, nhp = pm::half_pad(c->n);
+    const bool deferred = c->cfg.flags & PM_FLAG_DEFER_GUARDS;
+    float *delta = reinterpret_cast<float *>(c->ws.q);
+    int *cnt_next = (c->cfg.flags & PM_FLAG_NO_GUARDS) ? nullptr : c->ws.cnt_next;
+    pm_status st = tile_sort(c, x, p, s, true);
+    if (st != PM_OK) return st;
+    for (bool redo = true; redo;) {
+        LAUNCH(pm::K_PAINT, pm::launch_paint_tiles_delta(c->ws.xs, c->ws.koff, c->ws.quanta, c->nseg, 0, c->nseg, c->n,
+                                                         ldexp(1.0, -c->cfg.shift), -1.0, delta,
+                                                         guard(c, pm::FLAG_RECORDS), s));
+        st = solve_delta(delta);
+        if (st != PM_OK) return st;
+        if (deferred) {
+            st = finish_sort(c, x, p, s, &redo);
+            if (st != PM_OK) return st;
+            if (redo) continue;
+        }
+        if (cnt_next && !c->cnt_next_zero) LAUNCH(pm::K_FILL, pm::launch_fill_i32(cnt_next, c->nkeys + 1, s));
+        if (cnt_next) c->cnt_next_zero = false;
+        LAUNCH(pm::K_READOUT_KD,
+               pm::launch_readout_kd_tiles(c->ws.xs, c->ws.ps, c->P, c->ws.koff, c->ws.f, nhp, plane, n * plane, c->n,
+                                           (float)kick, (float)drift, x, p, c->ws.tags, c->ws.ids_tmp, c->ids,
+                                           guard(c, pm::FLAG_NAN), cnt_next,
+                                           c->verify_pending ? c->ws.flag + pm::FLAG_STALE : nullptr, s));
+        st = finish_sort(c, x, p, s, &redo);
+        if (st != PM_OK) return st;
+    }
+    c->permuted = true;
+    c->counts_ready = cnt_next != nullptr;
+    c->counts_x = x;
+    return check_guards(c, s);
 }
 
 // Position records (with segment tags) of x, and with v the records of a
@@ -433,7 +488,7 @@ pm_status paint_density(pm_ctx *c, const float *x, const float *v, bool index, h
     if (st != PM_OK) return st;
     float *d = reinterpret_cast<float *>(c->ws.q);
     LAUNCH(pm::K_PAINT, pm::launch_paint_tiles_delta(c->ws.xs, c->ws.koff, c->ws.quanta, c->nseg, 0, c->nseg, c->n,
-                                                     ldexp(1.0, -c->cfg.shift), -1.0, d, c->ws.flag, s));
+                                                     ldexp(1.0, -c->cfg.shift), -1.0, d, guard(c, pm::FLAG_OVERFLOW), s));
     *delta = d;
     return PM_OK;
 }
@@ -491,7 +546,7 @@ pm_status solve(pm_ctx *c, const int64_t *src, hipStream_t s, const float *delta
             LAUNCH(pm::K_R2C_X0, pm::launch_r2c_x0_f32(lg, delta, n, F, (int)nhp, plane, c->ws.tw, s));
         else
             LAUNCH(pm::K_R2C_X0,
-                   pm::launch_r2c_x0(lg, src, F, (int)nhp, plane, scale, -1.0, c->ws.tw, c->ws.flag, s));
+                   pm::launch_r2c_x0(lg, src, F, (int)nhp, plane, scale, -1.0, c->ws.tw, guard(c, pm::FLAG_OVERFLOW), s));
         LAUNCH(pm::K_COLS_FWD, pm::launch_cols(lg, false, F, nhp, plane, n, ncb, c->ws.tw, s));
         LAUNCH(pm::K_X0_GREEN, pm::launch_x0_green(lg, F, F, F + cs, plane, (int)nhp, coef, c->ws.tw, s));
         return force_rows(c, plane, s);
@@ -501,7 +556,8 @@ pm_status solve(pm_ctx *c, const int64_t *src, hipStream_t s, const float *delta
     if (delta)
         LAUNCH(pm::K_R2C, pm::launch_r2c_rows_f32(lg, delta, n, F, nhp, n2, c->ws.tw, s));
     else
-        LAUNCH(pm::K_R2C, pm::launch_r2c_rows_i64(lg, src, n, F, nhp, n2, scale, -1.0, c->ws.tw, c->ws.flag, s));
+        LAUNCH(pm::K_R2C, pm::launch_r2c_rows_i64(lg, src, n, F, nhp, n2, scale, -1.0, c->ws.tw,
+                                                  guard(c, pm::FLAG_OVERFLOW), s));
     // axis 1
     LAUNCH(pm::K_COLS_FWD, pm::launch_cols(lg, false, F, nhp, n * nhp, n, ncb, c->ws.tw, s));
     // axis 0 forward, gradient of the inverse Laplacian, axis 0 inverses (in place on F0)
@@ -666,7 +722,8 @@ pm_status learned_solve(pm_ctx *c, const float *th, double a, bool keep, hipStre
         if (delta)
             LAUNCH(pm::K_R2C, pm::launch_r2c_rows_f32(lg, delta, n, F, nhp, n2, c->ws.tw, s));
         else
-            LAUNCH(pm::K_R2C, pm::launch_r2c_rows_i64(lg, c->ws.q, n, F, nhp, n2, qs, -1.0, c->ws.tw, c->ws.flag, s));
+            LAUNCH(pm::K_R2C, pm::launch_r2c_rows_i64(lg, c->ws.q, n, F, nhp, n2, qs, -1.0, c->ws.tw,
+                                                      guard(c, pm::FLAG_OVERFLOW), s));
         LAUNCH(pm::K_COLS_FWD, pm::launch_cols(lg, false, F, nhp, n * nhp, n, ncb, c->ws.tw, s));
         LAUNCH(pm::K_COLS_FWD, pm::launch_cols(lg, false, F, n * nhp, nhp, n, ncb, c->ws.tw, s));
     }
@@ -696,7 +753,8 @@ pm_status learned_solve(pm_ctx *c, const float *th, double a, bool keep, hipStre
         if (delta)
             LAUNCH(pm::K_R2C_X0, pm::launch_r2c_x0_f32(lg, delta, n, F, (int)nhp, plane, c->ws.tw, s));
         else
-            LAUNCH(pm::K_R2C_X0, pm::launch_r2c_x0(lg, c->ws.q, F, (int)nhp, plane, qs, -1.0, c->ws.tw, c->ws.flag, s));
+            LAUNCH(pm::K_R2C_X0, pm::launch_r2c_x0(lg, c->ws.q, F, (int)nhp, plane, qs, -1.0, c->ws.tw,
+                                                   guard(c, pm::FLAG_OVERFLOW), s));
         LAUNCH(pm::K_COLS_FWD, pm::launch_cols(lg, false, F, nhp, n * nhp, n, ncb, c->ws.tw, s));
         float *F2r = reinterpret_cast<float *>(F + 2 * cs);
         LAUNCH(pm::K_NET, pm::launch_cnn_inf(c->ws.q, qs, delta, nullptr, rs, n, th, c->ws.net_wpk, c->ws.net_a2,
@@ -847,13 +905,14 @@ pm_status pm_init(const pm_config *cfg, void *workspace, size_t workspace_bytes,
         delete c;
         return fail(PM_ERR_DEVICE, "address of the static scratch array: %s", hipGetErrorString(e));
     }
-    e = hipHostMalloc(reinterpret_cast<void **>(&c->verify_host), sizeof(int), hipHostMallocDefault);
+    e = hipHostMalloc(reinterpret_cast<void **>(&c->guards), 2 * pm::FLAG_WORDS * sizeof(int),
+                      hipHostMallocMapped | hipHostMallocCoherent);
+    if (e == hipSuccess) std::fill(c->guards, c->guards + 2 * pm::FLAG_WORDS, 0);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&c->verify_ev, hipEventDisableTiming);
-    if (e == hipSuccess) e = hipHostMalloc(reinterpret_cast<void **>(&c->guard_host), 2 * sizeof(int), hipHostMallocDefault);
     for (int k = 0; k < 2 && e == hipSuccess; k++) e = hipEventCreateWithFlags(&c->guard_ev[k], hipEventDisableTiming);
     if (e != hipSuccess) {
         pm_free(c);
-        return fail(PM_ERR_DEVICE, "pinned flag copy: %s", hipGetErrorString(e));
+        return fail(PM_ERR_DEVICE, "pinned guard words: %s", hipGetErrorString(e));
     }
     *out = c;
     return PM_OK;
@@ -863,7 +922,7 @@ void pm_free(pm_ctx *ctx)
 {
     if (!ctx) return;
     for (hipEvent_t e : ctx->ev_pool) (void)hipEventDestroy(e);
-    // a flag copy queued into the pinned words may still be in flight
+    // kernels of the last call may still write the pinned words
     if (ctx->verify_ev) {
         (void)hipEventSynchronize(ctx->verify_ev);
         (void)hipEventDestroy(ctx->verify_ev);
@@ -873,8 +932,7 @@ void pm_free(pm_ctx *ctx)
             (void)hipEventSynchronize(e);
             (void)hipEventDestroy(e);
         }
-    if (ctx->verify_host) (void)hipHostFree(ctx->verify_host);
-    if (ctx->guard_host) (void)hipHostFree(ctx->guard_host);
+    if (ctx->guards) (void)hipHostFree(ctx->guards);
     delete ctx;
 }
 
@@ -1170,35 +1228,9 @@ pm_status pm_step(pm_ctx *c, float *x, float *p, double a_force, double a_kick0,
     if (st != PM_OK) return st;
     hipStream_t s = S(stream);
     const int64_t n = c->n, nhp = pm::half_pad(c->n), fp = pm::force_plane(c->n);
-    if (sorting_on(c)) {
-        // sort by tile, paint tile by tile, solve, read out tile by tile into
-        // the caller's arrays, which then hold the particles in sorted order
-        // the tile paint stores each cell's exact int64 sum as its float32
-        // density contrast, the value the transform would form from it
-        // the paint and the solve write only the workspace, so they are queued
-        // before a deferred check of taken-over counts and redone if stale
-        st = tile_sort(c, x, p, s, true);
-        if (st != PM_OK) return st;
-        float *delta = reinterpret_cast<float *>(c->ws.q);
-        for (bool redo = true; redo;) {
-            LAUNCH(pm::K_PAINT, pm::launch_paint_tiles_delta(c->ws.xs, c->ws.koff, c->ws.quanta, c->nseg, 0, c->nseg, c->n,
-                                                             ldexp(1.0, -c->cfg.shift), -1.0, delta, c->ws.flag, s));
-            st = solve(c, nullptr, s, delta);
-            if (st == PM_OK) st = finish_sort(c, x, p, s, &redo);
-            if (st != PM_OK) return st;
-        }
-        int *cnt_next = (c->cfg.flags & PM_FLAG_NO_GUARDS) ? nullptr : c->ws.cnt_next;
-        if (cnt_next && !c->cnt_next_zero) LAUNCH(pm::K_FILL, pm::launch_fill_i32(cnt_next, c->nkeys + 1, s));
-        if (cnt_next) c->cnt_next_zero = false;
-        LAUNCH(pm::K_READOUT_KD,
-               pm::launch_readout_kd_tiles(c->ws.xs, c->ws.ps, c->P, c->ws.koff, c->ws.f, nhp, fp, n * fp, c->n,
-                                           (float)kick, (float)drift, x, p, c->ws.tags, c->ws.ids_tmp, c->ids,
-                                           c->ws.flag, cnt_next, s));
-        c->permuted = true;
-        c->counts_ready = cnt_next != nullptr;
-        c->counts_x = x;
-        return check_guards(c, s);
-    }
+    if (sorting_on(c))
+        return sorted_step(c, x, p, kick, drift, fp, s,
+                           [&](const float *delta) { return solve(c, nullptr, s, delta); });
     const float *delta;
     st = paint_density(c, x, nullptr, true, s, &delta);
     if (st == PM_OK) st = solve(c, c->ws.q, s, delta);
@@ -1264,13 +1296,14 @@ pm_status pm_power(pm_ctx *c, const float *x, int32_t a_lo, int32_t a_hi, int32_
     auto field = [&](int lo, int hi, float2 *S) -> pm_status {
         if (tiles) {
             LAUNCH(pm::K_PAINT, pm::launch_paint_tiles_delta(c->ws.xs, c->ws.koff, c->ws.quanta, c->nseg, lo, hi, n,
-                                                             scale_of(lo, hi), -1.0, delta, c->ws.flag, s));
+                                                             scale_of(lo, hi), -1.0, delta,
+                                                             guard(c, pm::FLAG_OVERFLOW), s));
             return power_spectrum_field(c, delta, S, s);
         }
         LAUNCH(pm::K_FILL, pm::launch_fill_i64(c->ws.q, M, s));
         pm_status st = paint_atomic(c, x, lo, hi, c->ws.q, s);
         if (st != PM_OK) return st;
-        LAUNCH(pm::K_COPY, pm::launch_q_to_delta(c->ws.q, M, scale_of(lo, hi), delta, s, c->ws.flag));
+        LAUNCH(pm::K_COPY, pm::launch_q_to_delta(c->ws.q, M, scale_of(lo, hi), delta, s, guard(c, pm::FLAG_OVERFLOW)));
         return power_spectrum_field(c, delta, S, s);
     };
     pm_status st = tiles ? tile_records(c, x, nullptr, false, s) : PM_OK;
@@ -1433,31 +1466,9 @@ pm_status pm_learned_step(pm_ctx *c, const float *th, float *x, float *p, double
     if (st != PM_OK) return st;
     hipStream_t s = S(stream);
     const int64_t n = c->n, nhp = pm::half_pad(c->n);
-    if (sorting_on(c)) {
-        // as pm_step: tile sort, tile paint (float32 density contrast),
-        // (learned) solve, tile readout counting the next step's keys
-        st = tile_sort(c, x, p, s, true);
-        if (st != PM_OK) return st;
-        float *delta = reinterpret_cast<float *>(c->ws.q);
-        for (bool redo = true; redo;) {
-            LAUNCH(pm::K_PAINT, pm::launch_paint_tiles_delta(c->ws.xs, c->ws.koff, c->ws.quanta, c->nseg, 0, c->nseg, c->n,
-                                                             ldexp(1.0, -c->cfg.shift), -1.0, delta, c->ws.flag, s));
-            st = learned_solve(c, th, a_force, false, s, delta);
-            if (st == PM_OK) st = finish_sort(c, x, p, s, &redo);
-            if (st != PM_OK) return st;
-        }
-        int *cnt_next = (c->cfg.flags & PM_FLAG_NO_GUARDS) ? nullptr : c->ws.cnt_next;
-        if (cnt_next && !c->cnt_next_zero) LAUNCH(pm::K_FILL, pm::launch_fill_i32(cnt_next, c->nkeys + 1, s));
-        if (cnt_next) c->cnt_next_zero = false;
-        LAUNCH(pm::K_READOUT_KD,
-               pm::launch_readout_kd_tiles(c->ws.xs, c->ws.ps, c->P, c->ws.koff, c->ws.f, nhp, n * nhp, n * n * nhp, c->n,
-                                           (float)kick, (float)drift, x, p, c->ws.tags, c->ws.ids_tmp, c->ids,
-                                           c->ws.flag, cnt_next, s));
-        c->permuted = true;
-        c->counts_ready = cnt_next != nullptr;
-        c->counts_x = x;
-        return check_guards(c, s);
-    }
+    if (sorting_on(c))
+        return sorted_step(c, x, p, kick, drift, n * nhp, s,
+                           [&](const float *delta) { return learned_solve(c, th, a_force, false, s, delta); });
     const float *delta;
     st = paint_density(c, x, nullptr, true, s, &delta);
     if (st == PM_OK) st = learned_solve(c, th, a_force, false, s, delta);

@@ -205,7 +205,7 @@ __global__ __launch_bounds__(PAINT_T) void k_paint_tiles(const float4 *__restric
             bad |= (a[0] < GUARD_MIN_Q) | (a[1] < GUARD_MIN_Q) | (a[2] < GUARD_MIN_Q) | (a[3] < GUARD_MIN_Q);
             *reinterpret_cast<float4 *>(dm + ((int64_t)(ox + l0) * n + (oy + l1)) * n + (oz + l2)) = v;
         }
-        if (bad) atomicOr(flag, FLAG_OVERFLOW);
+        if (bad) raise(flag);
     } else {
         unsigned long long *mesh = static_cast<unsigned long long *>(out);
         for (int i = threadIdx.x; i < TILE * TILE * TILE; i += PAINT_T) {

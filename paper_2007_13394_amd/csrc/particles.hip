@@ -101,7 +101,7 @@ __global__ __launch_bounds__(256) void k_readout_kick_drift(float *x, float *p, 
         x[P + i] = x1;
         x[2 * P + i] = x2;
     }
-    if (bad) atomicOr(flag, FLAG_NAN);
+    if (bad) raise(flag);
 }
 
 constexpr int READOUT_T = 1024, FORCE_H = TILE + 1;
@@ -150,8 +150,10 @@ __global__ __launch_bounds__(READOUT_T) void k_readout_kd_tiles(const float4 *__
                                                                 int64_t fps, int64_t cs, int n, float kick, float drift,
                                                                 float *x, float *p, uint8_t *tags,
                                                                 const uint32_t *__restrict__ ids_tmp,
-                                                                uint32_t *ids, int *flag, int *cnt_next)
+                                                                uint32_t *ids, int *flag, int *cnt_next,
+                                                                const int *stale)
 {
+    if (stale && *stale) return;   // the records do not describe x: nothing is written
     // LDS: the (TILE + 1)^3 cells of the tile and its +1 halo, the three
     // force components of a cell interleaved in one float4
     constexpr int H = FORCE_H, ROWS = H * H, NB = 27 * 8;
@@ -237,7 +239,7 @@ __global__ __launch_bounds__(READOUT_T) void k_readout_kd_tiles(const float4 *__
         if (ids) ids[i] = ids_tmp[i];
         i = inext;
     }
-    if (bad) atomicOr(flag, FLAG_NAN);
+    if (bad) raise(flag);
     if (cnt_next) {
         __syncthreads();
         if (threadIdx.x < NB && hist[threadIdx.x] > 0) {
@@ -376,7 +378,7 @@ __global__ __launch_bounds__(READOUT_T) void k_readout_tiles(const float4 *__res
         i = inext;
     }
     if constexpr (OUT == OUT_KD) {
-        if (bad) atomicOr(o.flag, FLAG_NAN);
+        if (bad) raise(o.flag);
     }
     if constexpr (OUT == OUT_LOSS) {
 #pragma unroll
@@ -659,13 +661,13 @@ hipError_t launch_readout_kick_drift(float *x, float *p, int64_t P, const float2
 hipError_t launch_readout_kd_tiles(const float4 *xs, const Mom3 *ps, int64_t P, const int *koff, const float2 *f,
                                    int64_t rs_f, int64_t ps_f, int64_t comp_stride, int n, float kick, float drift,
                                    float *x, float *p, uint8_t *tags, const uint32_t *ids_tmp, uint32_t *ids, int *flag,
-                                   int *cnt_next, hipStream_t s)
+                                   int *cnt_next, const int *stale, hipStream_t s)
 {
     const int nt = n / TILE;
     if (nt < 2) return hipErrorInvalidValue;
     hipLaunchKernelGGL(k_readout_kd_tiles, dim3((unsigned)(nt * nt * nt)), dim3(READOUT_T), 0, s, xs, ps, P, koff,
                        reinterpret_cast<const float *>(f), 2 * rs_f, 2 * ps_f, 2 * comp_stride, n, kick, drift, x, p, tags,
-                       ids_tmp, ids, flag, cnt_next);
+                       ids_tmp, ids, flag, cnt_next, stale);
     return hipGetLastError();
 }
 

@@ -179,9 +179,18 @@ __device__ __forceinline__ void key_group(bool live, int k, uint64_t &group, int
     }
 }
 
-// Device-side guard bits (workspace flag word).  FLAG_STALE: tile counts
-// taken over from the previous step did not match the positions.
-enum { FLAG_OVERFLOW = 1, FLAG_NAN = 2, FLAG_STALE = 4 };
+// Guard words, one per condition, set to 1 by the kernel that meets it.  With
+// guards they lie in pinned host memory: the host reads them after the wait
+// that ends the call, without a copy (5-10 us each on the stream, of about
+// 100 us for a step on a 64^3 mesh).  A plain store per condition, as atomics
+// on host memory need not be carried out.  FLAG_STALE: tile counts taken over
+// from the previous step did not match the positions.  FLAG_RECORDS: overflow
+// of a paint from records that may be stale; dropped if they are.
+enum { FLAG_OVERFLOW, FLAG_NAN, FLAG_RECORDS, FLAG_STALE, FLAG_WORDS };
+__device__ __forceinline__ void raise(int *word)
+{
+    __hip_atomic_store(word, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
 // A painted cell below this many quanta has wrapped past 2^63.  Cells are
 // sums of positive particle quanta, but a particle's remainder corner (its
 // quantum minus seven rounded corners) can be a few units negative when its
@@ -295,16 +304,17 @@ struct Ctx {
     bool counts_ready = false;
     const float *counts_x = nullptr;
     bool cnt_next_zero = false;   // ws.cnt_next holds zeros (cleared by the scan that took its counts)
-    // a verification of taken-over counts still in flight: the flag word is
-    // copied to pinned verify_host and verify_ev marks the copy's end
+    // pinned guard words, two sets of FLAG_WORDS; a call's kernels write set
+    // guard_set (with PM_FLAG_NO_GUARDS nothing reads them: workspace words)
+    int *guards = nullptr;
+    int guard_set = 0;
+    // a verification of taken-over counts still in flight (verify_ev: its end,
+    // for calls that do not wait for the stream)
     bool verify_pending = false;
-    int *verify_host = nullptr;
     hipEvent_t verify_ev = nullptr;
-    // PM_FLAG_DEFER_GUARDS: the flag word of the last guarded call, on its way
-    // to pinned guard_host[guard_slot] behind guard_ev[guard_slot]
+    // PM_FLAG_DEFER_GUARDS: the last guarded call's words are in the other set
+    // once guard_ev of that set has passed
     bool guard_pending = false;
-    int guard_slot = 0;
-    int *guard_host = nullptr;   // two words
     hipEvent_t guard_ev[2] = {nullptr, nullptr};
     char *static_scratch = nullptr;   // this device's fixed scratch array (pm_paint_static)
     // launch trace
@@ -483,7 +493,8 @@ hipError_t launch_sort_scatter(const float *x, const float *p, const uint8_t *ta
                                const int64_t *seg_off, int n, int *cursor, float4 *xs, Mom3 *ps,
                                const uint32_t *ids_in, uint32_t *ids_out, hipStream_t s);
 // FLAG_STALE unless cursor[k] == koff[k + 1] for every key k < K.
-hipError_t launch_sort_verify(const int *cursor, const int *koff, int64_t K, int *flag, hipStream_t s);
+hipError_t launch_sort_verify(const int *cursor, const int *koff, int64_t K, int *stale, int *host_stale,
+                              hipStream_t s);
 
 // ---- launchers (particles.hip)
 hipError_t launch_fill_i64(int64_t *p, int64_t count, hipStream_t s);
@@ -495,10 +506,11 @@ hipError_t launch_readout_kick_drift(float *x, float *p, int64_t P, const float2
                                      int64_t comp_stride, int n, float kick, float drift, int *flag,
                                      hipStream_t s);
 // cnt_next (optional): counts per sort key of the positions written, added to.
+// stale (optional): a device word that, when set, keeps the kernel from writing.
 hipError_t launch_readout_kd_tiles(const float4 *xs, const Mom3 *ps, int64_t P, const int *koff, const float2 *f,
                                    int64_t rs_f, int64_t ps_f, int64_t comp_stride, int n, float kick, float drift,
                                    float *x, float *p, uint8_t *tags, const uint32_t *ids_tmp, uint32_t *ids, int *flag,
-                                   int *cnt_next, hipStream_t s);
+                                   int *cnt_next, const int *stale, hipStream_t s);
 // The same tile by tile from sorted records (index: each record's particle),
 // for particles that keep the caller's order: acc = F (launch_readout_tiles);
 // kick and drift of the caller's x and p; vals = F - target with red[0] += sum

@@ -384,21 +384,25 @@ __global__ __launch_bounds__(SORT_T) void k_sort_scatter_wg(const float *__restr
 
 // After a scatter from counts computed elsewhere (the previous readout):
 // every key's cursor must have reached the next key's offset, else the
-// counts did not describe x and FLAG_STALE is raised.
+// counts did not describe x and FLAG_STALE is raised, for the kernels queued
+// behind and for the host.
 __global__ __launch_bounds__(256) void k_sort_verify(const int *__restrict__ cursor, const int *__restrict__ koff,
-                                                     int64_t K, int *flag)
+                                                     int64_t K, int *stale, int *host_stale)
 {
     bool bad = false;
     for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < K; k += (int64_t)gridDim.x * blockDim.x)
         bad |= cursor[k] != koff[k + 1];
-    if (__any(bad) && (threadIdx.x & 63) == 0) atomicOr(flag, FLAG_STALE);
+    if (__any(bad) && (threadIdx.x & 63) == 0) {
+        raise(stale);
+        raise(host_stale);
+    }
 }
 
 }  // namespace
 
-hipError_t launch_sort_verify(const int *cursor, const int *koff, int64_t K, int *flag, hipStream_t s)
+hipError_t launch_sort_verify(const int *cursor, const int *koff, int64_t K, int *stale, int *host_stale, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_sort_verify, dim3(grid_for(K, 256, 65536)), dim3(256), 0, s, cursor, koff, K, flag);
+    hipLaunchKernelGGL(k_sort_verify, dim3(grid_for(K, 256, 65536)), dim3(256), 0, s, cursor, koff, K, stale, host_stale);
     return hipGetLastError();
 }
 
