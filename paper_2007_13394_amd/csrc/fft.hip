@@ -1016,7 +1016,7 @@ __global__ __launch_bounds__(1 << (LOGN - 1)) void k_r2c_x0(const SRC *src, int6
 template <int LOGN>
 __global__ __launch_bounds__(1 << (LOGN - 1)) void k_c2r_x0(const float2 *src, float *dst, int64_t dst_stride,
                                                             int64_t dst_plane, int nhp, int64_t plane,
-                                                            const float2 *__restrict__ tw, int64_t fs)
+                                                            const float2 *__restrict__ tw, int64_t fs, int j0)
 {
     constexpr int N = 1 << LOGN, L = N / 2, T = L, N2 = N / 16, RB = 16, LS = L, PS = SWZ_ROWS;
     src += blockIdx.y * fs;         // fields fs complex apart
@@ -1025,7 +1025,7 @@ __global__ __launch_bounds__(1 << (LOGN - 1)) void k_c2r_x0(const float2 *src, f
     __shared__ float2 twl[L];   // the row stages' twiddles (one per thread)
     __shared__ float2 xnq[RB];  // the Nyquist column X_L of the 16 rows
     const int tile = xcd_tile(blockIdx.x, gridDim.x);
-    const int j1 = tile / N, x1 = tile % N;
+    const int j1 = j0 + tile / N, x1 = tile % N;
     const int tid = threadIdx.x;
     const float2 *twN = tw + N;
     const float2 *s0 = src + (int64_t)j1 * plane + (int64_t)x1 * nhp;
@@ -1314,17 +1314,18 @@ hipError_t launch_r2c_x0_f32(int logn, const float *src, int64_t src_rs, float2 
 }
 
 hipError_t launch_c2r_x0(int logn, const float2 *src, float *dst, int64_t dst_stride, int64_t dst_plane, int nhp,
-                         int64_t plane, const float2 *tw, hipStream_t s, int nf, int64_t fs)
+                         int64_t plane, const float2 *tw, hipStream_t s, int nf, int64_t fs, int j0, int nj)
 {
-    if (logn < 8 || logn > 11 || nf < 1 || plane < ((int64_t)nhp << logn)) return hipErrorInvalidValue;
+    if (nj == 0) nj = (1 << logn) / 16;
+    if (logn < 8 || logn > 11 || nf < 1 || j0 < 0 || nj < 1 || j0 + nj > (1 << logn) / 16 || plane < ((int64_t)nhp << logn)) return hipErrorInvalidValue;
     // the rows are stored 16 bytes at a time
     if ((reinterpret_cast<uintptr_t>(dst) & 15) != 0 || dst_stride % 4 != 0 || dst_plane % 4 != 0 ||
         (nf > 1 && fs % 2 != 0) || dst_plane < (dst_stride << logn))
         return hipErrorInvalidValue;
-    const unsigned nb = (unsigned)((1 << logn) / 16) << logn;
+    const unsigned nb = (unsigned)nj << logn;
 #define C2RX(LG)                                                                                     \
     hipLaunchKernelGGL((k_c2r_x0<LG>), dim3(nb, (unsigned)nf), dim3(1 << (LG - 1)), 0, s, src, dst, dst_stride, \
-                       dst_plane, nhp, plane, tw, fs)
+                       dst_plane, nhp, plane, tw, fs, j0)
     switch (logn) {
     case 8: C2RX(8); break;
     case 9: C2RX(9); break;

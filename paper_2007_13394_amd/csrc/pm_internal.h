@@ -400,7 +400,8 @@ hipError_t launch_x0_learned(int logn, const float2 *srcd, const float2 *srcc, f
 hipError_t launch_x0_power(int logn, const float2 *srca, const float2 *srcb, int64_t plane, int nhp, int nbins,
                            int compensate, double norm, double *partial, int blocks, const float2 *tw, hipStream_t s);
 hipError_t launch_c2r_x0(int logn, const float2 *src, float *dst, int64_t dst_stride, int64_t dst_plane, int nhp,
-                         int64_t plane, const float2 *tw, hipStream_t s, int nf = 1, int64_t fs = 0);
+                         int64_t plane, const float2 *tw, hipStream_t s, int nf = 1, int64_t fs = 0,
+                         int j0 = 0, int nj = 0);
 
 hipError_t launch_ic_adj_mult(const float2 *G, int64_t nhp, int64_t fs, int n, const IcTables *ic, float2 *acc,
                               bool accumulate, hipStream_t s);
