@@ -35,6 +35,13 @@ __device__ __forceinline__ float2 cmul(float2 a, float2 b)
 {
     return make_float2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
 }
+// a b with its roundings spelled out: which product of the imaginary part is
+// fused is otherwise the compiler's choice.
+template <bool X>
+__device__ __forceinline__ float2 cmul_as(float2 a, float2 b)
+{
+    return make_float2(fmaf(a.x, b.x, -(a.y * b.y)), X ? fmaf(b.x, a.y, b.y * a.x) : fmaf(b.y, a.x, b.x * a.y));
+}
 __device__ __forceinline__ float2 cconj(float2 a) { return make_float2(a.x, -a.y); }
 
 constexpr int ilog2c(int v) { return v <= 1 ? 0 : 1 + ilog2c(v / 2); }
@@ -135,9 +142,11 @@ constexpr int padded(int n, int ps) { return ps > 0 && ps != SWZ_ROWS ? n + (n >
 // One Stockham stage of radix R over NC independent transforms of length L
 // held in LDS: element (c, l) at buf[c * SC + l * SL].  NS = product of the
 // radices already applied.  All butterflies of a thread are read before the
-// barrier and written after it, so the stage runs in place.
-template <int L, int R, int NS, int NC, int T, bool COLMAJ, int SL, int SC, bool INV, int PS = 0>
-__device__ __forceinline__ void stage(float2 *buf, const float2 *__restrict__ twL)
+// barrier and written after it, so the stage runs in place.  CYC > 0: the
+// transforms are rows c0 + c of cycles of CYC rows, whose twiddle products are
+// rounded one way in the first 256 R / L rows and the other way in the rest.
+template <int L, int R, int NS, int NC, int T, bool COLMAJ, int SL, int SC, bool INV, int PS = 0, int CYC = 0>
+__device__ __forceinline__ void stage(float2 *buf, const float2 *__restrict__ twL, int c0 = 0)
 {
     constexpr int NB = NC * (L / R);
     constexpr int PER = (NB + T - 1) / T;
@@ -164,7 +173,10 @@ __device__ __forceinline__ void stage(float2 *buf, const float2 *__restrict__ tw
                 for (int r = 1; r < R; r++) {
                     float2 w = twL[r * k * (L / (NS * R))];
                     if (INV) w.y = -w.y;
-                    v[b][r] = cmul(v[b][r], w);
+                    if constexpr (CYC > 0)
+                        v[b][r] = c0 + c < 256 / (L / R) ? cmul_as<true>(v[b][r], w) : cmul_as<false>(v[b][r], w);
+                    else
+                        v[b][r] = cmul(v[b][r], w);
                 }
             }
             Dft<R, INV>::run(v[b]);
@@ -184,24 +196,32 @@ __device__ __forceinline__ void stage(float2 *buf, const float2 *__restrict__ tw
 }
 
 // Full transform: stages of at most 2^MAXB, bits split as evenly as possible.
-template <int L, int NS, int NC, int T, bool COLMAJ, int SL, int SC, bool INV, int MAXB, int PS = 0>
-__device__ __forceinline__ void fft_from(float2 *buf, const float2 *__restrict__ twL)
+template <int L, int NS, int NC, int T, bool COLMAJ, int SL, int SC, bool INV, int MAXB, int PS = 0, int CYC = 0>
+__device__ __forceinline__ void fft_from(float2 *buf, const float2 *__restrict__ twL, int c0 = 0)
 {
     if constexpr (NS < L) {
         constexpr int rem = ilog2c(L / NS);
         constexpr int nst = (rem + MAXB - 1) / MAXB;
         constexpr int bits = (rem + nst - 1) / nst;
         constexpr int R = 1 << bits;
-        stage<L, R, NS, NC, T, COLMAJ, SL, SC, INV, PS>(buf, twL);
-        fft_from<L, NS * R, NC, T, COLMAJ, SL, SC, INV, MAXB, PS>(buf, twL);
+        stage<L, R, NS, NC, T, COLMAJ, SL, SC, INV, PS, CYC>(buf, twL, c0);
+        fft_from<L, NS * R, NC, T, COLMAJ, SL, SC, INV, MAXB, PS, CYC>(buf, twL, c0);
     }
 }
 
+// Rows: E complex elements per workgroup and 8 or 16 per thread.  Small meshes
+// have few rows, and a launch is done when its slowest chain of loads, stages
+// and stores is: 512 elements on one wavefront keep 256 workgroups on a 64^3
+// mesh.  (4096 on four wavefronts, as from 256^3 on, leave it 32: 8.2 us for a
+// mesh of rows forward and 7.9 us for three back, now 3.7 and 4.9.)
 template <int LOGN>
 struct RowCfg {
     static constexpr int N = 1 << LOGN, L = N / 2;
-    static constexpr int RB = (8192 / N) < (N * N) ? (8192 / N) : (N * N);
-    static constexpr int T = 256;
+    static constexpr int E = LOGN <= 6 ? 512 : LOGN == 7 ? 1024 : 4096;
+    static constexpr int RB = E / L < N * N ? E / L : N * N;
+    static constexpr int T = E / 8 < 256 ? E / 8 : 256;
+    // one pad slot per first radix: a stage's strided writes meet no bank twice
+    static constexpr int PS = ilog2c(L) <= 4 ? ilog2c(L) : (ilog2c(L) + (ilog2c(L) + 3) / 4 - 1) / ((ilog2c(L) + 3) / 4);
 };
 
 template <int LOGN, int WW = TILE_W>
@@ -228,19 +248,26 @@ constexpr int AX0_MAXB = 3;
 
 // ---------------------------------------------------------------- rows
 template <int LOGN, typename SRC>
-__global__ __launch_bounds__(256) void k_r2c_rows(const SRC *src, int64_t src_stride,
-                                                  float2 *dst, int64_t dst_stride, double scale,
-                                                  double offset, const float2 *__restrict__ tw, int *flag)
+__global__ __launch_bounds__(RowCfg<LOGN>::T) void k_r2c_rows(const SRC *src, int64_t src_stride,
+                                                              float2 *dst, int64_t dst_stride, double scale,
+                                                              double offset, const float2 *__restrict__ tw, int *flag)
 {
     using C = RowCfg<LOGN>;
-    constexpr int N = C::N, L = C::L, RB = C::RB, T = C::T;
-    __shared__ float2 buf[RB * L];
+    constexpr int N = C::N, L = C::L, RB = C::RB, T = C::T, PS = C::PS, PER = RB * L / T;
+    constexpr int NW = L > T ? L / T : 1;   // columns per thread
+    static_assert(RB * L % T == 0 && (L % T == 0 || T % L == 0), "whole rounds");
+    __shared__ float2 buf[padded(RB * L, PS)];
+    __shared__ float2 twl[L];   // the stages' twiddles
     const int64_t row0 = (int64_t)blockIdx.x * RB;
     const int tid = threadIdx.x;
+    for (int m = tid; m < L; m += T) twl[m] = tw[L + m];
+    float2 w[NW];   // the split's, of the thread's columns
+#pragma unroll
+    for (int i = 0; i < NW; i++) w[i] = tw[N + (tid + i * T) % L];
     bool bad = false;
-#pragma unroll 8
-    for (int e = tid; e < RB * L; e += T) {
-        const int r = e / L, m = e % L;
+#pragma unroll
+    for (int i = 0; i < PER; i++) {
+        const int e = tid + i * T, r = e / L, m = e % L;
         const SRC *s = src + (row0 + r) * src_stride + 2 * m;
         float a, b;
         if constexpr (std::is_same<SRC, int64_t>::value) {
@@ -253,57 +280,76 @@ __global__ __launch_bounds__(256) void k_r2c_rows(const SRC *src, int64_t src_st
             a = q.x;
             b = q.y;
         }
-        buf[e] = make_float2(a, b);
+        buf[pad<PS>(e)] = make_float2(a, b);
     }
     if (bad) raise(flag);
     __syncthreads();
-    fft_from<L, 1, RB, T, false, 1, L, false, 4>(buf, tw + L);
+    // the roundings of workgroups of 8192 / N rows: a run's particles stay the same bits
+    constexpr int CYC = 8192 / N < N * N ? 8192 / N : N * N;
+    fft_from<L, 1, RB, T, false, 1, L, false, 4, PS, CYC>(buf, twl, (int)(row0 % CYC));
     // X_k = (Z_k + conj Z_{L-k}) / 2 - i w^k (Z_k - conj Z_{L-k}) / 2, w = exp(-2 pi i / N)
-    for (int e = tid; e < RB * (L + 1); e += T) {
-        const int r = e / (L + 1), k = e % (L + 1);
-        const float2 zk = buf[r * L + (k & (L - 1))];
-        const float2 zc = cconj(buf[r * L + ((L - k) & (L - 1))]);
-        const float2 w = tw[N + k];
-        const float2 sum = cadd(zk, zc), t = cmul(w, csub(zk, zc));
+#pragma unroll
+    for (int i = 0; i < PER; i++) {
+        const int e = tid + i * T, r = e / L, k = e % L;
+        const float2 zk = buf[pad<PS>(e)];
+        const float2 zc = cconj(buf[pad<PS>(r * L + ((L - k) & (L - 1)))]);
+        const float2 sum = cadd(zk, zc), t = cmul_as<true>(csub(zk, zc), w[i % NW]);
         dst[(row0 + r) * dst_stride + k] = make_float2(0.5f * (sum.x + t.y), 0.5f * (sum.y - t.x));
     }
-    constexpr int PADC = (int)half_cols(N) - (L + 1);   // the last column tile's unused columns
-    for (int e = tid; e < RB * PADC; e += T) {
-        const int r = e / PADC, k = L + 1 + e % PADC;
-        dst[(row0 + r) * dst_stride + k] = make_float2(0.f, 0.f);
+    // k = L, from Z_0, and the last column tile's unused columns
+    constexpr int TAIL = (int)half_cols(N) - L;
+    for (int e = tid; e < RB * TAIL; e += T) {
+        const int r = e / TAIL, k = L + e % TAIL;
+        float2 v = make_float2(0.f, 0.f);
+        if (k == L) {
+            const float2 zk = buf[pad<PS>(r * L)], zc = cconj(zk);
+            const float2 sum = cadd(zk, zc), t = cmul_as<true>(csub(zk, zc), tw[N + L]);
+            v = make_float2(0.5f * (sum.x + t.y), 0.5f * (sum.y - t.x));
+        }
+        dst[(row0 + r) * dst_stride + k] = v;
     }
 }
 
 template <int LOGN>
-__global__ __launch_bounds__(256) void k_c2r_rows(const float2 *src, int64_t src_stride, float *dst,
-                                                  int64_t dst_stride, const float2 *__restrict__ tw)
+__global__ __launch_bounds__(RowCfg<LOGN>::T) void k_c2r_rows(const float2 *src, int64_t src_stride, float *dst,
+                                                              int64_t dst_stride, const float2 *__restrict__ tw)
 {
     using C = RowCfg<LOGN>;
-    constexpr int N = C::N, L = C::L, RB = C::RB, T = C::T, LS = L + 1;
-    __shared__ float2 buf[RB * LS];
+    constexpr int N = C::N, L = C::L, RB = C::RB, T = C::T, PS = C::PS, PER = RB * L / T, HL = L / 2;
+    static_assert(RB <= T && RB * L % T == 0, "one row end per thread");
+    __shared__ float2 buf[padded(RB * L, PS)];
+    __shared__ float2 xnq[RB];   // the Nyquist column X_L
+    __shared__ float2 twl[L];    // the stages' twiddles
     const int64_t row0 = (int64_t)blockIdx.x * RB;
     const int tid = threadIdx.x;
-#pragma unroll 8
-    for (int e = tid; e < RB * LS; e += T) {
-        const int r = e / LS, k = e % LS;
-        buf[e] = src[(row0 + r) * src_stride + k];
+    for (int m = tid; m < L; m += T) twl[m] = tw[L + m];
+#pragma unroll
+    for (int i = 0; i < PER; i++) {
+        const int e = tid + i * T, r = e / L, k = e % L;
+        buf[pad<PS>(e)] = src[(row0 + r) * src_stride + k];
     }
+    if (tid < RB) xnq[tid] = src[(row0 + tid) * src_stride + L];
     __syncthreads();
     // Z_k = A + i B, A = X_k + conj X_{L-k}, B = (X_k - conj X_{L-k}) exp(+2 pi i k / N);
-    // Z_{L-k} = conj A + i conj B.
-    for (int e = tid; e < RB * (L / 2 + 1); e += T) {
-        const int r = e / (L / 2 + 1), k = e % (L / 2 + 1);
-        const float2 X = buf[r * LS + k], Y = cconj(buf[r * LS + L - k]);
+    // Z_{L-k} = conj A + i conj B; k = 0 apart (no twiddle)
+    for (int e = tid; e < RB * HL; e += T) {
+        const int r = e / HL, k = 1 + e % HL;
+        const float2 X = buf[pad<PS>(r * L + k)], Y = cconj(buf[pad<PS>(r * L + L - k)]);
         const float2 A = cadd(X, Y), B = cmul(cconj(tw[N + k]), csub(X, Y));
-        buf[r * LS + k] = make_float2(A.x - B.y, A.y + B.x);
-        if (k != 0 && k != L / 2) buf[r * LS + L - k] = make_float2(A.x + B.y, B.x - A.y);
+        buf[pad<PS>(r * L + k)] = make_float2(A.x - B.y, A.y + B.x);
+        if (k != HL) buf[pad<PS>(r * L + L - k)] = make_float2(A.x + B.y, B.x - A.y);
+    }
+    if (tid < RB) {
+        const float2 X = buf[pad<PS>(tid * L)], Y = cconj(xnq[tid]);
+        const float2 A = cadd(X, Y), B = csub(X, Y);
+        buf[pad<PS>(tid * L)] = make_float2(A.x - B.y, A.y + B.x);
     }
     __syncthreads();
-    fft_from<L, 1, RB, T, false, 1, LS, true, 4>(buf, tw + L);
-#pragma unroll 8
-    for (int e = tid; e < RB * L; e += T) {
-        const int r = e / L, m = e % L;
-        *reinterpret_cast<float2 *>(dst + (row0 + r) * dst_stride + 2 * m) = buf[r * LS + m];
+    fft_from<L, 1, RB, T, false, 1, L, true, 4, PS>(buf, twl);
+#pragma unroll
+    for (int i = 0; i < PER; i++) {
+        const int e = tid + i * T, r = e / L, m = e % L;
+        *reinterpret_cast<float2 *>(dst + (row0 + r) * dst_stride + 2 * m) = buf[pad<PS>(e)];
     }
 }
 
@@ -1112,7 +1158,7 @@ hipError_t launch_r2c_rows_i64(int logn, const int64_t *src, int64_t src_stride,
 #define R2C_I64(LG)                                                                                  \
     {                                                                                                \
         const int64_t nb = nrows / RowCfg<LG>::RB;                                                   \
-        hipLaunchKernelGGL((k_r2c_rows<LG, int64_t>), dim3((unsigned)nb), dim3(256), 0, s, src,      \
+        hipLaunchKernelGGL((k_r2c_rows<LG, int64_t>), dim3((unsigned)nb), dim3(RowCfg<LG>::T), 0, s, src,      \
                            src_stride, dst, dst_stride, scale, offset, tw, flag);                   \
     }
     PM_DISPATCH_LOGN(logn, R2C_I64)
@@ -1125,7 +1171,7 @@ hipError_t launch_r2c_rows_f32(int logn, const float *src, int64_t src_stride, f
 #define R2C_F32(LG)                                                                                  \
     {                                                                                                \
         const int64_t nb = nrows / RowCfg<LG>::RB;                                                   \
-        hipLaunchKernelGGL((k_r2c_rows<LG, float>), dim3((unsigned)nb), dim3(256), 0, s, src,        \
+        hipLaunchKernelGGL((k_r2c_rows<LG, float>), dim3((unsigned)nb), dim3(RowCfg<LG>::T), 0, s, src,        \
                            src_stride, dst, dst_stride, 1.0, 0.0, tw, nullptr);                     \
     }
     PM_DISPATCH_LOGN(logn, R2C_F32)
@@ -1138,7 +1184,7 @@ hipError_t launch_c2r_rows(int logn, const float2 *src, int64_t src_stride, floa
 #define C2R(LG)                                                                                      \
     {                                                                                                \
         const int64_t nb = nrows / RowCfg<LG>::RB;                                                   \
-        hipLaunchKernelGGL((k_c2r_rows<LG>), dim3((unsigned)nb), dim3(256), 0, s, src, src_stride,   \
+        hipLaunchKernelGGL((k_c2r_rows<LG>), dim3((unsigned)nb), dim3(RowCfg<LG>::T), 0, s, src, src_stride,   \
                            dst, dst_stride, tw);                                                     \
     }
     PM_DISPATCH_LOGN(logn, C2R)
