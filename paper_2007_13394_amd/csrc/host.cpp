@@ -502,7 +502,9 @@ pm_status paint_density(pm_ctx *c, const float *x, const float *v, bool index, h
 // the columns wrote in the 256 MB last-level cache: with the whole mesh at a time
 // four 512^3 steps take 16.2 ms and three 1024^3 steps 75.2 ms, in groups of
 // about 0.27 GB 15.5 and 73.6, of 0.14 GB 15.8 and 76.0, of 0.07 GB 16.7 and 82
-// (launches too short).
+// (launches too short).  At 2048^3 the smallest group (16 planes) is that large and
+// its launches are too short for their workgroups of 1024 threads: 99 ms for a
+// step's six passes whole, 116 in groups.
 constexpr int64_t GROUP_COMPLEX = 36 << 20;
 pm_status force_rows(pm_ctx *c, int64_t plane, hipStream_t s)
 {
@@ -519,13 +521,15 @@ pm_status force_rows(pm_ctx *c, int64_t plane, hipStream_t s)
     // planes j1 + N/16 m, m < 16, of `step` values of j1 at a time
     const int n2 = n / 16;
     int step = n2;
-    while (step > 1 && 16 * step * n * nhp > GROUP_COMPLEX) step /= 2;
+    if (lg <= 10)
+        while (16 * step * n * nhp > GROUP_COMPLEX) step /= 2;
+    const bool whole = step == n2;
     for (int j = 0; j < n2; j += step)
         for (int d = 2; d >= 0; d--) {
             float2 *dst = F + d * cs;
             LAUNCH(pm::K_COLS_INV,
-                   pm::launch_cols(lg, true, (d == 0 ? F : F + cs) + j * plane, nhp, plane, step, ncb, c->ws.tw, s, 16,
-                                   n2 * plane, d, dst + j * plane));
+                   pm::launch_cols(lg, true, (d == 0 ? F : F + cs) + j * plane, nhp, plane, whole ? n : step, ncb, c->ws.tw,
+                                   s, whole ? 1 : 16, whole ? 0 : n2 * plane, d, dst + j * plane));
             LAUNCH(pm::K_C2R_X0, pm::launch_c2r_x0(lg, dst, reinterpret_cast<float *>(dst), 2 * nhp, 2 * plane, (int)nhp,
                                                    plane, c->ws.tw, s, 1, 0, j, step));
         }
