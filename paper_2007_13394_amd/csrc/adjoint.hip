@@ -199,7 +199,7 @@ __global__ __launch_bounds__(PQT) void k_paint_q3_tiles(const float4 *__restrict
     const int t2 = (int)morton_compact((unsigned)t), t1 = (int)morton_compact((unsigned)t >> 1),
               t0 = (int)morton_compact((unsigned)t >> 2);
     for (int i = threadIdx.x; i < 3 * NC; i += PQT) acc[0][i] = 0;
-    tile_ranges(koff, t, t0, t1, t2, nt, rbeg, rpre);
+    tile_ranges(koff, t, nt, rbeg, rpre);
     const int total = rpre[NRANGE];
     const int o[3] = {t0 * TILE, t1 * TILE, t2 * TILE};
     for (int k = threadIdx.x; k < total; k += PQT) {

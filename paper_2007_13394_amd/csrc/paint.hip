@@ -117,7 +117,12 @@ enum { PAINT_STORE = 0, PAINT_ADD = 1, PAINT_DELTA = 2 };
 // 512 threads, two particles each per round: the 33 KB of LDS allow four workgroups per CU, and eight
 // waves each hide the latency of the range, particle and store phases.  At C3 (2048^3) this takes
 // 16.7 ms against 18.6 ms for four particles per thread, 19.1 ms for 256 threads with four each and
-// 24.1 ms for 1024 threads with two; at 256^3 (19 M particles) the same order holds.
+// 24.1 ms for 1024 threads with two; at 256^3 (19 M particles) the same order holds.  Bound by a
+// tile's chain of round trips (ranges, records, cells) and two barriers: 1640 us for 17 M particles
+// on 1024^3, where the stores alone take 754.  With one wavefront finding the ranges (before, a
+// serial prefix and one more barrier) 512^3 went from 309 to 277 us, 256^3 from 37 to 34.5, 64^3
+// from 8.6 to 8.0.  Several tiles per workgroup with the next one's loads ahead cost more registers
+// than they hid (1024^3 1987 us at best).
 constexpr int PAINT_T = 512, NPT = 2;   // NPT particles per thread per round
 
 template <int MODE>
@@ -133,13 +138,19 @@ __global__ __launch_bounds__(PAINT_T) void k_paint_tiles(const float4 *__restric
     const int nt = n / TILE, mask = n - 1;
     // workgroups walk the tiles in Morton order (the sort keys' order, nt a
     // power of two): the neighbour ranges a tile reads were mostly just read
-    // by the tiles around it
-    const int t = xcd_tile(blockIdx.x, gridDim.x);
+    // by the tiles around it.  From 1024^3 on in row-major order: the cells
+    // written dominate, and tiles spread over the planes of a Morton block
+    // write at 3.2 TB/s there (5.7 in rows; at 512^3 5.2 against 5.8).  Both
+    // measured: 1024^3 1797 us in Morton order, 1640 in rows; 512^3 275 and
+    // 288, 256^3 34.6 and 36.0.
+    const int bt = xcd_tile(blockIdx.x, gridDim.x);
+    const bool rows = nt >= 64;
+    const int t = rows ? tile_index(bt / (nt * nt), (bt / nt) % nt, bt % nt) : bt;
     const int t2 = (int)morton_compact((unsigned)t), t1 = (int)morton_compact((unsigned)t >> 1),
               t0 = (int)morton_compact((unsigned)t >> 2);
     for (int i = threadIdx.x; i < TILE * TILE * TILE; i += PAINT_T) acc[i] = 0;
     for (int i = threadIdx.x; i < nseg; i += PAINT_T) qtab[i] = quanta[i];
-    tile_ranges(koff, t, t0, t1, t2, nt, rbeg, rpre);
+    tile_ranges(koff, t, nt, rbeg, rpre);
     const int total = rpre[NRANGE];
     const int ox = t0 * TILE, oy = t1 * TILE, oz = t2 * TILE;
     for (int k0 = threadIdx.x; k0 < total; k0 += NPT * PAINT_T) {

@@ -111,40 +111,47 @@ __device__ __forceinline__ int tile_key(float u0, float u1, float u2, int n)
 // Particle ranges of a tile paint: range 0 is the tile's own particles (all
 // flags), ranges 1..19 the particles of the lower neighbour e != 0 (bit d of
 // e: one tile lower along axis d) whose face flags f contain e, in (e, f)
-// order: exactly those with a +1 corner inside this tile.  rbeg[r] is the
-// first sorted index of range r, rpre the exclusive prefix of the lengths
-// (rpre[NRANGE] = total).  Called by the whole workgroup; ends with a barrier.
+// order: exactly those with a +1 corner inside this tile.  Lane r of a
+// wavefront loads range r, and the same wavefront stores them all: rbeg[r] the
+// first sorted index, rpre the exclusive prefix of the lengths (rpre[NRANGE] =
+// total).
 constexpr int NRANGE = 20;
-__device__ __forceinline__ void tile_ranges(const int *__restrict__ koff, int t, int t0, int t1, int t2, int nt,
-                                            int *rbeg, int *rpre)
+struct TileRange {
+    int beg, len;
+};
+__device__ __forceinline__ TileRange tile_range_load(const int *__restrict__ koff, int t, int nt)
 {
-    if (threadIdx.x < 64) {
-        const int e = threadIdx.x >> 3, f = threadIdx.x & 7;
-        int slot = -1, b = 0, len = 0;
-        if (e == 0 && f == 0) {
-            slot = 0;
-            b = koff[t * 8];
-            len = koff[t * 8 + 8] - b;
-        } else if (e != 0 && (f & e) == e) {
-            slot = 1;
-            for (int ee = 1; ee < e; ee++) slot += 1 << (3 - __popc(ee));
-            for (int ff = 0; ff < f; ff++) slot += ((ff & e) == e) ? 1 : 0;
-            const int s0 = (t0 - (e & 1) + nt) % nt, s1 = (t1 - ((e >> 1) & 1) + nt) % nt,
-                      s2 = (t2 - ((e >> 2) & 1) + nt) % nt;
-            const int tn = tile_index(s0, s1, s2);
-            b = koff[tn * 8 + f];
-            len = koff[tn * 8 + f + 1] - b;
-        }
-        if (slot >= 0) {
-            rbeg[slot] = b;
-            rpre[slot + 1] = len;
-        }
+    // e and f of range r: octal digit r from the right
+    constexpr uint64_t E = 076655444433222211110ull, F = 077675765473763275310ull;
+    const int lane = threadIdx.x & 63;
+    if (lane >= NRANGE) return TileRange{0, 0};
+    const int e = (int)(E >> (3 * lane)) & 7, f = (int)(F >> (3 * lane)) & 7;
+    const int t2 = (int)morton_compact((unsigned)t), t1 = (int)morton_compact((unsigned)t >> 1),
+              t0 = (int)morton_compact((unsigned)t >> 2);
+    const int s0 = (t0 - (e & 1)) & (nt - 1), s1 = (t1 - ((e >> 1) & 1)) & (nt - 1), s2 = (t2 - (e >> 2)) & (nt - 1);
+    const int k = tile_index(s0, s1, s2) * 8 + f;
+    const int beg = koff[k];
+    return TileRange{beg, koff[k + (lane == 0 ? 8 : 1)] - beg};
+}
+__device__ __forceinline__ void tile_range_store(TileRange r, int *rbeg, int *rpre)
+{
+    const int lane = threadIdx.x & 63;
+    int sum = r.len;   // inclusive prefix
+#pragma unroll
+    for (int d = 1; d < 32; d *= 2) {
+        const int below = __shfl_up(sum, d);
+        if (lane >= d) sum += below;
     }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        rpre[0] = 0;
-        for (int r = 1; r <= NRANGE; r++) rpre[r] += rpre[r - 1];
+    if (lane == 0) rpre[0] = 0;
+    if (lane < NRANGE) {
+        rbeg[lane] = r.beg;
+        rpre[lane + 1] = sum;
     }
+}
+// The ranges of one tile, for the whole workgroup; ends with a barrier.
+__device__ __forceinline__ void tile_ranges(const int *__restrict__ koff, int t, int nt, int *rbeg, int *rpre)
+{
+    if (threadIdx.x < 64) tile_range_store(tile_range_load(koff, t, nt), rbeg, rpre);
     __syncthreads();
 }
 

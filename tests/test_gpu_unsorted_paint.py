@@ -5,7 +5,6 @@ pm_density must equal (float)(Q 2^-shift - 1) of pm_paint_q's int64 mesh in
 every cell, bit for bit: below and above the size where the sort takes more
 rounds per thread, at meshes without tiles, and into a mesh that is not
 aligned for 16-byte stores."""
-import numpy as np
 import pytest
 import torch
 
@@ -16,7 +15,8 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("offset", [0, 1])
 @pytest.mark.parametrize("name,over", [("C5_fd16", {}), ("C5_fd32", {}), ("C1", dict(n_shell=3, n_fib=1)),
-                                       ("C5", dict(n_mesh=128, n_shell=7))])
+                                       ("C5", dict(n_mesh=128, n_shell=7)),
+                                       ("C1", dict(n_mesh=1024))])   # tiles in row-major order
 def test_density_equals_atomic_paint(dev, name, over, offset):
     from paper_2007_13394_amd import pm
     cfg = I.config(name, **over)
@@ -32,7 +32,7 @@ def test_density_equals_atomic_paint(dev, name, over, offset):
     q = torch.zeros(n ** 3, dtype=torch.int64, device=dev)
     for g in range(ctx.nseg):
         pm.pm_paint_q(ctx, x, int(off[g]), int(off[g + 1] - off[g]), int(quanta[g]), q)
-    ref = (q.cpu().numpy().astype(np.float64) * 2.0 ** -cfg["shift"] - 1.0).astype(np.float32)
+    ref = (q.double() * 2.0 ** -cfg["shift"] - 1.0).float()
     delta = torch.full((n ** 3 + offset,), 7.0, dtype=torch.float32, device=dev)[offset:]
     pm.pm_density(ctx, x, delta)
-    assert np.array_equal(delta.cpu().numpy(), ref)
+    assert torch.equal(delta, ref)
