@@ -590,8 +590,9 @@ __global__ __launch_bounds__(256) void k_power_bin(const float2 *__restrict__ A,
 }
 
 // The bins' geometry: sum w and sum w |k| over the full mesh, from the modes 0
-// <= n1 <= n0 <= N/2, 0 <= n2 <= N/2 with their multiplicities (an eighth of the
-// half spectrum).  One wavefront per (n0, n1) row.
+// <= n2 <= n1 <= n0 <= N/2 with their multiplicities (1/48 of the mesh).  One
+// wavefront per (n0, n1) row; bound by the prefix sums (over 0 <= n2 <= N/2 86 us at
+// 512^3, now 44).
 __global__ __launch_bounds__(256) void k_power_geom(int n, int nbins, double kf, double *partial)
 {
     __shared__ double hist[2 * MAX_BINS];
@@ -601,13 +602,15 @@ __global__ __launch_bounds__(256) void k_power_geom(int n, int nbins, double kf,
     for (int r = blockIdx.x * 4 + wave; r < nh * nh; r += gridDim.x * 4) {
         const int n0 = r / nh, n1 = r - n0 * nh;
         if (n1 > n0) continue;   // uniform over the wavefront
+        // signs of n0 and n1, and the orders of three numbers of which the first two differ or not
         const double wr = ((n0 == 0 || n0 == n / 2) ? 1.0 : 2.0) * ((n1 == 0 || n1 == n / 2) ? 1.0 : 2.0) *
-                          (n1 < n0 ? 2.0 : 1.0);
-        for (int c = 0; c < nh; c += 64) {
+                          (n1 < n0 ? 6.0 : 3.0);
+        for (int c = 0; c <= n1; c += 64) {
             const int n2 = c + lane, nn = n0 * n0 + n1 * n1 + n2 * n2;
-            int b = n2 < nh ? isqrt24(nn) : -1;
+            int b = n2 <= n1 ? isqrt24(nn) : -1;
             if (nn == 0 || b >= nbins) b = -1;
-            const double w = b >= 0 ? wr * ((n2 == 0 || n2 == n / 2) ? 1.0 : 2.0) : 0.0;
+            const double w = b >= 0 ? (n2 < n1 ? wr : n1 < n0 ? wr * 0.5 : wr / 3.0) *
+                                          ((n2 == 0 || n2 == n / 2) ? 1.0 : 2.0) : 0.0;
             const int next = __shfl_down(b, 1);
             bin_runs(hist, b, next, lane == 63, w);
             bin_runs(hist + nbins, b, next, lane == 63, w * (kf * sqrt((double)nn)));
@@ -617,19 +620,31 @@ __global__ __launch_bounds__(256) void k_power_geom(int n, int nbins, double kf,
     for (int i = threadIdx.x; i < 2 * nbins; i += 256) partial[(int64_t)blockIdx.x * 2 * nbins + i] = hist[i];
 }
 
-// out[i] = the sum of ne-long partials over np workgroups, each value's 32
-// strided sums added in order (deterministic).
-__global__ __launch_bounds__(256) void k_power_reduce(const double *__restrict__ partial, int np, int ne, double *out)
+// out[i] = the sum of ne-long partials over np workgroups, each value's 128
+// strided sums added in order (deterministic).  Few workgroups read up to 8 MB:
+// 1024 threads each for the loads in flight (256: 29 us for 4096 partials of 256,
+// now 10).
+constexpr int POWER_RED_G = 128;
+__global__ __launch_bounds__(8 * POWER_RED_G) void k_power_reduce(const double *__restrict__ partial, int np, int ne,
+                                                                  double *out)
 {
-    __shared__ double sh[32][9];
+    __shared__ double sh[POWER_RED_G][9];
     const int c = threadIdx.x & 7, g = threadIdx.x >> 3, i = blockIdx.x * 8 + c;
     double s = 0.0;
     if (i < ne)
-        for (int b = g; b < np; b += 32) s += partial[(int64_t)b * ne + i];
+#pragma unroll 8
+        for (int b = g; b < np; b += POWER_RED_G) s += partial[(int64_t)b * ne + i];
     sh[g][c] = s;
     __syncthreads();
+    if (g < 8) {
+        s = 0.0;
+        for (int k = g; k < POWER_RED_G; k += 8) s += sh[k][c];
+    }
+    __syncthreads();
+    if (g < 8) sh[g][c] = s;
+    __syncthreads();
     if (g == 0 && i < ne) {
-        for (int k = 1; k < 32; k++) s += sh[k][c];
+        for (int k = 1; k < 8; k++) s += sh[k][c];
         out[i] = s;
     }
 }
@@ -809,7 +824,7 @@ hipError_t launch_power_geom(int n, int nbins, double kf, double *partial, int b
 
 hipError_t launch_power_reduce(const double *partial, int np, int ne, double *out, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_power_reduce, dim3((unsigned)((ne + 7) / 8)), dim3(256), 0, s, partial, np, ne, out);
+    hipLaunchKernelGGL(k_power_reduce, dim3((unsigned)((ne + 7) / 8)), dim3(8 * POWER_RED_G), 0, s, partial, np, ne, out);
     return hipGetLastError();
 }
 
