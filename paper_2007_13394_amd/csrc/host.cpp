@@ -351,10 +351,10 @@ pm_status settle_sort(pm_ctx *c, hipStream_t s, bool *stale)
 // x in between, the check fails and the sort is redone from a fresh count
 // (the scatter never writes past the record arrays).  The check waits for the
 // stream, so it is used only when the end-of-call guards wait anyway.
-// With `defer`, a verification of taken-over counts is left in flight and
-// finish_sort settles it: the caller may queue work in between that writes
-// only the workspace, or that does nothing while ws.flag[FLAG_STALE] is set;
-// it is redone when the counts were stale.
+// With `defer`, the check of taken-over counts (verify_pending) is left to the
+// caller's tile paint and finish_sort settles it: the caller may queue work in
+// between that writes only the workspace, or that does nothing while
+// ws.flag[FLAG_STALE] is set; it is redone when the counts were stale.
 pm_status tile_sort(pm_ctx *c, const float *x, const float *p, hipStream_t s, bool defer = false)
 {
     const int64_t K = c->nkeys;
@@ -366,13 +366,10 @@ pm_status tile_sort(pm_ctx *c, const float *x, const float *p, hipStream_t s, bo
         LAUNCH(pm::K_SORT_SCATTER,
                pm::launch_sort_scatter(x, p, tin, c->P, c->nseg, c->ws.seg_off, c->n, c->ws.cnt, c->ws.xs,
                                        p ? c->ws.ps : nullptr, c->ids, c->ids ? c->ws.ids_tmp : nullptr, s));
+        c->verify_pending = true;
+        if (defer) return PM_OK;
         LAUNCH(pm::K_SORT_VERIFY, pm::launch_sort_verify(c->ws.cnt, c->ws.koff, K, c->ws.flag + pm::FLAG_STALE,
                                                          c->guards + pm::FLAG_STALE, s));
-        c->verify_pending = true;
-        if (defer) {
-            if (c->cfg.flags & PM_FLAG_DEFER_GUARDS) HIPCHK(hipEventRecord(c->verify_ev, s));
-            return PM_OK;
-        }
         HIPCHK(hipStreamSynchronize(s));
         bool stale;
         pm_status st = settle_sort(c, s, &stale);
@@ -428,7 +425,10 @@ pm_status sorted_step(pm_ctx *c, float *x, float *p, double kick, double drift, 
     for (bool redo = true; redo;) {
         LAUNCH(pm::K_PAINT, pm::launch_paint_tiles_delta(c->ws.xs, c->ws.koff, c->ws.quanta, c->nseg, 0, c->nseg, c->n,
                                                          ldexp(1.0, -c->cfg.shift), -1.0, delta,
-                                                         guard(c, pm::FLAG_RECORDS), s));
+                                                         guard(c, pm::FLAG_RECORDS), s,
+                                                         c->verify_pending ? c->ws.cnt : nullptr,
+                                                         c->ws.flag + pm::FLAG_STALE, c->guards + pm::FLAG_STALE));
+        if (deferred && c->verify_pending) HIPCHK(hipEventRecord(c->verify_ev, s));
         st = solve_delta(delta);
         if (st != PM_OK) return st;
         if (deferred) {

@@ -130,7 +130,8 @@ __global__ __launch_bounds__(PAINT_T) void k_paint_tiles(const float4 *__restric
                                                          const int *__restrict__ koff,
                                                          const int64_t *__restrict__ quanta, int nseg, int lo,
                                                          int hi, int n, void *out, double scale, double offset,
-                                                         int *flag)
+                                                         int *flag, const int *__restrict__ cursor, int *stale,
+                                                         int *host_stale)
 {
     __shared__ unsigned long long acc[TILE * TILE * TILE];
     __shared__ long long qtab[MAX_SEG];
@@ -151,6 +152,15 @@ __global__ __launch_bounds__(PAINT_T) void k_paint_tiles(const float4 *__restric
     for (int i = threadIdx.x; i < TILE * TILE * TILE; i += PAINT_T) acc[i] = 0;
     for (int i = threadIdx.x; i < nseg; i += PAINT_T) qtab[i] = quanta[i];
     tile_ranges(koff, t, nt, rbeg, rpre);
+    // counts taken over: every cursor of a scatter that they described has
+    // reached the next key's offset (k_sort_verify, without a launch of its own)
+    if (cursor && threadIdx.x >= PAINT_T - 8) {
+        const int k = t * 8 + (int)threadIdx.x - (PAINT_T - 8);
+        if (__any(cursor[k] != koff[k + 1]) && threadIdx.x == PAINT_T - 1) {
+            raise(stale);
+            raise(host_stale);
+        }
+    }
     const int total = rpre[NRANGE];
     const int ox = t0 * TILE, oy = t1 * TILE, oz = t2 * TILE;
     for (int k0 = threadIdx.x; k0 < total; k0 += NPT * PAINT_T) {
@@ -260,7 +270,8 @@ hipError_t launch_paint_tiles(const float4 *xs, const int *koff, const int64_t *
     const int nt = n / TILE;
     if (nt < 2) return hipErrorInvalidValue;
     hipLaunchKernelGGL(k_paint_tiles<PAINT_STORE>, dim3((unsigned)(nt * nt * nt)), dim3(PAINT_T), 0, s, xs, koff, quanta,
-                       nseg, seg_lo, seg_hi, n, static_cast<void *>(mesh), 0.0, 0.0, static_cast<int *>(nullptr));
+                       nseg, seg_lo, seg_hi, n, static_cast<void *>(mesh), 0.0, 0.0, static_cast<int *>(nullptr),
+                       static_cast<const int *>(nullptr), static_cast<int *>(nullptr), static_cast<int *>(nullptr));
     return hipGetLastError();
 }
 
@@ -270,19 +281,20 @@ hipError_t launch_paint_tiles_add(const float4 *xs, const int *koff, const int64
     const int nt = n / TILE;
     if (nt < 2) return hipErrorInvalidValue;
     hipLaunchKernelGGL(k_paint_tiles<PAINT_ADD>, dim3((unsigned)(nt * nt * nt)), dim3(PAINT_T), 0, s, xs, koff, quanta,
-                       nseg, seg_lo, seg_hi, n, static_cast<void *>(mesh), 0.0, 0.0, static_cast<int *>(nullptr));
+                       nseg, seg_lo, seg_hi, n, static_cast<void *>(mesh), 0.0, 0.0, static_cast<int *>(nullptr),
+                       static_cast<const int *>(nullptr), static_cast<int *>(nullptr), static_cast<int *>(nullptr));
     return hipGetLastError();
 }
 
 hipError_t launch_paint_tiles_delta(const float4 *xs, const int *koff, const int64_t *quanta, int nseg, int seg_lo,
                                     int seg_hi, int n, double scale, double offset, float *delta, int *flag,
-                                    hipStream_t s)
+                                    hipStream_t s, const int *cursor, int *stale, int *host_stale)
 {
     const int nt = n / TILE;
     // rows are stored 16 bytes at a time
     if (nt < 2 || (reinterpret_cast<uintptr_t>(delta) & 15) != 0) return hipErrorInvalidValue;
     hipLaunchKernelGGL(k_paint_tiles<PAINT_DELTA>, dim3((unsigned)(nt * nt * nt)), dim3(PAINT_T), 0, s, xs, koff, quanta,
-                       nseg, seg_lo, seg_hi, n, static_cast<void *>(delta), scale, offset, flag);
+                       nseg, seg_lo, seg_hi, n, static_cast<void *>(delta), scale, offset, flag, cursor, stale, host_stale);
     return hipGetLastError();
 }
 

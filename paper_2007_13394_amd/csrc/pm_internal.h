@@ -482,10 +482,12 @@ hipError_t launch_paint_tiles_add(const float4 *xs, const int *koff, const int64
                                   int seg_hi, int n, int64_t *mesh, hipStream_t s);
 // Tile paint of segments [seg_lo, seg_hi), stored as the float32 density
 // contrast (float)(Q scale + offset) of each cell's exact int64 sum (overflow
-// flag as the transforms raise it).  delta: 16-byte aligned.
+// flag as the transforms raise it).  delta: 16-byte aligned.  cursor (optional):
+// also the check of launch_sort_verify, of the scatter that made the records.
 hipError_t launch_paint_tiles_delta(const float4 *xs, const int *koff, const int64_t *quanta, int nseg, int seg_lo,
                                     int seg_hi, int n, double scale, double offset, float *delta, int *flag,
-                                    hipStream_t s);
+                                    hipStream_t s, const int *cursor = nullptr, int *stale = nullptr,
+                                    int *host_stale = nullptr);
 
 // ---- launchers (sort.hip)
 // Counting sort by tile key: counts per key (cnt zeroed by the caller), an
