@@ -72,8 +72,9 @@ typedef enum {
 enum {
     PM_FLAG_NO_FLIP = 1,   /* keep one direction set on every neutrino site */
     PM_FLAG_NO_GUARDS = 2, /* skip the end-of-call device flag check (no host sync) */
-    PM_FLAG_NO_SORT = 4,   /* keep particles in segment order (pm_step paints with
-                              global atomics and gathers the force: slower) */
+    PM_FLAG_NO_SORT = 4,   /* keep particles in segment order (pm_step then sorts
+                              records into the workspace on every call and reads
+                              the force out by tile through their indices) */
     PM_FLAG_LEARNED = 8,   /* reserve the workspace of the learned force correction
                               (pm_learned_*; N a power of two >= 16) */
     PM_FLAG_NU_PSEUDO = 16, /* pseudo-random neutrino velocities, one particle per
@@ -81,9 +82,9 @@ enum {
                                pm_ic_pseudo instead of pm_ic */
     PM_FLAG_DEFER_GUARDS = 32 /* check each call's guard words without waiting for
                                  it: they are read by the next guarded call after
-                                 that call has queued its own work, or by pm_sync.  The next call
-                                 (or pm_sync) returns the error; the failing call
-                                 returns PM_OK.  No host wait per call. */
+                                 that call has queued its own work, or by pm_sync.
+                                 The next call (or pm_sync) returns the error; the
+                                 failing call returns PM_OK.  No host wait per call. */
 };
 
 /* Simulation parameters (Table 1 of the paper names the counts).  All
