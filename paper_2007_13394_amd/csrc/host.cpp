@@ -475,8 +475,9 @@ pm_status tile_records(pm_ctx *c, const float *x, const float *v, bool index, hi
 // with global atomics into the int64 mesh Q (*delta null).  The cells are the
 // same integers either way.  A tile paint moves 20 bytes per particle and 4
 // per cell instead of eight scattered 8-byte atomics per particle, which the
-// eight L2s cannot combine (v: also sorted into ps): 19 M particles on 512^3 take 1.3 ms (count, scan,
-// scatter, paint) against 3.9 ms, 69 k on 64^3 40 us against 105 us.
+// eight L2s cannot combine: 19 M particles on 512^3 take 0.95 ms (count, scan,
+// scatter, paint) against 3.9 ms, 69 k on 64^3 40 us against 105 us.  v: also
+// sorted, into ps; index: also each record's particle.
 pm_status paint_density(pm_ctx *c, const float *x, const float *v, bool index, hipStream_t s, const float **delta)
 {
     *delta = nullptr;
