@@ -923,7 +923,7 @@ pm_status pm_init(const pm_config *cfg, void *workspace, size_t workspace_bytes,
         return fail(PM_ERR_DEVICE, "address of the static scratch array: %s", hipGetErrorString(e));
     }
     e = hipHostMalloc(reinterpret_cast<void **>(&c->guards), 2 * pm::FLAG_WORDS * sizeof(int),
-                      hipHostMallocMapped | hipHostMallocCoherent);
+                      hipHostMallocMapped | hipHostMallocCoherent | hipHostMallocPortable);
     if (e == hipSuccess) std::fill(c->guards, c->guards + 2 * pm::FLAG_WORDS, 0);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&c->verify_ev, hipEventDisableTiming);
     for (int k = 0; k < 2 && e == hipSuccess; k++) e = hipEventCreateWithFlags(&c->guard_ev[k], hipEventDisableTiming);
