@@ -322,8 +322,7 @@ pm_status paint_atomic(pm_ctx *c, const float *x, int lo, int hi, int64_t *mesh,
 }
 
 // Reads a verification that has ended.  Stale: the words are cleared, with what
-// a paint of the stale records may have set; the counts left for the next step
-// are still the zeros that the scan wrote.
+// a paint of the stale records may have set.
 pm_status settle_sort(pm_ctx *c, hipStream_t s, bool *stale)
 {
     c->verify_pending = false;
@@ -335,7 +334,6 @@ pm_status settle_sort(pm_ctx *c, hipStream_t s, bool *stale)
     *guard(c, pm::FLAG_RECORDS) = 0;
     LAUNCH(pm::K_FILL, pm::launch_fill_i32(c->ws.flag + pm::FLAG_STALE, 1, s));
     c->counts_ready = false;
-    c->cnt_next_zero = true;
     return PM_OK;
 }
 
@@ -355,14 +353,18 @@ pm_status settle_sort(pm_ctx *c, hipStream_t s, bool *stale)
 // caller's tile paint and finish_sort settles it: the caller may queue work in
 // between that writes only the workspace, or that does nothing while
 // ws.flag[FLAG_STALE] is set; it is redone when the counts were stale.
+// Such a caller is a step: its readout counts the next keys, into the counts
+// that the scan clears for it.  Without `defer` they stay as they are, for the
+// next call on x (a step after a paint of C2's particles 3.2 ms; cleared by the
+// paint, they made it sort, paint and solve twice: 8.2 ms).
 pm_status tile_sort(pm_ctx *c, const float *x, const float *p, hipStream_t s, bool defer = false)
 {
     const int64_t K = c->nkeys;
     const uint8_t *tin = c->permuted ? c->ws.tags : nullptr;
     c->verify_pending = false;
     if (c->counts_ready && x == c->counts_x && !(c->cfg.flags & PM_FLAG_NO_GUARDS)) {
-        LAUNCH(pm::K_SORT_SCAN, pm::launch_scan(c->ws.cnt_next, c->ws.koff, K + 1, c->ws.bsum, s, c->ws.cnt, true));
-        c->cnt_next_zero = true;
+        LAUNCH(pm::K_SORT_SCAN, pm::launch_scan(c->ws.cnt_next, c->ws.koff, K + 1, c->ws.bsum, s, c->ws.cnt, defer));
+        if (defer) c->cnt_next_zero = true;
         LAUNCH(pm::K_SORT_SCATTER,
                pm::launch_sort_scatter(x, p, tin, c->P, c->nseg, c->ws.seg_off, c->n, c->ws.cnt, c->ws.xs,
                                        p ? c->ws.ps : nullptr, c->ids, c->ids ? c->ws.ids_tmp : nullptr, s));
@@ -398,7 +400,9 @@ pm_status finish_sort(pm_ctx *c, const float *x, const float *p, hipStream_t s, 
     else
         HIPCHK(hipStreamSynchronize(s));
     pm_status st = settle_sort(c, s, redo);
-    return st == PM_OK && *redo ? tile_sort(c, x, p, s) : st;
+    if (st != PM_OK || !*redo) return st;
+    c->cnt_next_zero = true;   // as the scan left them: the readout has added nothing
+    return tile_sort(c, x, p, s);
 }
 
 // One sorted step: sort by tile, paint tile by tile, solve, read out tile by
