@@ -84,7 +84,10 @@ enum {
                                  it: they are read by the next guarded call after
                                  that call has queued its own work, or by pm_sync.
                                  The next call (or pm_sync) returns the error; the
-                                 failing call returns PM_OK.  No host wait per call. */
+                                 failing call returns PM_OK.  No host wait for a
+                                 call's end; a sorted step that takes over the last
+                                 step's counts waits for their check, which comes
+                                 before its paint and solve. */
 };
 
 /* Simulation parameters (Table 1 of the paper names the counts).  All
