@@ -279,13 +279,29 @@ pm_status check_guards(pm_ctx *c, hipStream_t s)
 
 bool sorting_on(const pm_ctx *c) { return c->nkeys > 0 && !(c->cfg.flags & PM_FLAG_NO_SORT); }
 
+// Whether particles in the caller's order are read out by tile.  A tile costs
+// the staging of its 59 KB of the force meshes however few its particles (500 us
+// at 512^3, 3560 at 1024^3); a gather costs each particle its twelve rows, which
+// lattice neighbours share and neutrinos do not: about 0.09 ns more than by tile for
+// a CDM particle and three times that for a neutrino, against 15 ns for a tile.
+// So by tile from 160 CDM particles a tile, a neutrino counting as three.  Readouts
+// by tile and by gather (with the scatter), us, one side and the other of the line:
+// 512^3 with 64 CDM particles a tile 553 and 242, with 64 and 9 neutrinos 577 and
+// 347, with 8 and 70 785 and 859, with 512 and 70 1098 and 1532; 256^3 with 64 61 and 32,
+// with 8 and 70 91 and 102; 1024^3 with 64 and 9 4362 and 2490.  Below 256^3 there are
+// too few tiles for their cost to show (128^3 with 64 17.4 and 15.5, 64^3 13.2 and 14.8).
+bool tile_readout(const pm_ctx *c)
+{
+    return c->nkeys > 0 && (c->logn < 8 || c->nc + 3 * c->nn >= 160 * (c->nkeys / 8));
+}
+
 // Force meshes (planes ps_f, components comp apart) read out at x for
 // particles in the caller's order: by tile from the records paint_density has
 // sorted, else a gather.
 pm_status readout_force(pm_ctx *c, const float *x, int64_t ps_f, int64_t comp, float *acc, hipStream_t s)
 {
     const int64_t nhp = pm::half_pad(c->n);
-    if (c->nkeys > 0)
+    if (tile_readout(c))
         LAUNCH(pm::K_READOUT, pm::launch_readout_tiles(c->ws.xs, c->ws.ids_tmp, c->P, c->ws.koff, c->ws.f, nhp, ps_f, comp,
                                                        c->n, acc, s));
     else
@@ -297,7 +313,7 @@ pm_status readout_force(pm_ctx *c, const float *x, int64_t ps_f, int64_t comp, f
 pm_status readout_step(pm_ctx *c, float *x, float *p, int64_t ps_f, int64_t comp, double kick, double drift, hipStream_t s)
 {
     const int64_t nhp = pm::half_pad(c->n);
-    if (c->nkeys > 0)
+    if (tile_readout(c))
         LAUNCH(pm::K_READOUT_KD,
                pm::launch_readout_kd_index_tiles(c->ws.xs, c->ws.ids_tmp, c->P, c->ws.koff, c->ws.f, nhp, ps_f, comp, c->n,
                                                  (float)kick, (float)drift, x, p, guard(c, pm::FLAG_NAN), s));
@@ -1242,7 +1258,7 @@ pm_status pm_force(pm_ctx *c, const float *x, float *acc, void *stream)
     if (!c || !x || !acc) return fail(PM_ERR_ARG, "NULL argument to pm_force");
     hipStream_t s = S(stream);
     const float *delta;
-    pm_status st = paint_density(c, x, nullptr, true, s, &delta);
+    pm_status st = paint_density(c, x, nullptr, tile_readout(c), s, &delta);
     if (st == PM_OK) st = solve(c, c->ws.q, s, delta);
     if (st != PM_OK) return st;
     const int64_t fp = pm::force_plane(c->n);
@@ -1263,7 +1279,7 @@ pm_status pm_step(pm_ctx *c, float *x, float *p, double a_force, double a_kick0,
         return sorted_step(c, x, p, kick, drift, fp, s,
                            [&](const float *delta) { return solve(c, nullptr, s, delta); });
     const float *delta;
-    st = paint_density(c, x, nullptr, true, s, &delta);
+    st = paint_density(c, x, nullptr, tile_readout(c), s, &delta);
     if (st == PM_OK) st = solve(c, c->ws.q, s, delta);
     if (st != PM_OK) return st;
     st = readout_step(c, x, p, fp, n * fp, kick, drift, s);
@@ -1478,7 +1494,7 @@ pm_status pm_learned_force(pm_ctx *c, const float *th, double a, const float *x,
     if (st != PM_OK) return st;
     hipStream_t s = S(stream);
     const float *delta;
-    st = paint_density(c, x, nullptr, true, s, &delta);
+    st = paint_density(c, x, nullptr, tile_readout(c), s, &delta);
     if (st == PM_OK) st = learned_solve(c, th, a, false, s, delta);
     if (st != PM_OK) return st;
     const int64_t n = c->n, nhp = pm::half_pad(c->n);
@@ -1501,7 +1517,7 @@ pm_status pm_learned_step(pm_ctx *c, const float *th, float *x, float *p, double
         return sorted_step(c, x, p, kick, drift, n * nhp, s,
                            [&](const float *delta) { return learned_solve(c, th, a_force, false, s, delta); });
     const float *delta;
-    st = paint_density(c, x, nullptr, true, s, &delta);
+    st = paint_density(c, x, nullptr, tile_readout(c), s, &delta);
     if (st == PM_OK) st = learned_solve(c, th, a_force, false, s, delta);
     if (st != PM_OK) return st;
     st = readout_step(c, x, p, n * nhp, n * n * nhp, kick, drift, s);
