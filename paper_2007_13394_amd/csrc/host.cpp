@@ -402,7 +402,7 @@ pm_status tile_sort(pm_ctx *c, const float *x, const float *p, hipStream_t s, bo
         if (st != PM_OK || !stale) return st;
     }
     LAUNCH(pm::K_FILL, pm::launch_fill_i32(c->ws.cnt, K + 1, s));
-    LAUNCH(pm::K_SORT_COUNT, pm::launch_sort_count(x, c->P, c->n, c->ws.cnt, s));
+    LAUNCH(pm::K_SORT_COUNT, pm::launch_sort_count(x, c->P, c->n, c->permuted, c->ws.cnt, s));
     // koff <- exclusive scan of the counts; cnt <- the same, as cursors
     LAUNCH(pm::K_SORT_SCAN, pm::launch_scan(c->ws.cnt, c->ws.koff, K + 1, c->ws.bsum, s, c->ws.cnt));
     LAUNCH(pm::K_SORT_SCATTER,
@@ -491,7 +491,7 @@ pm_status tile_records(pm_ctx *c, const float *x, const float *v, bool index, hi
 {
     const int64_t K = c->nkeys;
     LAUNCH(pm::K_FILL, pm::launch_fill_i32(c->ws.cnt, K + 1, s));
-    LAUNCH(pm::K_SORT_COUNT, pm::launch_sort_count(x, c->P, c->n, c->ws.cnt, s));
+    LAUNCH(pm::K_SORT_COUNT, pm::launch_sort_count(x, c->P, c->n, c->permuted, c->ws.cnt, s));
     LAUNCH(pm::K_SORT_SCAN, pm::launch_scan(c->ws.cnt, c->ws.koff, K + 1, c->ws.bsum, s, c->ws.cnt));
     LAUNCH(pm::K_SORT_SCATTER,
            pm::launch_sort_scatter(x, v, c->permuted ? c->ws.tags : nullptr, c->P, c->nseg, c->ws.seg_off, c->n,
@@ -1201,7 +1201,7 @@ pm_status pm_paint_static(pm_ctx *c, const float *x, int32_t seg_lo, int32_t seg
     float4 *xs = reinterpret_cast<float4 *>(c->static_scratch + STATIC_XS);
     // the counts start at zero (a fill kernel, which a graph capture may hold)
     LAUNCH(pm::K_FILL, pm::launch_fill_i32(cnt, K + 1, s));
-    LAUNCH(pm::K_SORT_COUNT, pm::launch_sort_count(x, c->P, c->n, cnt, s));
+    LAUNCH(pm::K_SORT_COUNT, pm::launch_sort_count(x, c->P, c->n, c->permuted, cnt, s));
     LAUNCH(pm::K_SORT_SCAN, pm::launch_scan(cnt, koff, K + 1, bsum, s, cnt));
     LAUNCH(pm::K_SORT_SCATTER, pm::launch_sort_scatter(x, nullptr, c->permuted ? c->ws.tags : nullptr, c->P, c->nseg,
                                                        c->ws.seg_off, c->n, cnt, xs, nullptr, nullptr, nullptr, s));

@@ -495,8 +495,9 @@ hipError_t launch_paint_tiles_delta(const float4 *xs, const int *koff, const int
 // copy, the scatter's cursors; clear: the counts are zeroed), and the
 // scatter of particles to their cursor slots (cursor advanced by the counts).
 // ids_out (optional): ids_in[i], or the particle's index i without ids_in, in
-// sorted order.
-hipError_t launch_sort_count(const float *x, int64_t P, int n, int *cnt, hipStream_t s);
+// sorted order.  sorted (and tag_in for the scatter): x is in the order of an earlier
+// sort, not canonical.
+hipError_t launch_sort_count(const float *x, int64_t P, int n, bool sorted, int *cnt, hipStream_t s);
 hipError_t launch_scan(int *in, int *out, int64_t n, int *block_sums, hipStream_t s, int *out2 = nullptr,
                        bool clear = false);
 hipError_t launch_sort_scatter(const float *x, const float *p, const uint8_t *tag_in, int64_t P, int nseg,

@@ -5,14 +5,15 @@
 // TILE^3-cell block holding floor(u); bit d of the flags is set when floor(u_d) is the last
 // cell of the tile along axis d (its +1 cloud-in-cell corner then lies in the
 // next tile).  Counting: one atomic per distinct key per wavefront (lanes
-// sharing a key are grouped by ballot), so lattice-ordered CDM, where most of
-// a wavefront falls in one tile, costs few atomics.  Offsets come from an
+// sharing a key are grouped by ballot) or, in the form for large sets, per chunk of
+// 2048 particles (gathered in an LDS hash table), so lattice-ordered CDM, where
+// most of a wavefront falls in one tile, costs few atomics.  Offsets come from an
 // exclusive scan of the counts, which also leaves a copy of them as per-key
 // cursors; the scatter recomputes each particle's key from its position,
-// takes its slot from the cursor (one returning atomic per key and
-// wavefront, lanes ranked by ballot), and writes the position record (with
-// the segment tag), the momentum and the optional id there.  The order of
-// particles within a key depends on the order of the atomics.
+// takes its slot from the cursor (one returning atomic per key and wavefront or
+// chunk), and writes the position record (with the segment tag), the momentum and
+// the optional id there.  The order of particles within a key depends on the
+// order of the atomics.
 #include "pm_internal.h"
 
 namespace pm {
@@ -29,12 +30,31 @@ inline unsigned grid_for(int64_t n, int block, int64_t cap = 65536LL * 16)
 
 // Each workgroup takes a chunk of consecutive particles, workgroups numbered so
 // that each XCD owns a contiguous run of chunks (the scatter of a nearly
-// sorted state then writes whole cache lines from one L2).  Below SORT_FEW
-// particles one per thread: a small sort waits on its chain of rounds and not
-// on memory bandwidth or atomics (69 k particles on 64^3, against eight per
-// thread: count 27 -> 9 us, scatter 33 -> 11 us; sorted steps 13.3 -> 6.4 us).
+// sorted state then writes whole cache lines from one L2).
+//
+// Two forms: one particle per thread, grouped by key within a wavefront, and
+// chunks of WG_R per thread, grouped within the workgroup.  Chunks bring a
+// key's atomics down and cost a chain of eight rounds, so they pay where atomics
+// to one key queue up: with many particles per key, sooner in canonical order, where
+// a key's particles lie scattered over the launch.  Wavefront form / chunks, us, by
+// particles and @ particles per key.
+//   count and scatter, canonical order: chunks from 2^16 with 128 per key and
+//   from 2^20.  9 k @134 14/25; 69 k @134 36/31, @17 25/29; 298 k @582 85/47, @73
+//   37/36, @9 33/38; 549 k @1072 213/89, @134 80/62, @17 65/62; 803 k @196 108/83, @25
+//   85/87; 2.4 M @582 161/122, @73 143/115; 19 M @582 998/680, @73 1055/779.
+//   scatter of a step: chunks from 2^16 with 640 per key, from 2^20 with 128 and
+//   from 2^26.  69 k @1072 17.3/15.0, @134 7.8/15.2; 298 k @582 14.2/16.0; 406 k @792
+//   21.0/18.2; 549 k @1072 29.4/20.6, @134 14.4/18.9; 803 k @1568 42.3/22.4, @196
+//   21.0/19.6; 2.4 M @582 53/33, @73 35/43, @9 36/48; 4.4 M @134 79/68, @17 56/73; 19 M
+//   @582 410/251, @73 235/250, @9 248/282; 153 M @73 1530/1460.
 constexpr int SORT_T = 256;
-constexpr int64_t SORT_FEW = 1 << 20;
+
+inline bool by_chunks(int64_t P, int n, bool sorted)
+{
+    const int64_t nt = n / TILE, keys = 8 * nt * nt * nt;
+    if (P >= (sorted ? 1 << 26 : 1 << 20)) return true;
+    return P >= 1 << 16 && P >= (sorted && P < 1 << 20 ? 640 : 128) * keys;
+}
 
 __global__ __launch_bounds__(SORT_T) void k_sort_count(const float *__restrict__ x, int64_t P, int n, int *cnt)
 {
@@ -406,15 +426,16 @@ hipError_t launch_sort_verify(const int *cursor, const int *koff, int64_t K, int
     return hipGetLastError();
 }
 
-hipError_t launch_sort_count(const float *x, int64_t P, int n, int *cnt, hipStream_t s)
+hipError_t launch_sort_count(const float *x, int64_t P, int n, bool sorted, int *cnt, hipStream_t s)
 {
-    const int64_t ch = P < SORT_FEW ? SORT_T : WG_R * SORT_T, nb = (P + ch - 1) / ch;
+    const bool chunks = by_chunks(P, n, sorted);
+    const int64_t ch = chunks ? WG_R * SORT_T : SORT_T, nb = (P + ch - 1) / ch;
     if (nb > 0x7fffffff) return hipErrorInvalidValue;
     const dim3 grid((unsigned)(nb > 0 ? nb : 1));
-    if (P < SORT_FEW)
-        hipLaunchKernelGGL(k_sort_count, grid, dim3(SORT_T), 0, s, x, P, n, cnt);
-    else
+    if (chunks)
         hipLaunchKernelGGL(k_sort_count_wg, grid, dim3(SORT_T), 0, s, x, P, n, cnt);
+    else
+        hipLaunchKernelGGL(k_sort_count, grid, dim3(SORT_T), 0, s, x, P, n, cnt);
     return hipGetLastError();
 }
 
@@ -441,17 +462,18 @@ hipError_t launch_sort_scatter(const float *x, const float *p, const uint8_t *ta
                                const int64_t *seg_off, int n, int *cursor, float4 *xs, Mom3 *ps,
                                const uint32_t *ids_in, uint32_t *ids_out, hipStream_t s)
 {
-    const int64_t ch = P < SORT_FEW ? SORT_T : WG_R * SORT_T, nb = (P + ch - 1) / ch;
+    const bool chunks = by_chunks(P, n, tag_in != nullptr);
+    const int64_t ch = chunks ? WG_R * SORT_T : SORT_T, nb = (P + ch - 1) / ch;
     if (nb > 0x7fffffff || (ids_in && !ids_out)) return hipErrorInvalidValue;
     const dim3 grid((unsigned)(nb > 0 ? nb : 1));
     const int hi = ids_in ? 1 : (ids_out ? 2 : 0);
 #define SCATTER_K(HP, HT, HI)                                                                         \
     {                                                                                                \
-        if (P < SORT_FEW)                                                                            \
-            hipLaunchKernelGGL((k_sort_scatter<HP, HT, HI>), grid, dim3(SORT_T), 0, s, x, p, tag_in, P, nseg, seg_off, \
+        if (chunks)                                                                                  \
+            hipLaunchKernelGGL((k_sort_scatter_wg<HP, HT, HI>), grid, dim3(SORT_T), 0, s, x, p, tag_in, P, nseg, seg_off, \
                                n, cursor, xs, ps, ids_in, ids_out);                                  \
         else                                                                                         \
-            hipLaunchKernelGGL((k_sort_scatter_wg<HP, HT, HI>), grid, dim3(SORT_T), 0, s, x, p, tag_in, P, nseg, seg_off, \
+            hipLaunchKernelGGL((k_sort_scatter<HP, HT, HI>), grid, dim3(SORT_T), 0, s, x, p, tag_in, P, nseg, seg_off, \
                                n, cursor, xs, ps, ids_in, ids_out);                                  \
     }
 #define SCATTER_I(HP, HT)                                                                             \
