@@ -279,6 +279,26 @@ pm_status check_guards(pm_ctx *c, hipStream_t s)
 
 bool sorting_on(const pm_ctx *c) { return c->nkeys > 0 && !(c->cfg.flags & PM_FLAG_NO_SORT); }
 
+// Whether the density of segments [lo, hi) is painted by tile, from records
+// sorted into the workspace, or with global atomics.  By tile where the
+// configuration can, but for few particles or few tiles.  One launch of atomics
+// paints a segment (in sorted order all of them); the sort and the paint are five
+// launches.  pm_density by tile / with atomics, us: 512 particles on 32^3 33/28, on
+// 64^3 36/29, on 128^3 43/38, 4096 35/29 on 64^3, 41/39 on 128^3; but 33 k on 128^3
+// 41/46, 4096 on 256^3 62/87.  A 32^3 mesh has eight tiles, that is eight workgroups,
+// for all its particles, and atomics cost it 5 us more for each segment: 33 k
+// particles in one segment 48/34, 37 k in eleven 51/85, 69 k 72/89, 319 k 198/157;
+// in sorted order, where its sort is fast and atomics meet on a cell, 69 k 61/51,
+// 319 k 139/159.
+bool tile_paint(const pm_ctx *c, int lo, int hi)
+{
+    if (c->nkeys == 0) return false;
+    const int64_t P = c->seg_off[hi] - c->seg_off[lo], segments = c->permuted ? 1 : hi - lo;
+    if (segments == 1 && P <= 4096 && c->n <= 128) return false;
+    if (c->n >= 64) return true;
+    return c->permuted ? P >= 3 << 16 : P < (segments - 1) << 14;
+}
+
 // Whether particles in the caller's order are read out by tile.  A tile costs
 // the staging of its 59 KB of the force meshes however few its particles (500 us
 // at 512^3, 3560 at 1024^3); a gather costs each particle its twelve rows, which
@@ -289,10 +309,11 @@ bool sorting_on(const pm_ctx *c) { return c->nkeys > 0 && !(c->cfg.flags & PM_FL
 // 512^3 with 64 CDM particles a tile 553 and 242, with 64 and 9 neutrinos 577 and
 // 347, with 8 and 70 785 and 859, with 512 and 70 1098 and 1532; 256^3 with 64 61 and 32,
 // with 8 and 70 91 and 102; 1024^3 with 64 and 9 4362 and 2490.  Below 256^3 there are
-// too few tiles for their cost to show (128^3 with 64 17.4 and 15.5, 64^3 13.2 and 14.8).
+// too few tiles for their cost to show (128^3 with 64 17.4 and 15.5, 64^3 13.2 and 14.8),
+// and a density painted with atomics leaves no records to read out.
 bool tile_readout(const pm_ctx *c)
 {
-    return c->nkeys > 0 && (c->logn < 8 || c->nc + 3 * c->nn >= 160 * (c->nkeys / 8));
+    return tile_paint(c, 0, c->nseg) && (c->logn < 8 || c->nc + 3 * c->nn >= 160 * (c->nkeys / 8));
 }
 
 // Force meshes (planes ps_f, components comp apart) read out at x for
@@ -501,8 +522,9 @@ pm_status tile_records(pm_ctx *c, const float *x, const float *v, bool index, hi
 }
 
 // Density contrast of every segment of x for a solve: by tile into the Q
-// region as float32 (*delta set) where the configuration can tile-sort, else
-// with global atomics into the int64 mesh Q (*delta null).  The cells are the
+// region as float32 (*delta set) where records are asked for or tile_paint says
+// so, with global atomics into the int64 mesh Q (*delta null) otherwise and
+// always where the configuration cannot tile-sort.  The cells are the
 // same integers either way.  A tile paint moves 20 bytes per particle and 4
 // per cell instead of eight scattered 8-byte atomics per particle, which the
 // eight L2s cannot combine: 19 M particles on 512^3 take 0.95 ms (count, scan,
@@ -511,7 +533,7 @@ pm_status tile_records(pm_ctx *c, const float *x, const float *v, bool index, hi
 pm_status paint_density(pm_ctx *c, const float *x, const float *v, bool index, hipStream_t s, const float **delta)
 {
     *delta = nullptr;
-    if (c->nkeys == 0) {
+    if (c->nkeys == 0 || !(v || index || tile_paint(c, 0, c->nseg))) {
         LAUNCH(pm::K_FILL, pm::launch_fill_i64(c->ws.q, (int64_t)c->n * c->n * c->n, s));
         return paint_atomic(c, x, 0, c->nseg, c->ws.q, s);
     }
@@ -1335,11 +1357,13 @@ pm_status pm_power(pm_ctx *c, const float *x, int32_t a_lo, int32_t a_hi, int32_
         return (double)M / tot;
     };
     // density contrast of one segment range: by tile from one sort of the
-    // records where the configuration can, else with global atomics
+    // density contrast of one segment range: by tile from one sort of the
+    // records, or with global atomics
     const int64_t cs = (int64_t)n * n * pm::half_pad(n);
     float2 *SA = c->ws.f, *SB = c->ws.f + cs;
     float *delta = reinterpret_cast<float *>(c->ws.f + 2 * cs);
-    const bool tiles = c->nkeys > 0;
+    const bool cross = a_lo != b_lo || a_hi != b_hi;
+    const bool tiles = tile_paint(c, a_lo, a_hi) || (cross && tile_paint(c, b_lo, b_hi));
     auto field = [&](int lo, int hi, float2 *S) -> pm_status {
         if (tiles) {
             LAUNCH(pm::K_PAINT, pm::launch_paint_tiles_delta(c->ws.xs, c->ws.koff, c->ws.quanta, c->nseg, lo, hi, n,
@@ -1355,7 +1379,6 @@ pm_status pm_power(pm_ctx *c, const float *x, int32_t a_lo, int32_t a_hi, int32_
     };
     pm_status st = tiles ? tile_records(c, x, nullptr, false, s) : PM_OK;
     if (st == PM_OK) st = field(a_lo, a_hi, SA);
-    const bool cross = a_lo != b_lo || a_hi != b_hi;
     if (st == PM_OK && cross) st = field(b_lo, b_hi, SB);
     if (st == PM_OK) st = power_bins(c, SA, cross ? SB : SA, nbins, compensate, k_mean, pk, n_modes, s);
     return st == PM_OK ? check_guards(c, s) : st;
@@ -1382,7 +1405,7 @@ pm_status pm_density(pm_ctx *c, const float *x, float *delta, void *stream)
     hipStream_t s = S(stream);
     const int64_t M = (int64_t)c->n * c->n * c->n;
     const double qs = ldexp(1.0, -c->cfg.shift);
-    if (c->nkeys > 0) {
+    if (tile_paint(c, 0, c->nseg)) {
         // the tile paint stores 16 bytes at a time: a caller's mesh that is not
         // aligned for it is copied to from the workspace.  No cell is refused
         // here (the flag goes to an unused word).
@@ -1537,11 +1560,12 @@ pm_status pm_learned_loss(pm_ctx *c, const float *th, double a, const float *x, 
     const double M = (double)n2 * n;
     float2 *F = c->ws.f;
     float *Fr = reinterpret_cast<float *>(F);
+    // the gradient paints its cotangent by tile where it can
+    const bool tiles = dth ? c->nkeys > 0 : tile_readout(c);
     const float *delta;
-    st = paint_density(c, x, nullptr, true, s, &delta);
+    st = paint_density(c, x, nullptr, tiles, s, &delta);
     if (st == PM_OK) st = learned_solve(c, th, a, dth != nullptr, s, delta);
     if (st != PM_OK) return st;
-    const bool tiles = c->nkeys > 0;
     if (tiles) {
         // the force error goes to the sorted records' vectors
         LAUNCH(pm::K_FILL, pm::launch_zero_f64(c->ws.net_red, 4 * pm::RED_SLOTS, s));
