@@ -969,8 +969,7 @@ __global__ __launch_bounds__(X0Cfg<N>::T, 2) void k_x0_power(const float2 *srca,
                 if constexpr (CROSS) q = w[s * R2 + l];
                 double val = ((double)p.x * q.x + (double)p.y * q.y) * wgt;
                 if (compensate) val *= win[n0];
-                const int next = __shfl_down(b, 1);
-                bin_runs(hist, b, next, c == C - 1, b >= 0 ? val : 0.0);
+                bin_runs(hist, bin_runs_of(b), b >= 0 ? val : 0.0);
             }
     }
     __syncthreads();

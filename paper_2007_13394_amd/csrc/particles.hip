@@ -563,7 +563,7 @@ __global__ __launch_bounds__(256) void k_power_bin(const float2 *__restrict__ A,
     for (int i = threadIdx.x; i < nbins; i += 256) hist[i] = 0.0;
     if (compensate) window_table(win, n, 256);
     __syncthreads();
-    const int nh = n / 2 + 1, lane = threadIdx.x & 63;
+    const int nh = n / 2 + 1;
     const int64_t m = (int64_t)n * n * nh;
     for (int64_t t0 = (int64_t)blockIdx.x * 256; t0 < m; t0 += (int64_t)gridDim.x * 256) {
         const int64_t t = t0 + threadIdx.x;
@@ -582,8 +582,7 @@ __global__ __launch_bounds__(256) void k_power_bin(const float2 *__restrict__ A,
                 if (compensate) v *= win[n0] * win[n1] * win[n2];
             }
         }
-        const int next = __shfl_down(b, 1);
-        bin_runs(hist, b, next, lane == 63, v);
+        bin_runs(hist, bin_runs_of(b), v);
     }
     __syncthreads();
     for (int i = threadIdx.x; i < nbins; i += 256) partial[(int64_t)blockIdx.x * nbins + i] = hist[i];
@@ -611,9 +610,9 @@ __global__ __launch_bounds__(256) void k_power_geom(int n, int nbins, double kf,
             if (nn == 0 || b >= nbins) b = -1;
             const double w = b >= 0 ? (n2 < n1 ? wr : n1 < n0 ? wr * 0.5 : wr / 3.0) *
                                           ((n2 == 0 || n2 == n / 2) ? 1.0 : 2.0) : 0.0;
-            const int next = __shfl_down(b, 1);
-            bin_runs(hist, b, next, lane == 63, w);
-            bin_runs(hist + nbins, b, next, lane == 63, w * (kf * sqrt((double)nn)));
+            const BinRuns run = bin_runs_of(b);
+            bin_runs(hist, run, w);
+            bin_runs(hist + nbins, run, w * (kf * sqrt((double)nn)));
         }
     }
     __syncthreads();
