@@ -98,6 +98,19 @@ __device__ __forceinline__ void hash_clear(int *keys, int *cnt)
     }
 }
 
+// One of a wavefront's runs of neighbouring lanes with one key: its first lane, and
+// the lane behind its last.
+struct KeyRun {
+    int first, end;
+};
+__device__ __forceinline__ KeyRun key_run(int key)
+{
+    const int lane = threadIdx.x & 63, below = __shfl_up(key, 1);
+    const uint64_t starts = __ballot(lane == 0 || below != key), upto = ~0ull >> (63 - lane);
+    const uint64_t above = starts & ~upto;
+    return KeyRun{63 - __clzll((long long)(starts & upto)), above ? __ffsll((unsigned long long)above) - 1 : 64};
+}
+
 __global__ __launch_bounds__(SORT_T) void k_sort_count_wg(const float *__restrict__ x, int64_t P, int n, int *cnt)
 {
     __shared__ int hkey[HASH], hcnt[HASH];
@@ -115,7 +128,9 @@ __global__ __launch_bounds__(SORT_T) void k_sort_count_wg(const float *__restric
 #pragma unroll
     for (int r = 0; r < WG_R; r++) {
         const bool live = c0 + threadIdx.x + r * SORT_T < P;
-        if (live) atomicAdd(hcnt + hash_slot(hkey, tile_key(a0[r], a1[r], a2[r], n)), 1);
+        const int key = live ? tile_key(a0[r], a1[r], a2[r], n) : -1;
+        const KeyRun run = key_run(key);
+        if (live && (int)(threadIdx.x & 63) == run.first) atomicAdd(hcnt + hash_slot(hkey, key), run.end - run.first);
     }
     __syncthreads();
     for (int i = threadIdx.x; i < HASH; i += SORT_T)
@@ -348,11 +363,14 @@ __device__ __forceinline__ void scatter_wg(int *hkey, int *hcnt, int64_t c0, con
 #pragma unroll
     for (int r = 0; r < WG_R; r++) {
         const bool live = c0 + threadIdx.x + r * SORT_T < P;
-        at[r] = 0;
-        if (live) {
-            const int h = hash_slot(hkey, tile_key(a0[r], a1[r], a2[r], n));
-            at[r] = (h << 16) | atomicAdd(hcnt + h, 1);
+        const int key = live ? tile_key(a0[r], a1[r], a2[r], n) : -1, lane = threadIdx.x & 63;
+        const KeyRun run = key_run(key);
+        int slot = 0;
+        if (live && lane == run.first) {
+            const int h = hash_slot(hkey, key);
+            slot = (h << 16) | atomicAdd(hcnt + h, run.end - run.first);
         }
+        at[r] = __shfl(slot, run.first) + lane - run.first;
     }
     if constexpr (HP) {
 #pragma unroll
