@@ -197,7 +197,7 @@ double growth_G(const Ctx &c, double a)
 // sigma8^2 / int dlnk k^(3 + n_s) T^2 W^2(8 k) / (2 pi^2) over k = 1e-6 .. 1e3,
 // W the top-hat window.  16-point Gauss-Legendre panels in ln k: 16 up to
 // k = 1, then one per unit of k (2.5 periods of W^2) up to 200 and one per four
-// units beyond, where 1e-8 of the integral is left.  6.8e3 evaluations agree
+// units beyond, where 1e-8 of the integral is left.  6640 evaluations agree
 // with 4e6 Simpson intervals to a few 1e-12 (0.3 ms; 4e5 intervals took 22 ms).
 double pk_amplitude(const Ctx &c)
 {

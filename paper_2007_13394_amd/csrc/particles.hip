@@ -620,7 +620,7 @@ __global__ __launch_bounds__(256) void k_power_geom(int n, int nbins, double kf,
 }
 
 // out[i] = the sum of ne-long partials over np workgroups, each value's 128
-// strided sums added in order (deterministic).  Few workgroups read up to 8 MB:
+// strided sums added in order (deterministic).  Few workgroups read up to 16 MB:
 // 1024 threads each for the loads in flight (256: 29 us for 4096 partials of 256,
 // now 10).
 constexpr int POWER_RED_G = 128;

@@ -34,26 +34,29 @@ inline unsigned grid_for(int64_t n, int block, int64_t cap = 65536LL * 16)
 //
 // Two forms: one particle per thread, grouped by key within a wavefront, and
 // chunks of WG_R per thread, grouped within the workgroup.  Chunks bring a
-// key's atomics down and cost a chain of eight rounds, so they pay where atomics
-// to one key queue up: with many particles per key, sooner in canonical order, where
-// a key's particles lie scattered over the launch.  Wavefront form / chunks, us, by
-// particles and @ particles per key.
-//   count and scatter, canonical order: chunks from 2^16 with 128 per key and
-//   from 2^20.  9 k @134 14/25; 69 k @134 36/31, @17 25/29; 298 k @582 85/47, @73
-//   37/36, @9 33/38; 549 k @1072 213/89, @134 80/62, @17 65/62; 803 k @196 108/83, @25
-//   85/87; 2.4 M @582 161/122, @73 143/115; 19 M @582 998/680, @73 1055/779.
-//   scatter of a step: chunks from 2^16 with 640 per key, from 2^20 with 128 and
-//   from 2^26.  69 k @1072 17.3/15.0, @134 7.8/15.2; 298 k @582 14.2/16.0; 406 k @792
-//   21.0/18.2; 549 k @1072 29.4/20.6, @134 14.4/18.9; 803 k @1568 42.3/22.4, @196
-//   21.0/19.6; 2.4 M @582 53/33, @73 35/43, @9 36/48; 4.4 M @134 79/68, @17 56/73; 19 M
-//   @582 410/251, @73 235/250, @9 248/282; 153 M @73 1530/1460.
+// key's atomics down and cost a chain of eight rounds (15 us at least), so they pay
+// where atomics to one key queue up: with many particles per key, sooner in
+// canonical order, where a key's particles lie scattered over the launch.
+// Wavefront form / chunks, us, by particles and @ particles per key.
+//   count and scatter, canonical order: chunks from 2^18 with 512 per key and from
+//   2^20.  Evolved state (initial conditions): 69 k @134 36/32 (13/27); 267 k @521
+//   64/44 (23/28); 298 k @582 85/49 (24/30), @73 37/37 (17/29); 549 k @1072 214/90
+//   (37/36), @134 79/61 (23/31), @17 65/63; 803 k @196 108/83, @25 84/91; 2.4 M @582
+//   158/125 (40/53), @73 141/114 (47/60); 19 M @582 970/684 (285/258), @73 1059/768
+//   (339/298).
+//   scatter of a step: chunks from 2^18 with 640 per key, from 2^20 with 128 and
+//   from 2^26.  69 k @1072 17.1/15.0, @134 7.8/15.3; 298 k @582 14.2/15.8; 406 k @792
+//   21.8/18.0; 549 k @1072 29.8/20.2, @134 15.0/18.8; 803 k @1568 44.3/22.8, @196
+//   21.5/19.8; 2.4 M @582 58/29, @73 35/40, @9 32/44; 4.4 M @134 80/64, @17 58/72; 19 M
+//   @582 410/244, @73 237/247, @9 242/278; 153 M @73 1530/1460.
 constexpr int SORT_T = 256;
 
 inline bool by_chunks(int64_t P, int n, bool sorted)
 {
     const int64_t nt = n / TILE, keys = 8 * nt * nt * nt;
     if (P >= (sorted ? 1 << 26 : 1 << 20)) return true;
-    return P >= 1 << 16 && P >= (sorted && P < 1 << 20 ? 640 : 128) * keys;
+    const int64_t per_key = !sorted ? 512 : P < 1 << 20 ? 640 : 128;
+    return P >= 1 << 18 && P >= per_key * keys;
 }
 
 __global__ __launch_bounds__(SORT_T) void k_sort_count(const float *__restrict__ x, int64_t P, int n, int *cnt)

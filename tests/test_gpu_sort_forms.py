@@ -1,6 +1,6 @@
 """The two forms of the tile sort's passes on both sides of the lines between them
-on a 64^3 mesh (512 keys): 2^16 particles in canonical order, 640 per key in sorted
-order; and at 128^3 (4096 keys) sorted ones between 128 and 640 per key on both sides
+on a 64^3 mesh (512 keys): 2^18 particles, 512 per key, in canonical order, 640 per key
+in sorted order; and at 128^3 (4096 keys) sorted ones between 128 and 640 per key on both sides
 of 2^20, at 256^3 (32768 keys) fewer than 128.  The checks are those of
 test_gpu_sort_sizes."""
 import pytest
@@ -14,8 +14,8 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("clustered", [False, True])
 @pytest.mark.parametrize("over", [
-    dict(n_mesh=64, n_cdm=32, n_sites=4, n_shell=7, n_fib=36),     # P = 2^16 - 64
-    dict(n_mesh=64, n_cdm=32, n_sites=4, n_shell=27, n_fib=9),     # P = 2^16 + 64
+    dict(n_mesh=64, n_cdm=32, n_sites=4, n_shell=49, n_fib=36),    # P = 2^18 - 448
+    dict(n_mesh=64, n_cdm=64, n_sites=1, n_shell=3, n_fib=1),      # P = 2^18 + 9
     dict(n_mesh=64, n_cdm=64, n_sites=4, n_shell=33, n_fib=15),    # P = 640 x 512 - 64
     dict(n_mesh=64, n_cdm=64, n_sites=4, n_shell=41, n_fib=12),    # P = 640 x 512 + 64
     dict(n_mesh=128, n_cdm=64, n_sites=4, n_shell=63, n_fib=98),   # P = 2^20 + 7872
