@@ -74,7 +74,9 @@ enum {
     PM_FLAG_NO_GUARDS = 2, /* skip the end-of-call device flag check (no host sync) */
     PM_FLAG_NO_SORT = 4,   /* keep particles in segment order (pm_step then sorts
                               records into the workspace on every call and reads
-                              the force out by tile through their indices) */
+                              the force out by tile through their indices; few or
+                              sparse particles are painted with global atomics and
+                              gather it) */
     PM_FLAG_LEARNED = 8,   /* reserve the workspace of the learned force correction
                               (pm_learned_*; N a power of two >= 16) */
     PM_FLAG_NU_PSEUDO = 16, /* pseudo-random neutrino velocities, one particle per
